@@ -22,6 +22,8 @@
  *     (-1,0), (0,-1), e_5..e_8 = (1,1), (-1,1), (-1,-1), (1,-1).
  *   - Device buffers are owned by the caller (allocated e.g. by PyTorch) and must stay
  *     valid until fdlbm_destroy.  The library never allocates or frees device memory.
+ *   - A step call of several steps may take three or five of them in one launch; the state
+ *     after it, its buffer and its bits are those of as many single steps.
  *   - All work is issued on the HIP stream given at creation (NULL = the default stream).
  *     Steps return without synchronising; fdlbm_get_state, fdlbm_get_populations,
  *     fdlbm_diagnostics and fdlbm_mode_projection synchronise that stream.
@@ -80,7 +82,8 @@ typedef struct fdlbm_params {
                          * (1/s_xx - 1/2)(1/s_q - 1/2) = 1/6 (section 3-b)                   */
     double force_x, force_y; /* uniform body force per node and step, Strang-split (section 1) */
     int32_t kernel;     /* FDLBM_KERNEL_*                                                     */
-    int32_t tile_rows;  /* sweep kernel: rows per wavefront, 2..1024 (0 or 1 = choose); tuning */
+    int32_t tile_rows;  /* sweep kernel: rows per wavefront of a launch that takes one step,
+                         * 2..1024 (0 or 1 = choose); tuning                                  */
     int32_t check_every;/* > 0: fdlbm_step / mrt_step scan the state for non-finite values
                          * every check_every steps and return FDLBM_EUNSTABLE if one is found
                          * (this synchronises the stream at each check)                       */

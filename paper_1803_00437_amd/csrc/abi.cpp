@@ -1,6 +1,7 @@
 // C ABI of the FD-LBM / MRT D2Q9 library (declarations and contracts in include/fdlbm.h).
 // Host code only: validation, scratch layout, stream-ordered launches of the kernels in
 // the other translation units, and FP64 host <-> device staging.
+#include <algorithm>
 #include <cmath>
 #include <vector>
 #include <cstdio>
@@ -390,15 +391,43 @@ static int run_diag(fdlbm_ctx *c, double out[DIAG_SLOTS])
     return FDLBM_OK;
 }
 
+// How `n` consecutive steps are dealt to launches of five, three or one steps.  A launch reads one
+// state buffer and writes the other whatever its steps, and the current state has to lie in
+// state_a after an even number of steps: launches of an odd number of steps keep that.  One or
+// two fives give way where that leaves no single steps.
+struct Launches {
+    int64_t fives = 0, threes = 0, ones = 0;
+};
+static Launches deal_steps(int64_t n, int most)
+{
+    Launches l;
+    if (most >= 5) {
+        l.fives = n / 5;
+        for (int64_t back = 0; back <= 2 && back <= n / 5; ++back)
+            if ((n % 5 + 5 * back) % 3 == 0) {
+                l.fives -= back;
+                break;
+            }
+        n -= 5 * l.fives;
+    }
+    if (most >= 3) l.threes = n / 3;
+    l.ones = n - 3 * l.threes;
+    return l;
+}
+
 static int advance(fdlbm_ctx *c, int64_t nsteps)
 {
     HIPCHK(hipSetDevice(c->device), "hipSetDevice");
     const bool fd = three_words(c->p.scheme);
     const bool ref = uses_reference(c->p);
+    const bool disk = c->p.bc == FDLBM_BC_DISK;
     FdArgs fa = fd_args(c->p);
     const MrtArgs ma{c->p.nx, c->p.ny, c->p.bc == FDLBM_BC_WALLS_Y ? 1 : 0, c->p.dtype, c->p.s_e, c->p.s_xx, c->s_q,
                      c->p.s_eps, c->p.force_x, c->p.force_y, c->p.kernel, c->p.tile_rows, wall_xi(c->p)};
-    for (int64_t s = 0; s < nsteps; ++s) {
+    // the disk's wall acts between the steps
+    const int most = disk || fd ? 1 : mrt_max_fused(ma);
+    // one launch of k steps from the current buffer into the other one
+    auto take = [&](int k) -> int {
         // stochastic rounding draws fresh bits every step, reproducibly from the step count
         fa.seed = pcg_hash(uint32_t(c->steps));
         void *src = c->buf[c->cur], *dst = c->buf[c->cur ^ 1];
@@ -406,13 +435,13 @@ static int advance(fdlbm_ctx *c, int64_t nsteps)
         // every rest node after the state was set or under a body force (which moves the
         // rest nodes too), else only the ring the previous step could reach
         const bool disk_full = c->disk_full || c->p.force_x != 0.0 || c->p.force_y != 0.0;
-        if (c->p.bc == FDLBM_BC_DISK && fd) {
+        if (disk && fd) {
             HIPCHK(launch_disk_fill(c->disk, c->p.dtype, src, disk_full, c->stream), "disk fill launch");
             c->disk_full = false;
         }
         hipError_t e;
         if (!fd)
-            e = launch_mrt(ma, src, dst, c->stream);
+            e = launch_mrt(ma, k, src, dst, c->stream);
         else if (ref)
             e = launch_fd_reference(fa, src, dst, c->scratch + c->L.fstar, c->stream);
         else
@@ -424,13 +453,25 @@ static int advance(fdlbm_ctx *c, int64_t nsteps)
         // MRT in the disk: the wall acts on the streamed populations, after the step; the
         // solid nodes the links reach go back to rest (every solid node after the state was
         // set or under a body force)
-        if (c->p.bc == FDLBM_BC_DISK && !fd) {
+        if (disk && !fd) {
             HIPCHK(launch_mrt_disk(c->mdisk, c->p.dtype, dst, disk_full, c->stream), "mrt disk launch");
             c->disk_full = false;
         }
         c->cur ^= 1;
-        ++c->steps;
-        if (c->p.check_every > 0 && c->steps % c->p.check_every == 0) {
+        c->steps += k;
+        return FDLBM_OK;
+    };
+    for (int64_t left = nsteps; left > 0;) {
+        // up to the next check of the state
+        const int64_t every = c->p.check_every;
+        const int64_t n = every > 0 ? std::min<int64_t>(left, every - c->steps % every) : left;
+        const Launches l = deal_steps(n, most);
+        for (int64_t i = 0; i < l.fives + l.threes + l.ones; ++i) {
+            const int rc = take(i < l.fives ? 5 : i < l.fives + l.threes ? 3 : 1);
+            if (rc) return rc;
+        }
+        left -= n;
+        if (every > 0 && c->steps % every == 0) {
             double d[DIAG_SLOTS];
             int rc = run_diag(c, d);
             if (rc) return rc;
@@ -546,7 +587,7 @@ int fdlbm_autotune(fdlbm_ctx *c, int32_t reps, int32_t *out_lane_cols, int32_t *
             if (fd) return launch_fd_sweep(fa, sh.rows, sh.cols, src, dst, c->stream);
             const MrtArgs ma{c->p.nx, c->p.ny, c->p.bc == FDLBM_BC_WALLS_Y ? 1 : 0, c->p.dtype, c->p.s_e, c->p.s_xx, c->s_q,
                              c->p.s_eps, c->p.force_x, c->p.force_y, c->p.kernel, sh.rows, wall_xi(c->p)};
-            return launch_mrt(ma, src, dst, c->stream);
+            return launch_mrt(ma, 1, src, dst, c->stream);
         };
         Shape best{0, 0};
         float best_ms = 0.0f;

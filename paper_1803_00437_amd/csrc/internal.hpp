@@ -133,7 +133,9 @@ struct MrtDisk {
 hipError_t launch_mrt_disk(const MrtDisk &d, int dtype, void *pop, bool full, hipStream_t s);
 
 // MRT D2Q9 stream-collide (push) step.
-hipError_t launch_mrt(const MrtArgs &a, const void *src, void *dst, hipStream_t s);
+// `steps` consecutive steps in one launch, 1 .. mrt_max_fused(a)
+int mrt_max_fused(const MrtArgs &a);
+hipError_t launch_mrt(const MrtArgs &a, int steps, const void *src, void *dst, hipStream_t s);
 
 // Conversions between host-staged FP64 planes and device storage: element by element (the
 // D3Q19 state, the batch modes), and row by row between nf FP64 planes and the

@@ -3,14 +3,15 @@
 //
 // Storage: the nine deviations f_k - w_k from the rest populations, row-interleaved (row j
 // of population k at element (9 j + k) nx, pop_elem): the nine rows a node row reads are
-// adjacent in memory, and so are the rows it writes.  Two kernels:
-// one thread per node (mrt_kernel), and the vectorised sweep over lane groups of columns
-// (mrt_sweep_kernel, the default).  Each relaxes the non-conserved moments of a node and
+// adjacent in memory, and so are the rows it writes.  Three kernels: one thread per node
+// (mrt_kernel, the reference), and over lane groups of columns the fused sweep
+// (mrt_fused_kernel, the default: one, three or five steps per launch) and the sweep for walls
+// at a general distance (mrt_xi_kernel).  Each relaxes the non-conserved moments of a node and
 // pushes f*_k to x + e_k in the other buffer.  A population whose destination lies beyond
 // a wall returns with the opposite velocity: halfway bounce-back (the wall half-way
 // between the last fluid row and the next one, section 3-c), or the interpolated
-// bounce-back of Bouzidi et al. for a wall at another distance xi, in both kernels (they
-// agree bit for bit).  Algorithmic traffic: 9 values read + 9 written per node.
+// bounce-back of Bouzidi et al. for a wall at another distance xi (all kernels agree bit for
+// bit).  Traffic: 9 values read + 9 written per node and launch.
 #include "fd_sweep_body.hpp"
 #include "fdlbm_device.hpp"
 #include "internal.hpp"
@@ -201,7 +202,7 @@ __global__ void __launch_bounds__(256) mrt_kernel(const T *__restrict__ in, T *_
     }
 }
 
-// Vectorised MRT step.  A wavefront owns 64*CPL consecutive columns (CPL per lane, one
+// Walls at a distance xi, one step per launch.  A wavefront owns 64*CPL consecutive columns (CPL per lane, one
 // aligned vector access per population row) of R rows.  After the collision, the
 // populations moving along +x / -x are shifted by one column across lanes with DPP
 // whole-wave shifts, so every store is an aligned vector too; the outermost lane on each
@@ -215,16 +216,14 @@ __global__ void __launch_bounds__(256) mrt_kernel(const T *__restrict__ in, T *_
 // prefetch past the last row use an offset beyond the row and are dropped, so every row
 // issues the same memory operations without branches.
 //
-// WALL: 0 periodic in y; 1 walls half-way between rows (halfway bounce-back); 2 walls at a
-// distance xi (interpolated bounce-back, the same expressions as mrt_kernel; for xi < 1/2
+// The bounce-back is interpolated with the same expressions as in mrt_kernel; for xi < 1/2
 // the row next to the wall row is loaded and collided once more for f*_k(x - e_k), the
-// populations at x - e_k coming from the neighbouring lane with the same DPP shifts).
-template <typename T, int CPL, int WALL>
-__global__ void __launch_bounds__(256) mrt_sweep_kernel(const T *__restrict__ in, T *__restrict__ out, int nx, int ny,
+// populations at x - e_k coming from the neighbouring lane with the same DPP shifts.
+template <typename T, int CPL>
+__global__ void __launch_bounds__(256) mrt_xi_kernel(const T *__restrict__ in, T *__restrict__ out, int nx, int ny,
                                                         int rows, int strips_x, int ntiles,
                                                         MrtCoef<typename Storage<T>::C> k, typename Storage<T>::C xi)
 {
-    constexpr bool WALLS = WALL != 0;
     using C = typename Storage<T>::C;
     using namespace sweep;
     constexpr int S = 64 * CPL - 2 * CPL;  // stored columns per strip
@@ -262,14 +261,14 @@ __global__ void __launch_bounds__(256) mrt_sweep_kernel(const T *__restrict__ in
     // populations returning from a wall into this row: kq leaves along (ex, ey) (ey = +1 at
     // the top wall, -1 at the bottom one) and returns as kb; ynb is the row behind the node
     auto bounce = [&](const C(&f)[CPL][9], int kq, int kb, int ex, int ynb, Group<T, CPL> &b) {
-        if (WALL == 1 || xi == C(0.5)) {
+        if (xi == C(0.5)) {  // a distance that rounds to 1/2 in the arithmetic type
 #pragma unroll
             for (int c = 0; c < CPL; ++c) b.v[c] = Storage<T>::store(f[c][kq]);
         } else if (xi > C(0.5)) {
 #pragma unroll
             for (int c = 0; c < CPL; ++c)
                 b.v[c] = Storage<T>::store(f[c][kq] / (C(2) * xi) + (C(2) * xi - C(1)) / (C(2) * xi) * f[c][kb]);
-        } else if constexpr (WALL == 2) {
+        } else {
             C h[CPL][9];
             collide_row(ynb, h);
             // f*_kq at x - e_kq: column - ex, i.e. from the left for ex = +1, the right for -1
@@ -292,14 +291,10 @@ __global__ void __launch_bounds__(256) mrt_sweep_kernel(const T *__restrict__ in
             for (int c = 0; c < CPL; ++c) f[c][q] = Storage<T>::load(cur[q].v[c]);
 #pragma unroll
         for (int c = 0; c < CPL; ++c) collide<C>(f[c], k);
-        // destination rows (wave-uniform); with walls a population leaving the channel
+        // destination rows (wave-uniform); a population leaving the channel
         // returns to its own node with the opposite velocity
-        int yp = y + 1, ym = y - 1;
-        const bool top_wall = WALLS && yp == ny, bottom_wall = WALLS && ym < 0;
-        if (!WALLS) {
-            if (yp == ny) yp = 0;
-            if (ym < 0) ym = ny - 1;
-        }
+        const int yp = y + 1, ym = y - 1;
+        const bool top_wall = yp == ny, bottom_wall = ym < 0;
         Group<T, CPL> g[9];
         // velocities (0,0), (0,+1), (0,-1) keep their column
 #pragma unroll
@@ -363,6 +358,205 @@ __global__ void __launch_bounds__(256) mrt_sweep_kernel(const T *__restrict__ in
     }
 }
 
+// MRT steps: K time steps in one pass over memory (K = 1, 3 or 5).  One step moves 18 words per node
+// and keeps the vector units 24 % busy; here a wavefront reads a row once, takes it through K
+// stages it holds on chip and writes the populations of K steps later.
+//
+// A wavefront owns a strip of 64*CPL columns (CPL per lane) for R output rows and walks up the rows,
+// one input row per tick, the next row's nine loads in flight.  At tick t stage s collides row
+// ya + t - s.  Streaming between stages needs the rows on both sides: stage s keeps, of the row it
+// collided last, the populations that stay in that row (0, 1, 3) and those on their way up (2, 5,
+// 6; also the row's before), already shifted along x with DPP whole-wave shifts; the next row it
+// collides brings the three that come down, and the row below it enters stage s + 1.  The last stage pushes, as the one-step kernel does.  Every
+// stage widens the input by one row and one column on each side: R + 2 (K - 1) rows are read for
+// R written (the rows beyond are collided again by the neighbouring wavefronts, from the same
+// values in the same order, so every node keeps its bits), and the K columns each side fit in the
+// halo lanes of the strip (K columns rounded up to whole lanes).
+//
+// Walls half-way between rows (xi = 1/2): a bounced population stays in its row, so at the bottom
+// row the three "from below" are that row's own downward ones, and at the top row the three on
+// their way up wait for the next tick as that row's downward ones.
+//
+// What bounds it (8192^2 FP32): one step moved 18 words per node and took 866 us; five take 5 x 234 us,
+// 88 vector instructions per node and step, near the issue rate.  What a stage keeps is 9 CPL
+// registers; with every stage in registers three steps spilled (349 us per step against 340), so
+// the first one or two stages stay there and the others in LDS (9 KB per stage and wavefront: two
+// blocks of four wavefronts fit a compute unit up to two such stages).
+template <int K> constexpr int mrt_reg_stages() { return K > 4 ? 2 : 1; }
+template <typename T, int CPL, int K> struct MrtStrip {
+    static constexpr int P = (K + CPL - 1) / CPL;  // halo lanes on each side
+    static constexpr int S = (64 - 2 * P) * CPL;   // stored columns
+};
+
+template <typename T, int CPL, int AM, int K, bool WALLS>
+__global__ void __launch_bounds__(256, K > 1 ? 2 : 1) mrt_fused_kernel(const T *__restrict__ in, T *__restrict__ out, int nx, int ny,
+                                                        int rows, int strips_x, int ntiles,
+                                                        MrtCoef<typename Storage<T>::C> k)
+{
+    using C = typename Storage<T>::C;
+    using namespace sweep;
+    using G = MrtStrip<T, CPL, K>;
+    const int lane = threadIdx.x & 63;
+    const int tile = blockIdx.x * 4 + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    if (tile >= ntiles) return;  // uniform over the wavefront
+    const int band = tile / strips_x, sx = tile - band * strips_x;
+    // element-aligned accesses: the last strip ends at column nx - 1 (see sweep_tile)
+    const bool shift_last = AM == AM_UNAL && sx == strips_x - 1 && nx > G::S;
+    const int xl = (shift_last ? nx - G::S : sx * G::S) - G::P * CPL + CPL * lane;
+    const LaneCols<CPL, AM> lc = make_lane_cols<T, CPL, AM>(xl, nx, lane >= G::P && lane < 64 - G::P);
+    const int y0 = band * rows, y1 = min(y0 + rows, ny);
+    // stage s collides rows max(y0 - (K-1-s), 0 with walls) .. min(y1-1 + (K-1-s), ny-1 with walls)
+    const int ya = WALLS ? max(y0 - (K - 1), 0) : y0 - (K - 1);
+    const int yb = WALLS ? min(y1 - 1 + (K - 1), ny - 1) : y1 - 1 + (K - 1);
+    const int nticks = y1 - 1 - ya + K;  // the last stage reaches row y1 - 1 at the last one
+
+    auto load_row = [&](int y, Group<T, CPL>(&g)[9]) {
+        const bool use = y <= yb;
+        int yy = y < 0 ? y + ny : (y >= ny ? y - ny : y);
+        yy = min(max(yy, 0), ny - 1);
+#pragma unroll
+        for (int q = 0; q < 9; ++q) g[q] = row_load<T, CPL, AM>(row_rsrc(in + pop_elem(0, 0, q, nx), yy, 9 * nx, nx), lc, use);
+    };
+    auto put = [&](int q, int y, const C(&v)[CPL]) {
+        Group<T, CPL> g;
+#pragma unroll
+        for (int c = 0; c < CPL; ++c) g.v[c] = Storage<T>::store(v[c]);
+        row_store<T, CPL, AM>(row_rsrc(out + pop_elem(0, 0, q, nx), y, 9 * nx, nx), lc, true, g);
+    };
+
+    // Kept between rows, per stage but the last: slots 0..2 the populations 0, 1, 3 of the row
+    // collided last, 3..5 and 6..8 the 2, 5, 6 of the last two rows (by the row's parity, which is
+    // static in the loop below).  The first KR stages keep them in registers, the others in LDS.
+    constexpr int KR = K - 1 < mrt_reg_stages<K>() ? K - 1 : mrt_reg_stages<K>(), KL = K - 1 - KR;
+    using V = Group<C, CPL>;
+    V reg[KR > 0 ? KR : 1][9];
+    __shared__ V lds[KL > 0 ? 4 : 1][KL > 0 ? KL : 1][9][KL > 0 ? 64 : 1];
+    const int wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    auto keep = [&](int s, int slot, const C(&v)[CPL]) {
+        V g;
+#pragma unroll
+        for (int c = 0; c < CPL; ++c) g.v[c] = v[c];
+        if (s < KR)
+            reg[s < KR ? s : 0][slot] = g;
+        else
+            lds[wv][s < KR ? 0 : s - KR][slot][lane] = g;
+    };
+    auto kept = [&](int s, int slot, C(&v)[CPL]) {
+        const V g = s < KR ? reg[s < KR ? s : 0][slot] : lds[wv][s < KR ? 0 : s - KR][slot][lane];
+#pragma unroll
+        for (int c = 0; c < CPL; ++c) v[c] = g.v[c];
+    };
+#pragma unroll
+    for (int s = 0; s < KR; ++s)
+#pragma unroll
+        for (int q = 0; q < 9; ++q)
+#pragma unroll
+            for (int c = 0; c < CPL; ++c) reg[s][q].v[c] = C(0);
+
+    auto tick = [&](int t, int ph, const Group<T, CPL>(&cur)[9]) {  // ph = t & 1
+        C f[9][CPL];  // the row entering the stage, then its shifted post-collision populations
+#pragma unroll
+        for (int q = 0; q < 9; ++q)
+#pragma unroll
+            for (int c = 0; c < CPL; ++c) f[q][c] = Storage<T>::load(cur[q].v[c]);
+#pragma unroll
+        for (int s = 0; s < K; ++s) {
+            const int y = ya + t - s;  // row of this stage
+            // a stage starts with the first row it needs: the rows before it are not complete
+            if (s > 0 && y < (WALLS ? max(y0 - (K - 1 - s), 0) : y0 - (K - 1 - s))) return;
+#pragma unroll
+            for (int c = 0; c < CPL; ++c) {
+                C p[9];
+#pragma unroll
+                for (int q = 0; q < 9; ++q) p[q] = f[q][c];
+                collide<C>(p, k);
+#pragma unroll
+                for (int q = 0; q < 9; ++q) f[q][c] = p[q];
+            }
+            // populations returning from a wall, unshifted
+            C b[3][CPL];
+            const bool bottom = WALLS && y == 0, top = WALLS && y == ny - 1;
+            if (bottom || top)
+#pragma unroll
+                for (int c = 0; c < CPL; ++c) {
+                    b[0][c] = bottom ? f[4][c] : f[2][c];
+                    b[1][c] = bottom ? f[7][c] : f[5][c];
+                    b[2][c] = bottom ? f[8][c] : f[6][c];
+                }
+            // +x movers (1, 5, 8) arrive from the column on the left, -x movers (3, 6, 7) from
+            // the column on the right
+            const int rq[3] = {1, 5, 8}, lq[3] = {3, 6, 7};
+#pragma unroll
+            for (int i = 0; i < 3; ++i) {
+                const C fl = from_left(f[rq[i]][CPL - 1]), fr = from_right(f[lq[i]][0]);
+#pragma unroll
+                for (int c = CPL - 1; c > 0; --c) f[rq[i]][c] = f[rq[i]][c - 1];
+                f[rq[i]][0] = fl;
+#pragma unroll
+                for (int c = 0; c < CPL - 1; ++c) f[lq[i]][c] = f[lq[i]][c + 1];
+                f[lq[i]][CPL - 1] = fr;
+            }
+            if (s < K - 1) {
+                const int u = 3 + 3 * ((ph + s) & 1), v = 9 - u;  // slots of rows y and y - 2; of row y - 1
+                const int stay[3] = {0, 1, 3}, rising[3] = {2, 5, 6}, falling[3] = {4, 7, 8};
+#pragma unroll
+                for (int i = 0; i < 3; ++i) {
+                    C own[CPL], below[CPL];
+                    kept(s, i, own);
+                    kept(s, u + i, below);
+                    keep(s, i, f[stay[i]]);
+                    if (top)
+                        keep(s, u + i, b[i]);
+                    else
+                        keep(s, u + i, f[rising[i]]);
+                    if (bottom) keep(s, v + i, b[i]);
+                    if (WALLS && y == ny) kept(s, v + i, f[falling[i]]);  // the top row has its own
+#pragma unroll
+                    for (int c = 0; c < CPL; ++c) {
+                        f[stay[i]][c] = own[c];
+                        f[rising[i]][c] = below[c];
+                    }
+                }
+            } else {
+                // the last stage: push (rows y0 .. y1 - 1; the guard above starts it at y0)
+                put(0, y, f[0]);
+                put(1, y, f[1]);
+                put(3, y, f[3]);
+                if (top) {
+                    put(4, y, b[0]);
+                    put(7, y, b[1]);
+                    put(8, y, b[2]);
+                } else {
+                    const int yp = !WALLS && y + 1 == ny ? 0 : y + 1;
+                    put(2, yp, f[2]);
+                    put(5, yp, f[5]);
+                    put(6, yp, f[6]);
+                }
+                if (bottom) {
+                    put(2, y, b[0]);
+                    put(5, y, b[1]);
+                    put(6, y, b[2]);
+                } else {
+                    const int ym = !WALLS && y == 0 ? ny - 1 : y - 1;
+                    put(4, ym, f[4]);
+                    put(7, ym, f[7]);
+                    put(8, ym, f[8]);
+                }
+            }
+        }
+    };
+
+    Group<T, CPL> A[9], B[9];
+    load_row(ya, A);
+    for (int t = 0; t < nticks; t += 2) {
+        load_row(ya + t + 1, B);
+        tick(t, 0, A);
+        if (t + 1 >= nticks) break;
+        load_row(ya + t + 2, A);
+        tick(t + 1, 1, B);
+    }
+}
+
 // Equilibrium populations of host-order FP64 planes (drho, Jx, Jy; node (i, j) at j nx + i),
 // stored row-interleaved; one block row of columns per grid row.
 template <typename T>
@@ -404,36 +598,81 @@ __global__ void __launch_bounds__(256) mrt_moments_kernel(const T *__restrict__ 
         }
 }
 
-template <typename T, int CPL>
-hipError_t run_sweep(const MrtArgs &a, MrtCoef<typename Storage<T>::C> k, const void *src, void *dst, hipStream_t s)
+// Rows per wavefront of a fused launch.  A wavefront of R rows collides R + K - 1 rows per stage on
+// average, and the work is dealt to 1024 SIMDs: the time goes as ceil(wavefronts / 1024) (R + K - 1),
+// whose minimum balances the rows collided twice against a last wave that is nearly empty.
+int fused_rows(int strips_x, int ny, int K)
 {
-    constexpr int S = 64 * CPL - 2 * CPL;
-    const int rows = a.tile_rows > 0 ? a.tile_rows : 1;  // 1 measured best at 8192^2 (1 % over 2)
+    int best = 1;
+    long best_cost = -1;
+    for (int rows = 1; rows <= 128 && rows <= ny; ++rows) {
+        const long waves = (long)strips_x * ((ny + rows - 1) / rows);
+        const long cost = (waves + 1023) / 1024 * (rows + K - 1);
+        if (best_cost < 0 || cost < best_cost) {
+            best_cost = cost;
+            best = rows;
+        }
+    }
+    return best;
+}
+
+template <typename T, int CPL, int AM, int K, bool WALLS>
+hipError_t run_fused(const MrtArgs &a, MrtCoef<typename Storage<T>::C> k, const void *src, void *dst, hipStream_t s)
+{
+    constexpr int S = MrtStrip<T, CPL, K>::S;
     const int strips_x = (a.nx + S - 1) / S;
+    // one step: 1 row per wavefront measured best at 8192^2 (1 % over 2)
+    const int rows = K == 1 ? (a.tile_rows > 0 ? a.tile_rows : 1) : fused_rows(strips_x, a.ny, K);
     const int ntiles = strips_x * ((a.ny + rows - 1) / rows);
-    const int blocks = (ntiles + 3) / 4;
-    using C = typename Storage<T>::C;
-    if (a.walls && a.xi != 0.5)
-        hipLaunchKernelGGL((mrt_sweep_kernel<T, CPL, 2>), blocks, 256, 0, s, static_cast<const T *>(src),
-                           static_cast<T *>(dst), a.nx, a.ny, rows, strips_x, ntiles, k, C(a.xi));
-    else if (a.walls)
-        hipLaunchKernelGGL((mrt_sweep_kernel<T, CPL, 1>), blocks, 256, 0, s, static_cast<const T *>(src),
-                           static_cast<T *>(dst), a.nx, a.ny, rows, strips_x, ntiles, k, C(0.5));
-    else
-        hipLaunchKernelGGL((mrt_sweep_kernel<T, CPL, 0>), blocks, 256, 0, s, static_cast<const T *>(src),
-                           static_cast<T *>(dst), a.nx, a.ny, rows, strips_x, ntiles, k, C(0.5));
+    hipLaunchKernelGGL((mrt_fused_kernel<T, CPL, AM, K, WALLS>), (ntiles + 3) / 4, 256, 0, s, static_cast<const T *>(src),
+                       static_cast<T *>(dst), a.nx, a.ny, rows, strips_x, ntiles, k);
     return hipGetLastError();
 }
 
-template <typename T> hipError_t run(const MrtArgs &a, const void *src, void *dst, hipStream_t s)
+template <typename T, int CPL, int AM>
+hipError_t run_steps(const MrtArgs &a, MrtCoef<typename Storage<T>::C> k, int steps, const void *src, void *dst, hipStream_t s)
+{
+    if (a.walls) switch (steps) {
+        case 1: return run_fused<T, CPL, AM, 1, true>(a, k, src, dst, s);
+        case 3: return run_fused<T, CPL, AM, 3, true>(a, k, src, dst, s);
+        case 5: return run_fused<T, CPL, AM, 5, true>(a, k, src, dst, s);
+        default: return hipErrorInvalidValue;
+        }
+    switch (steps) {
+    case 1: return run_fused<T, CPL, AM, 1, false>(a, k, src, dst, s);
+    case 3: return run_fused<T, CPL, AM, 3, false>(a, k, src, dst, s);
+    case 5: return run_fused<T, CPL, AM, 5, false>(a, k, src, dst, s);
+    default: return hipErrorInvalidValue;
+    }
+}
+
+// Walls at a general distance: one step per launch, aligned accesses only.
+template <typename T, int CPL>
+hipError_t run_xi(const MrtArgs &a, MrtCoef<typename Storage<T>::C> k, const void *src, void *dst, hipStream_t s)
+{
+    constexpr int S = 64 * CPL - 2 * CPL;
+    const int rows = a.tile_rows > 0 ? a.tile_rows : 1;
+    const int strips_x = (a.nx + S - 1) / S;
+    const int ntiles = strips_x * ((a.ny + rows - 1) / rows);
+    using C = typename Storage<T>::C;
+    hipLaunchKernelGGL((mrt_xi_kernel<T, CPL>), (ntiles + 3) / 4, 256, 0, s, static_cast<const T *>(src),
+                       static_cast<T *>(dst), a.nx, a.ny, rows, strips_x, ntiles, k, C(a.xi));
+    return hipGetLastError();
+}
+
+template <typename T> hipError_t run(const MrtArgs &a, int steps, const void *src, void *dst, hipStream_t s)
 {
     using C = typename Storage<T>::C;
     MrtCoef<C> k{C(a.s_e), C(a.s_xx), C(a.s_q), C(a.s_eps), C(0.5 * a.fx), C(0.5 * a.fy), C(a.fx), C(a.fy)};
     if (a.kernel != FDLBM_KERNEL_REFERENCE) {
         constexpr int CPL = sizeof(T) == 8 ? 2 : 4;
-        if (a.nx % CPL == 0) return run_sweep<T, CPL>(a, k, src, dst, s);
-        if (a.nx % 2 == 0) return run_sweep<T, 2>(a, k, src, dst, s);
-        return run_sweep<T, 1>(a, k, src, dst, s);
+        if (a.walls && a.xi != 0.5) {
+            if (a.nx % CPL == 0) return run_xi<T, CPL>(a, k, src, dst, s);
+            if (a.nx % 2 == 0) return run_xi<T, 2>(a, k, src, dst, s);
+            return run_xi<T, 1>(a, k, src, dst, s);
+        }
+        if (a.nx % CPL == 0) return run_steps<T, CPL, sweep::AM_VEC>(a, k, steps, src, dst, s);
+        return run_steps<T, CPL, sweep::AM_UNAL>(a, k, steps, src, dst, s);
     }
     dim3 blk(64, 4), grd((a.nx + 63) / 64, (a.ny + 3) / 4);
     if (a.walls)
@@ -449,9 +688,19 @@ inline unsigned rows_grid(int ny) { return (unsigned)(ny < 65536 ? ny : 65536); 
 
 }  // namespace
 
-hipError_t launch_mrt(const MrtArgs &a, const void *src, void *dst, hipStream_t s)
+// Steps per launch.  Five where the state streams from HBM: 8192^2 FP32 866 us per step one by one,
+// 340 in threes, 234 in fives; 2500^2 82, 39, 31.  A smaller state stays in the caches, a launch
+// lasts R + 2 (K - 1) ticks of one wavefront per SIMD, and three are as fast or faster: 1200^2 FP32
+// 21, 9.3, 10.7 us; 1021 x 770 FP64 22.9, 9.1, 9.7.  The two meet between 60 and 90 MB in both types.
+int mrt_max_fused(const MrtArgs &a)
 {
-    return a.dtype == FDLBM_F64 ? run<double>(a, src, dst, s) : run<float>(a, src, dst, s);
+    if (a.kernel == FDLBM_KERNEL_REFERENCE || (a.walls && a.xi != 0.5)) return 1;
+    return 9 * (size_t)a.nx * (size_t)a.ny * dtype_bytes(a.dtype) >= (size_t(80) << 20) ? 5 : 3;
+}
+
+hipError_t launch_mrt(const MrtArgs &a, int steps, const void *src, void *dst, hipStream_t s)
+{
+    return a.dtype == FDLBM_F64 ? run<double>(a, steps, src, dst, s) : run<float>(a, steps, src, dst, s);
 }
 
 hipError_t launch_mrt_init(int dtype, const double *dr, const double *jx, const double *jy, void *pop, int nx, int ny,

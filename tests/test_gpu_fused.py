@@ -1,0 +1,72 @@
+"""Several steps in one launch against the one-step reference kernels, bit for bit.
+
+A call of n steps is dealt to launches of up to three steps; the state after it, and the buffer
+it lies in, are those of n single steps for every n, on grids whose widths and heights leave
+partial strips, bands shorter than the rows a fused launch reads beyond them, and halo rows
+that wrap around the grid."""
+import numpy as np
+import pytest
+
+import workloads as W
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def F():
+    import torch
+
+    assert torch.cuda.is_available(), "GPU tests need a HIP device"
+    import paper_1803_00437_amd as F
+
+    F.load_library()
+    return F
+
+
+MRT_SHAPES = [(8, 8), (9, 13), (64, 4), (250, 45), (496, 17), (263, 8), (1021, 70), (37, 300), (240, 130)]
+
+
+@pytest.mark.parametrize("dtype", ["f32", "f64"])
+@pytest.mark.parametrize("bc", ["periodic", "walls"])
+@pytest.mark.parametrize("nx,ny", MRT_SHAPES)
+def test_mrt_steps_in_one_launch_equal_reference(F, nx, ny, bc, dtype):
+    if bc == "periodic" and ny < 8:
+        pytest.skip("periodic grids have at least eight rows")
+    init = W.random_state(nx, ny, seed=nx + ny, amp=0.02)
+    kw = dict(scheme="mrt", dtype=dtype, bc=bc, s_xx=1.3, s_e=1.1, s_eps=1.2, s_q=1.4, force=(2e-5, -1e-5))
+    ref = F.FdLbm(nx, ny, kernel="reference", **kw)
+    got = F.FdLbm(nx, ny, **kw)
+    ref.set_state(*init)
+    got.set_state(*init)
+    for n in (3, 1, 2, 4, 5, 8, 14):
+        print(f"  mrt fused {nx}x{ny} {bc} {dtype} +{n}", flush=True)
+        ref.step(n)
+        got.step(n)
+        assert got.steps == ref.steps
+        assert np.array_equal(got.get_populations(), ref.get_populations())
+        # the documented buffer: state_a after an even number of steps since creation
+        name = "state_b" if got.steps % 2 else "state_a"
+        assert bool((getattr(got.buffers, name) == getattr(ref.buffers, name)).all())
+    got.close()
+    ref.close()
+
+
+@pytest.mark.parametrize("dtype,nx,ny", [("f32", 1501, 1600), ("f32", 2600, 905), ("f64", 1203, 1000), ("f64", 998, 1300)])
+@pytest.mark.parametrize("bc", ["periodic", "walls"])
+def test_mrt_five_steps_in_one_launch_equal_reference(F, nx, ny, dtype, bc):
+    """States past the size from which a launch takes five steps."""
+    init = W.random_state(nx, ny, seed=nx, amp=0.02)
+    kw = dict(scheme="mrt", dtype=dtype, bc=bc, s_xx=1.6, s_e=1.1, quartic=True, force=(1e-5, 2e-5))
+    ref = F.FdLbm(nx, ny, kernel="reference", **kw)
+    got = F.FdLbm(nx, ny, **kw)
+    assert got.state_bytes >= 80 << 20
+    ref.set_state(*init)
+    got.set_state(*init)
+    for n in (5, 11, 7):
+        print(f"  mrt fused {nx}x{ny} {bc} {dtype} +{n}", flush=True)
+        ref.step(n)
+        got.step(n)
+        name = "state_b" if got.steps % 2 else "state_a"
+        assert bool((getattr(got.buffers, name) == getattr(ref.buffers, name)).all())
+    got.close()
+    ref.close()
