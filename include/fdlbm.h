@@ -82,15 +82,16 @@ typedef struct fdlbm_params {
                          * (1/s_xx - 1/2)(1/s_q - 1/2) = 1/6 (section 3-b)                   */
     double force_x, force_y; /* uniform body force per node and step, Strang-split (section 1) */
     int32_t kernel;     /* FDLBM_KERNEL_*                                                     */
-    int32_t tile_rows;  /* sweep kernel: rows per wavefront of a launch that takes one step,
-                         * 2..1024 (0 or 1 = choose); tuning                                  */
+    int32_t tile_rows;  /* sweep kernel: rows per wavefront, 2..1024 (0 or 1 = choose); tuning.
+                         * Other than 0, every launch takes one step                          */
     int32_t check_every;/* > 0: fdlbm_step / mrt_step scan the state for non-finite values
                          * every check_every steps and return FDLBM_EUNSTABLE if one is found
                          * (this synchronises the stream at each check)                       */
     int32_t lane_cols;  /* sweep kernel: grid columns per lane, 0 (choose), 1 (3-point only),
                          * 2, or 4 (FP32 / FP16); any nx: where nx is not a multiple, a lane's
                          * columns are one element-aligned access (FP32, FP64) or one access
-                         * each (FP16), with the same results; tuning knob                    */
+                         * each (FP16), with the same results; tuning knob.  Other than 0,
+                         * every launch takes one step                                        */
     double wall_xi;     /* walls: their distance beyond the first and last fluid rows, in
                          * (0, 1]; 0 selects 1/2 (sections 3-b, 3-c: the channel
                          * [1 - xi, N + xi] of Fig. 6).  FD-LBM: ghost rows by linear

@@ -59,6 +59,12 @@ FdArgs fd_args(const fdlbm_params &p)
                   wall_xi(p)};
 }
 
+MrtArgs mrt_args(const fdlbm_params &p, double s_q)
+{
+    return MrtArgs{p.nx, p.ny, p.bc == FDLBM_BC_WALLS_Y ? 1 : 0, p.dtype, p.s_e, p.s_xx, s_q, p.s_eps, p.force_x, p.force_y,
+                   p.kernel, p.tile_rows, wall_xi(p)};
+}
+
 // the disk's ghost-node table; false if the disk does not fit (checked by validate)
 bool disk_table(const fdlbm_params &p, DiskTable *t)
 {
@@ -70,6 +76,14 @@ bool uses_reference(const fdlbm_params &p)
     if (!three_words(p.scheme)) return false;
     if (p.kernel == FDLBM_KERNEL_REFERENCE) return true;
     return !fd_sweep_supported(fd_args(p), p.lane_cols);
+}
+
+// Steps that one launch of a context may take.  The disk's wall acts between the steps; a tile
+// shape asked for is that of one-step launches.
+int max_fused(const fdlbm_params &p, double s_q)
+{
+    if (p.bc == FDLBM_BC_DISK || uses_reference(p) || p.tile_rows != 0 || p.lane_cols != 0) return 1;
+    return three_words(p.scheme) ? fd_max_fused(fd_args(p)) : mrt_max_fused(mrt_args(p, s_q));
 }
 
 int validate(const fdlbm_params *p)
@@ -192,6 +206,7 @@ struct fdlbm_ctx {
     DiskFill disk;   // FDLBM_BC_DISK: the ghost-node table in the scratch buffer
     MrtDisk mdisk;   // FDLBM_BC_DISK, MRT: the boundary-link table in the scratch buffer
     bool disk_full;  // the next fill sets every rest node to rest (the state was just set)
+    int most;        // steps that one launch may take
 
     size_t n() const { return (size_t)p.nx * (size_t)p.ny; }
     double *sd(size_t off) const { return reinterpret_cast<double *>(scratch + off); }
@@ -236,6 +251,7 @@ int fdlbm_create(const fdlbm_params *p, void *state_a, void *state_b, void *scra
         c->disk = DiskFill{p->nx, p->ny, 0, 0, nullptr, nullptr, nullptr, nullptr, nullptr};
         c->mdisk = MrtDisk{p->nx, p->ny, 0, 0, nullptr, nullptr, nullptr, nullptr, nullptr};
         c->disk_full = true;
+        c->most = max_fused(*p, c->s_q);
         hipError_t e = hipGetDevice(&c->device);
         size_t sb = 0;
         fdlbm_workspace_bytes(p, &sb, nullptr);
@@ -391,12 +407,14 @@ static int run_diag(fdlbm_ctx *c, double out[DIAG_SLOTS])
     return FDLBM_OK;
 }
 
-// How `n` consecutive steps are dealt to launches of five, three or one steps.  A launch reads one
-// state buffer and writes the other whatever its steps, and the current state has to lie in
-// state_a after an even number of steps: launches of an odd number of steps keep that.  One or
-// two fives give way where that leaves no single steps.
+// How `n` consecutive steps are dealt to launches of up to `most` steps.  A launch reads one state
+// buffer and writes the other whatever its steps, and the current state has to lie in state_a
+// after an even number of steps: launches of five, three and one steps keep that, those of two
+// come in pairs.  One or two fives give way where that leaves no single steps.
 struct Launches {
-    int64_t fives = 0, threes = 0, ones = 0;
+    int64_t fives = 0, threes = 0, twos = 0, ones = 0;
+    int64_t count() const { return fives + threes + twos + ones; }
+    int steps(int64_t i) const { return i < fives ? 5 : i < fives + threes ? 3 : i < fives + threes + twos ? 2 : 1; }
 };
 static Launches deal_steps(int64_t n, int most)
 {
@@ -411,7 +429,8 @@ static Launches deal_steps(int64_t n, int most)
         n -= 5 * l.fives;
     }
     if (most >= 3) l.threes = n / 3;
-    l.ones = n - 3 * l.threes;
+    if (most == 2) l.twos = n / 4 * 2;
+    l.ones = n - 3 * l.threes - 2 * l.twos;
     return l;
 }
 
@@ -422,10 +441,8 @@ static int advance(fdlbm_ctx *c, int64_t nsteps)
     const bool ref = uses_reference(c->p);
     const bool disk = c->p.bc == FDLBM_BC_DISK;
     FdArgs fa = fd_args(c->p);
-    const MrtArgs ma{c->p.nx, c->p.ny, c->p.bc == FDLBM_BC_WALLS_Y ? 1 : 0, c->p.dtype, c->p.s_e, c->p.s_xx, c->s_q,
-                     c->p.s_eps, c->p.force_x, c->p.force_y, c->p.kernel, c->p.tile_rows, wall_xi(c->p)};
-    // the disk's wall acts between the steps
-    const int most = disk || fd ? 1 : mrt_max_fused(ma);
+    const MrtArgs ma = mrt_args(c->p, c->s_q);
+    const int most = c->most;
     // one launch of k steps from the current buffer into the other one
     auto take = [&](int k) -> int {
         // stochastic rounding draws fresh bits every step, reproducibly from the step count
@@ -444,8 +461,10 @@ static int advance(fdlbm_ctx *c, int64_t nsteps)
             e = launch_mrt(ma, k, src, dst, c->stream);
         else if (ref)
             e = launch_fd_reference(fa, src, dst, c->scratch + c->L.fstar, c->stream);
-        else
+        else if (k == 1)
             e = launch_fd_sweep(fa, c->p.tile_rows, c->p.lane_cols, src, dst, c->stream);
+        else
+            e = launch_fd_fused(fa, src, dst, c->stream);
         if (e != hipSuccess)
             return device_error(e, c->p.scheme == FDLBM_SCHEME_FD    ? "fdlbm_step launch"
                                    : c->p.scheme == FDLBM_SCHEME_MRT ? "mrt_step launch"
@@ -466,8 +485,8 @@ static int advance(fdlbm_ctx *c, int64_t nsteps)
         const int64_t every = c->p.check_every;
         const int64_t n = every > 0 ? std::min<int64_t>(left, every - c->steps % every) : left;
         const Launches l = deal_steps(n, most);
-        for (int64_t i = 0; i < l.fives + l.threes + l.ones; ++i) {
-            const int rc = take(i < l.fives ? 5 : i < l.fives + l.threes ? 3 : 1);
+        for (int64_t i = 0; i < l.count(); ++i) {
+            const int rc = take(l.steps(i));
             if (rc) return rc;
         }
         left -= n;
@@ -585,8 +604,8 @@ int fdlbm_autotune(fdlbm_ctx *c, int32_t reps, int32_t *out_lane_cols, int32_t *
         auto launch = [&](const Shape &sh) -> hipError_t {
             if (fd && ref) return launch_fd_reference(fa, src, dst, c->scratch + c->L.fstar, c->stream);
             if (fd) return launch_fd_sweep(fa, sh.rows, sh.cols, src, dst, c->stream);
-            const MrtArgs ma{c->p.nx, c->p.ny, c->p.bc == FDLBM_BC_WALLS_Y ? 1 : 0, c->p.dtype, c->p.s_e, c->p.s_xx, c->s_q,
-                             c->p.s_eps, c->p.force_x, c->p.force_y, c->p.kernel, sh.rows, wall_xi(c->p)};
+            MrtArgs ma = mrt_args(c->p, c->s_q);
+            ma.tile_rows = sh.rows;
             return launch_mrt(ma, 1, src, dst, c->stream);
         };
         Shape best{0, 0};

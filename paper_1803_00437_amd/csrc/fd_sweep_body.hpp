@@ -130,13 +130,16 @@ __device__ __forceinline__ void buf_store_group(__amdgpu_buffer_rsrc_t r, unsign
 //            periodic edge accesses them one by one instead, behind a branch that only
 //            the wavefronts holding such a lane take (any nx; 4- and 8-byte elements,
 //            whose vector accesses need no more than element alignment on this GPU)
-constexpr int AM_VEC = 0, AM_COL = 1, AM_UNAL = 2;
+//   AM_SEAM  one access at an element-aligned offset, in strips laid out so that the periodic
+//            edge falls between two lanes (any nx wider than a strip; 4- and 8-byte elements,
+//            2-byte ones where nx is even)
+constexpr int AM_VEC = 0, AM_COL = 1, AM_UNAL = 2, AM_SEAM = 3;
 
 // Byte offsets of a lane's loads and stores in a row (OFF_NONE: none): [0] the vector
 // access (AM_VEC, AM_UNAL), [c] or [1 + c] column c (AM_COL, AM_UNAL).  Stores leave out the
 // columns the tile does not store.
 template <int CPL, int AM> struct LaneCols {
-    static constexpr int K = AM == AM_VEC ? 1 : AM == AM_COL ? CPL : 1 + CPL;
+    static constexpr int K = AM == AM_VEC || AM == AM_SEAM ? 1 : AM == AM_COL ? CPL : 1 + CPL;
     unsigned ld[K], st[K];
     bool edge;   // AM_UNAL: a lane of this wavefront crosses the edge (wave-uniform)
     bool cross;  // AM_UNAL: this lane's columns cross the edge

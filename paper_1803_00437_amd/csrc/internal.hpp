@@ -47,6 +47,10 @@ size_t fd_reference_scratch_bytes(const FdArgs &a);
 // (0 = default; 1 for 3-point differences only, 2, or 4 for FP32/FP16 only).
 hipError_t launch_fd_sweep(const FdArgs &a, int tile_rows, int lane_cols, const void *src, void *dst, hipStream_t s);
 bool fd_sweep_supported(const FdArgs &a, int lane_cols);
+// FD-LBM and LW-ACM, several steps in one launch: fd_max_fused(a) of them (1: not offered for these
+// arguments).
+int fd_max_fused(const FdArgs &a);
+hipError_t launch_fd_fused(const FdArgs &a, const void *src, void *dst, hipStream_t s);
 
 // Batch of independent periodic FD-LBM grids (3-point differences) -------------------
 constexpr int BATCH_CHUNK = 65536;  // nodes per block of the A(t) reduction

@@ -70,3 +70,33 @@ def test_mrt_five_steps_in_one_launch_equal_reference(F, nx, ny, dtype, bc):
         assert bool((getattr(got.buffers, name) == getattr(ref.buffers, name)).all())
     got.close()
     ref.close()
+
+
+FD_SHAPES = [(8, 8), (9, 13), (64, 12), (250, 45), (240, 17), (263, 9), (502, 16), (1021, 70), (37, 300), (480, 130)]
+FD_KINDS = [("fd", 3, "periodic", 0.5), ("fd", 3, "walls", 0.5), ("fd", 3, "walls", 0.8), ("fd", 5, "periodic", 0.5), ("lwacm", 3, "periodic", 0.5)]
+
+
+@pytest.mark.parametrize("dtype", ["f32", "f64", "f16"])
+@pytest.mark.parametrize("scheme,stencil,bc,xi", FD_KINDS)
+@pytest.mark.parametrize("forced", [False, True])
+@pytest.mark.parametrize("nx,ny", FD_SHAPES)
+def test_fd_steps_in_one_launch_equal_reference(F, nx, ny, scheme, stencil, bc, xi, dtype, forced):
+    if forced and scheme == "lwacm":
+        pytest.skip("the LW-ACM step has no body force")
+    init = W.random_state(nx, ny, seed=nx + ny, amp=0.02)
+    kw = dict(scheme=scheme, dtype=dtype, bc=bc, s_xx=1.3, s_e=1.1)
+    if scheme == "fd":
+        kw.update(stencil=stencil, wall_xi=xi, force=(2e-5, -1e-5) if forced else (0.0, 0.0))
+    ref = F.FdLbm(nx, ny, kernel="reference", **kw)
+    got = F.FdLbm(nx, ny, **kw)
+    ref.set_state(*init)
+    got.set_state(*init)
+    for n in (3, 1, 2, 4, 8):
+        print(f"  {scheme}{stencil} fused {nx}x{ny} {bc} xi {xi} {dtype} +{n}", flush=True)
+        ref.step(n)
+        got.step(n)
+        name = "state_b" if got.steps % 2 else "state_a"
+        assert got.steps == ref.steps
+        assert bool((getattr(got.buffers, name) == getattr(ref.buffers, name)).all())
+    got.close()
+    ref.close()
