@@ -42,7 +42,7 @@ typedef struct fdlbm3d_params {
                             post-collision planes then a gather (needs the larger scratch)        */
     int32_t tile_rows;   /* sweep: wavefronts per block along y, 8, 12 or 16 (0 = 12), two of which
                             hold halo rows                                                        */
-    int32_t tile_planes; /* sweep: planes per block along z, 1 .. 4096 (0 = 64 in FP32, 32 in FP64) */
+    int32_t tile_planes; /* sweep: planes per block along z, 1 .. 4096 (0 = chosen from the grid) */
 } fdlbm3d_params;
 
 typedef struct fdlbm3d_diag {

@@ -15,13 +15,16 @@
 //     exchanged through LDS, twice per plane: the stored fields of the plane (for the
 //     y-differences) and the x-shifted group sums sent to the row above and below;
 //   * the block sweeps TZ planes along z; each lane keeps its column's fields of three
-//     planes in registers (plus one loaded ahead), and the partial update of the plane below
+//     planes in registers (plus one loaded ahead; four slots), and the partial update of the plane below
 //     until the plane above has been formed;
-//   * measured at 512^3 (FP32): 12 rows per block and 64 planes run fastest (86 000 MLUPS);
-//     16 rows leave one block per compute unit (68 000), 8 rows spend a third of the work on
-//     halo rows (83 000), 14 rows split 4/4/3/3 over the SIMDs so that a second block does not
-//     fit (69 000); unrolling the plane loop to rename the window instead of copying it raised
-//     the registers past six wavefronts per SIMD and ran 5-17 % slower;
+//   * measured at 512^3 (FP32): 12 rows per block and 64 planes run fastest (16 rows leave one
+//     block per compute unit, 8 rows spend a third of the work on halo rows, 14 rows split 4/4/3/3
+//     over the SIMDs so that a second block does not fit); the plane loop is unrolled over the four
+//     slots of the window, which takes the 16 register copies per plane out (about 250 vector
+//     instructions per plane and wavefront, from 265; 80 registers, six wavefronts per SIMD): 1439
+//     -> 1419 us per step at 512^3, 287 -> 275 at 256^3 with 64 planes, FP64 256^3 525 -> 478;
+//   * planes per block by the number of blocks that run at once (tile_planes in abi3d.cpp): 256^3
+//     FP32 275 -> 218 us, 200 x 150 x 100 115 -> 50, 32^3 112 -> 8.4;
 //   * every index wraps (periodic grid), so a grid narrower than a tile is covered by lanes,
 //     rows or planes that repeat: they compute and store the same bits.  The last strip, row
 //     band and plane band are shifted back to end at the grid's edge, so tiles overlap there
@@ -125,7 +128,7 @@ __global__ __launch_bounds__(256) void d3_ref_gather(const T *__restrict__ st, c
 constexpr int LANES = 64, XU = LANES - 4;  // columns per wavefront, of which updated
 
 template <typename T, int WY>
-__global__ __launch_bounds__(LANES *WY) void d3_sweep_kernel(const T *__restrict__ st, T *__restrict__ out, int nx,
+__global__ __launch_bounds__(LANES *WY, sizeof(T) == 8 ? 3 : 6) void d3_sweep_kernel(const T *__restrict__ st, T *__restrict__ out, int nx,
                                                              int ny, int nz, int tz, Coef3<T> k)
 {
     using C = T;
@@ -168,13 +171,15 @@ __global__ __launch_bounds__(LANES *WY) void d3_sweep_kernel(const T *__restrict
         for (int f = 0; f < 4; ++f) d[f] = __builtin_bit_cast(T, Ops::load(rsrc(st, f, pz), off));
     };
 
-    // window: planes p-1, p, p+1 of this row; nxt: plane p+2; outer row (halo waves): plane p
-    C win[3][4], nxt[4], orow[4], onxt[4];
+    // window of four planes of this row, plane p + j in slot (ph + 1 + j) % 4 (p - 1, p, p + 1 in
+    // use, p + 2 in flight), and of the outer row (halo waves), plane p in slot ph % 2: the loop is
+    // unrolled four times, so the slots are static and nothing is copied
+    C win[4][4], orow[2][4];
     load4(off_row, wrapi(z0 - 2, nz), win[0]);
     load4(off_row, wrapi(z0 - 1, nz), win[1]);
     load4(off_row, wrapi(z0, nz), win[2]);
-    for (int f = 0; f < 4; ++f) orow[f] = onxt[f] = C(0);
-    if (halo_lo || halo_hi) load4(off_out, wrapi(z0 - 1, nz), orow);
+    for (int f = 0; f < 4; ++f) orow[0][f] = orow[1][f] = C(0);
+    if (halo_lo || halo_hi) load4(off_out, wrapi(z0 - 1, nz), orow[0]);
     auto next_plane = [&](int z) { return z + 1 == nz ? 0 : z + 1; };
     int zn = wrapi(z0 + 1, nz);  // plane p+2: this row's next load
     int zo = wrapi(z0, nz);      // plane p+1: the outer row's next load
@@ -187,36 +192,37 @@ __global__ __launch_bounds__(LANES *WY) void d3_sweep_kernel(const T *__restrict
     D3Part<C> part{0, 0, 0, 0};
     C o0m1s = 0, o0m1x = 0, o17 = 0, o16 = 0;
 
-    for (int it = 0; it < tz + 2; ++it) {
-        load4(off_row, zn, nxt);  // plane p + 2 (p = z0 - 1 + it: the plane formed now)
-        if (halo_lo || halo_hi) load4(off_out, zo, onxt);
+    auto sweep_plane = [&](int it, int ph) __attribute__((always_inline)) {
+        C(&wm)[4] = win[ph % 4], (&c)[4] = win[(ph + 1) % 4], (&wp)[4] = win[(ph + 2) % 4];
+        C(&oc)[4] = orow[ph % 2];
+        load4(off_row, zn, win[(ph + 3) % 4]);  // plane p + 2 (p = z0 - 1 + it: the plane formed now)
+        if (halo_lo || halo_hi) load4(off_out, zo, orow[(ph + 1) % 2]);
 
-        for (int f = 0; f < 4; ++f) lds_f[w][f][lane] = win[1][f];
+        for (int f = 0; f < 4; ++f) lds_f[w][f][lane] = c[f];
         __syncthreads();
         C up[4], dn[4];
         for (int f = 0; f < 4; ++f) {
-            up[f] = halo_hi ? orow[f] : lds_f[halo_hi ? w : w + 1][f][lane];
-            dn[f] = halo_lo ? orow[f] : lds_f[halo_lo ? w : w - 1][f][lane];
+            up[f] = halo_hi ? oc[f] : lds_f[halo_hi ? w : w + 1][f][lane];
+            dn[f] = halo_lo ? oc[f] : lds_f[halo_lo ? w : w - 1][f][lane];
         }
 
         // differences along x (lanes), y (LDS rows) and z (window planes)
-        const C *c = win[1];
         const C jj[3] = {c[1], c[2], c[3]};
         C gr[3], dj[3][3];
         gr[0] = from_right(c[0]) - from_left(c[0]);
         gr[1] = up[0] - dn[0];
-        gr[2] = win[2][0] - win[0][0];
+        gr[2] = wp[0] - wm[0];
         for (int b = 0; b < 3; ++b) {
             dj[0][b] = from_right(c[1 + b]) - from_left(c[1 + b]);
             dj[1][b] = up[1 + b] - dn[1 + b];
-            dj[2][b] = win[2][1 + b] - win[0][1 + b];
+            dj[2][b] = wp[1 + b] - wm[1 + b];
         }
         C dp[3];
         for (int b = 0; b < 3; ++b) {
             const C px = c[1 + b] * c[1];  // J_b J_x of this column, for the neighbours' x-differences
             const C dx = from_right(px) - from_left(px);
             const C dy = d3_pdiff(up[1 + b], up[2], dn[1 + b], dn[2]);
-            const C dz = d3_pdiff(win[2][1 + b], win[2][3], win[0][1 + b], win[0][3]);
+            const C dz = d3_pdiff(wp[1 + b], wp[3], wm[1 + b], wm[3]);
             dp[b] = d3_flux(dx, dy, dz);
         }
         C f[Q];
@@ -257,8 +263,8 @@ __global__ __launch_bounds__(LANES *WY) void d3_sweep_kernel(const T *__restrict
             // the plane below (p - 1) is complete: its arrivals from plane p are in
             if (it >= 2) {
                 C r, x, y, z;
-                d3_finish(part, s0m1 - o0m1s, x0m1 - o0m1x, in17 - o17, in16 - o16, win[0][0], win[0][1], win[0][2],
-                          win[0][3], r, x, y, z);
+                d3_finish(part, s0m1 - o0m1s, x0m1 - o0m1x, in17 - o17, in16 - o16, wm[0], wm[1], wm[2], wm[3], r, x,
+                          y, z);
                 const C v[4] = {r, x, y, z};
                 for (int f = 0; f < 4; ++f)
                     Ops::store(__builtin_bit_cast(typename Ops::W, v[f]), rsrc(out, f, zs), off_st);
@@ -280,11 +286,12 @@ __global__ __launch_bounds__(LANES *WY) void d3_sweep_kernel(const T *__restrict
         zn = next_plane(zn);
         zo = next_plane(zo);
         zs = next_plane(zs);
-        for (int q = 0; q < 4; ++q) {
-            win[0][q] = win[1][q];
-            win[1][q] = win[2][q];
-            win[2][q] = nxt[q];
-            orow[q] = onxt[q];
+    };
+    for (int it0 = 0; it0 < tz + 2; it0 += 4) {
+#pragma unroll
+        for (int ph = 0; ph < 4; ++ph) {
+            if (it0 + ph >= tz + 2) break;
+            sweep_plane(it0 + ph, ph);
         }
     }
 }

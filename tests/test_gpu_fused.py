@@ -100,3 +100,22 @@ def test_fd_steps_in_one_launch_equal_reference(F, nx, ny, scheme, stencil, bc, 
         assert bool((getattr(got.buffers, name) == getattr(ref.buffers, name)).all())
     got.close()
     ref.close()
+
+
+@pytest.mark.parametrize("dtype", ["f32", "f64"])
+@pytest.mark.parametrize("nx,ny,nz", [(3, 3, 3), (61, 11, 5), (64, 10, 2 * 37 + 1), (120, 21, 130), (256, 130, 9)])
+def test_d3_planes_chosen_from_the_grid_equal_reference(F, nx, ny, nz, dtype):
+    """The default planes per block: one block of planes, uneven ones, and the smallest grid."""
+    init = W.random_state3(nx, ny, nz, seed=nx + nz, amp=0.02)
+    kw = dict(dtype=dtype, s_nu=1.4, s_e=1.2)
+    ref = F.FdLbm3D(nx, ny, nz, kernel="reference", **kw)
+    got = F.FdLbm3D(nx, ny, nz, **kw)
+    ref.set_state(*init)
+    got.set_state(*init)
+    print(f"  d3 {nx}x{ny}x{nz} {dtype}", flush=True)
+    ref.step(5)
+    got.step(5)
+    size = 4 * nx * ny * nz * (8 if dtype == "f64" else 4)  # the buffers are padded to 256 bytes
+    assert bool((got.buffers.state_b[:size] == ref.buffers.state_b[:size]).all())
+    got.close()
+    ref.close()
