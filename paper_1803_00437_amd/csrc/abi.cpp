@@ -86,6 +86,14 @@ int max_fused(const fdlbm_params &p, double s_q)
     return three_words(p.scheme) ? fd_max_fused(fd_args(p)) : mrt_max_fused(mrt_args(p, s_q));
 }
 
+// Tiles that stay in registers for several steps, where they are the faster way.
+TilePlan tile_plan(const fdlbm_params &p, double s_q)
+{
+    if (p.bc == FDLBM_BC_DISK || p.kernel != FDLBM_KERNEL_AUTO || uses_reference(p) || p.tile_rows != 0 || p.lane_cols != 0)
+        return TilePlan();
+    return three_words(p.scheme) ? fd_tile_plan(fd_args(p)) : mrt_tile_plan(mrt_args(p, s_q));
+}
+
 int validate(const fdlbm_params *p)
 {
     if (!p) return FDLBM_EINVAL;
@@ -207,6 +215,7 @@ struct fdlbm_ctx {
     MrtDisk mdisk;   // FDLBM_BC_DISK, MRT: the boundary-link table in the scratch buffer
     bool disk_full;  // the next fill sets every rest node to rest (the state was just set)
     int most;        // steps that one launch may take
+    TilePlan tile;   // tile.steps > 0: launches of tiles, up to so many steps each
 
     size_t n() const { return (size_t)p.nx * (size_t)p.ny; }
     double *sd(size_t off) const { return reinterpret_cast<double *>(scratch + off); }
@@ -252,6 +261,7 @@ int fdlbm_create(const fdlbm_params *p, void *state_a, void *state_b, void *scra
         c->mdisk = MrtDisk{p->nx, p->ny, 0, 0, nullptr, nullptr, nullptr, nullptr, nullptr};
         c->disk_full = true;
         c->most = max_fused(*p, c->s_q);
+        c->tile = tile_plan(*p, c->s_q);
         hipError_t e = hipGetDevice(&c->device);
         size_t sb = 0;
         fdlbm_workspace_bytes(p, &sb, nullptr);
@@ -434,6 +444,24 @@ static Launches deal_steps(int64_t n, int most)
     return l;
 }
 
+// `n` consecutive steps in launches of tiles of up to `most` steps (an odd number): odd numbers of
+// steps, as even as they can be (`high` launches of `low` + 2 steps, the others of `low`), and as
+// many launches as keep the buffer's parity.
+struct TileLaunches {
+    int64_t count, high;
+    int low;
+};
+static TileLaunches deal_tiles(int64_t n, int most)
+{
+    TileLaunches l;
+    l.count = (n + most - 1) / most;
+    l.count += (l.count ^ n) & 1;
+    l.low = int(n / l.count);
+    l.low -= l.low % 2 == 0;
+    l.high = (n - l.count * l.low) / 2;
+    return l;
+}
+
 static int advance(fdlbm_ctx *c, int64_t nsteps)
 {
     HIPCHK(hipSetDevice(c->device), "hipSetDevice");
@@ -484,10 +512,24 @@ static int advance(fdlbm_ctx *c, int64_t nsteps)
         // up to the next check of the state
         const int64_t every = c->p.check_every;
         const int64_t n = every > 0 ? std::min<int64_t>(left, every - c->steps % every) : left;
-        const Launches l = deal_steps(n, most);
-        for (int64_t i = 0; i < l.count(); ++i) {
-            const int rc = take(l.steps(i));
-            if (rc) return rc;
+        if (c->tile.steps > 0) {
+            const TileLaunches l = deal_tiles(n, c->tile.steps);
+            for (int64_t i = 0; i < l.count; ++i) {
+                TilePlan tile = c->tile;
+                tile.steps = i < l.high ? l.low + 2 : l.low;
+                const void *src = c->buf[c->cur];
+                void *dst = c->buf[c->cur ^ 1];
+                HIPCHK(fd ? launch_fd_tile(fa, tile, src, dst, c->stream) : launch_mrt_tile(ma, tile, src, dst, c->stream),
+                       "step launch");
+                c->cur ^= 1;
+                c->steps += tile.steps;
+            }
+        } else {
+            const Launches l = deal_steps(n, most);
+            for (int64_t i = 0; i < l.count(); ++i) {
+                const int rc = take(l.steps(i));
+                if (rc) return rc;
+            }
         }
         left -= n;
         if (every > 0 && c->steps % every == 0) {

@@ -473,21 +473,6 @@ int fused_rows(int strips_x, int ny, int K, int H, bool walls, int waves_per_sim
     return best;
 }
 
-// Columns from one strip to the next such that no lane's columns cross the periodic edge (AM_SEAM),
-// or 0.  The last strip starts at nx - S, so its lanes meet the edge between two of them; the one
-// before must not reach beyond the edge with its halo lanes, and the strips still have to cover the
-// row.  FP16 strips start at even columns (4-byte accesses).
-template <typename T, int CPL, int H, int K> int seam_stride(int nx)
-{
-    using G = FusedStrip<CPL, H, K>;
-    if (nx < G::S + G::P * CPL || (sizeof(T) == 2 && nx % 2)) return 0;
-    const int strips = (nx + G::S - 1) / G::S;
-    if (strips <= 2) return strips == 2 ? G::S : 0;
-    int stride = std::min(G::S, (nx - G::S - G::P * CPL) / (strips - 2));
-    if (sizeof(T) == 2) stride &= ~1;
-    return (strips - 2) * stride + G::S >= nx - G::S ? stride : 0;
-}
-
 template <typename T, int CPL, int ST, bool WALLS, bool FORCE, int AM, int K, int KR, int KC>
 hipError_t run(const FdArgs &fa, const void *src, void *dst, hipStream_t s)
 {
@@ -500,7 +485,7 @@ hipError_t run(const FdArgs &fa, const void *src, void *dst, hipStream_t s)
     a.ny = fa.ny;
     a.strips_x = (fa.nx + G::S - 1) / G::S;
     a.stride = G::S;
-    if (AM == AM_SEAM) a.stride = seam_stride<T, CPL, H, K>(fa.nx);
+    if (AM == AM_SEAM) a.stride = seam_stride(fa.nx, G::S, G::P, CPL, sizeof(T));
     a.rows = fused_rows(a.strips_x, fa.ny, K, H, WALLS, fused_waves<ST>());
     a.ntiles = a.strips_x * ((fa.ny + a.rows - 1) / a.rows);
     a.k = make_coef<typename Storage<T>::C>(ST, fa.s_xx, fa.s_e, fa.fx, fa.fy);
@@ -514,7 +499,8 @@ template <typename T, int CPL, int ST, bool WALLS, bool FORCE, int K, int KR, in
 hipError_t dispatch_width(const FdArgs &a, const void *src, void *dst, hipStream_t s)
 {
     if (a.nx % CPL == 0) return run<T, CPL, ST, WALLS, FORCE, AM_VEC, K, KR, KC>(a, src, dst, s);
-    if (seam_stride<T, CPL, Stencil<ST>::H, K>(a.nx) > 0)
+    using G = FusedStrip<CPL, Stencil<ST>::H, K>;
+    if (seam_stride(a.nx, G::S, G::P, CPL, sizeof(T)) > 0)
         return run<T, CPL, ST, WALLS, FORCE, AM_SEAM, K, KR, KC>(a, src, dst, s);
     return run<T, CPL, ST, WALLS, FORCE, sizeof(T) >= 4 ? AM_UNAL : AM_COL, K, KR, KC>(a, src, dst, s);
 }
@@ -542,6 +528,21 @@ int fd_max_fused(const FdArgs &a)
     if (a.stencil == 1) return 3;
     if (a.walls && (a.xi < 0.5 || a.ny < 16 || a.stencil == 5)) return 1;  // see fused_rows() and ghost_rules()
     return 2;
+}
+
+// Time of one step in launches of K = fd_max_fused(a), in us: the wavefronts each SIMD gets times the
+// rows each takes through K stages of us_row each, and 3 us per launch.  us_row is measured (one
+// stage of one row of 64 CPL columns: 256^2, 1024^2, 2048^2).
+double fd_fused_us(const FdArgs &a)
+{
+    const int K = fd_max_fused(a), H = a.stencil == 1 ? 0 : a.stencil == 3 ? 1 : 2, CPL = a.dtype == FDLBM_F64 ? 2 : 4;
+    const bool f64 = a.dtype == FDLBM_F64;
+    const double us_row = H == 0 ? (f64 ? 0.27 : 0.37) : H == 1 ? (f64 ? 0.52 : 0.62) : (f64 ? 0.7 : 0.68);
+    const int P = (K * (H + 1) + CPL - 1) / CPL, S = (64 - 2 * P) * CPL, strips = (a.nx + S - 1) / S;
+    if (K == 1) return 3.0 + 14.0 * us_row * ((strips * ((a.ny + 7) / 8) + 1023) / 1024);
+    const int rows = fused_rows(strips, a.ny, K, H, a.walls != 0, a.stencil == 5 ? 1 : 2);
+    const long each = ((long)strips * ((a.ny + rows - 1) / rows) + 1023) / 1024;
+    return 3.0 / K + double(each) * (rows + 2 * K * (H + 1)) * us_row;
 }
 
 template <typename T, int CPL> static hipError_t launch(const FdArgs &a, const void *src, void *dst, hipStream_t s)

@@ -228,6 +228,22 @@ template <int CPL, int H> struct Strip {
     static constexpr int S = W - 2 * P;
 };
 
+// AM_SEAM: columns from one strip to the next (of 64*CPL columns, P halo lanes a side, S stored)
+// such that no lane's columns cross the periodic edge, or 0 if there is no such layout.  The last
+// strip starts at nx - S, so its lanes meet the edge between two of them; the one before must not
+// reach beyond the edge with its halo lanes, and the strips still have to cover the row.  Strips of
+// 2-byte elements start at even columns (4-byte accesses).
+inline int seam_stride(int nx, int S, int P, int CPL, int elem_bytes)
+{
+    if (nx < S + P * CPL || (elem_bytes == 2 && nx % 2)) return 0;
+    const int strips = (nx + S - 1) / S;
+    if (strips <= 2) return strips == 2 ? S : 0;
+    const int room = (nx - S - P * CPL) / (strips - 2);
+    int stride = room < S ? room : S;
+    if (elem_bytes == 2) stride &= ~1;
+    return (strips - 2) * stride + S >= nx - S ? stride : 0;
+}
+
 // One grid as a tile sees it: the first rows of the input and output fields (rows of a field
 // 3 nx apart, see fd_elem), size, rows per wavefront and the
 // reconstruction constants.

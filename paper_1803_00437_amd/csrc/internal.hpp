@@ -52,6 +52,48 @@ bool fd_sweep_supported(const FdArgs &a, int lane_cols);
 int fd_max_fused(const FdArgs &a);
 hipError_t launch_fd_fused(const FdArgs &a, const void *src, void *dst, hipStream_t s);
 
+// Small and medium grids: a block advances a tile of 64 cols columns by 16 rows rows up to `steps`
+// steps in registers (an odd number: see advance() in abi.cpp).  steps = 0: the sweep kernels.
+struct TilePlan {
+    int cols = 0, rows = 0, steps = 0;
+};
+struct TileShape {
+    int cols, rows;
+};
+// The fastest shape and number of steps for a grid, or the sweep if its estimate `sweep_us` (per
+// step) is less.  A block's launch, loads and stores take 2.5 us and 0.85 us (FP64 1.2) per row and
+// column of a lane; a step takes 0.3 us and row_us per row and column of a lane.  A compute unit gets
+// one block of 256 after the other, two at once where the shape's registers allow.  reach: rows and columns a step loses on
+// each side.  Measured against the estimate (us per step): 64^2 FP64 2.3 (2.4), 256^2 FP32 2.3
+// (2.4), 1024^2 6.7 (7.4), 1001 x 777 5-point 9.0 (9.0), where the sweep takes 4.5, 6.1, 10.2 and 12.
+inline TilePlan plan_tiles(int nx, int ny, int reach, int elem_bytes, double row_us, const TileShape *shapes, int count,
+                           double sweep_us)
+{
+    TilePlan best;
+    double best_us = 0.95 * sweep_us;
+    for (int i = 0; i < count; ++i)
+        for (int steps = 1; steps <= 25; steps += 2) {
+            const int cols = 64 * shapes[i].cols - 2 * reach * steps, rows = 16 * shapes[i].rows - 2 * reach * steps;
+            if (cols < 1 || rows < 1) break;
+            const int64_t blocks = (int64_t)((nx + cols - 1) / cols) * ((ny + rows - 1) / rows);
+            const int area = shapes[i].cols * shapes[i].rows;
+            const int64_t each = (blocks + 255) / 256, rounds = area * elem_bytes <= 8 ? (each + 1) / 2 : each;
+            const double start = 2.5 + 0.2 * area * (elem_bytes == 8 ? 6 : 4.25) + 0.3 * steps;
+            const double us = (double(rounds) * start + double(each) * steps * area * row_us) / steps;
+            if (us < best_us) {
+                best_us = us;
+                best.cols = shapes[i].cols;
+                best.rows = shapes[i].rows;
+                best.steps = steps;
+            }
+        }
+    return best;
+}
+// FD-LBM and LW-ACM: the plan (steps = 0 where the tiles do not apply) and a launch of p.steps steps.
+TilePlan fd_tile_plan(const FdArgs &a);
+double fd_fused_us(const FdArgs &a);
+hipError_t launch_fd_tile(const FdArgs &a, const TilePlan &p, const void *src, void *dst, hipStream_t s);
+
 // Batch of independent periodic FD-LBM grids (3-point differences) -------------------
 constexpr int BATCH_CHUNK = 65536;  // nodes per block of the A(t) reduction
 struct BatchInstance {
@@ -140,6 +182,8 @@ hipError_t launch_mrt_disk(const MrtDisk &d, int dtype, void *pop, bool full, hi
 // `steps` consecutive steps in one launch, 1 .. mrt_max_fused(a)
 int mrt_max_fused(const MrtArgs &a);
 hipError_t launch_mrt(const MrtArgs &a, int steps, const void *src, void *dst, hipStream_t s);
+TilePlan mrt_tile_plan(const MrtArgs &a);
+hipError_t launch_mrt_tile(const MrtArgs &a, const TilePlan &p, const void *src, void *dst, hipStream_t s);
 
 // Conversions between host-staged FP64 planes and device storage: element by element (the
 // D3Q19 state, the batch modes), and row by row between nf FP64 planes and the

@@ -390,7 +390,7 @@ template <typename T, int CPL, int K> struct MrtStrip {
 
 template <typename T, int CPL, int AM, int K, bool WALLS>
 __global__ void __launch_bounds__(256, K > 1 ? 2 : 1) mrt_fused_kernel(const T *__restrict__ in, T *__restrict__ out, int nx, int ny,
-                                                        int rows, int strips_x, int ntiles,
+                                                        int rows, int strips_x, int stride, int ntiles,
                                                         MrtCoef<typename Storage<T>::C> k)
 {
     using C = typename Storage<T>::C;
@@ -401,8 +401,8 @@ __global__ void __launch_bounds__(256, K > 1 ? 2 : 1) mrt_fused_kernel(const T *
     if (tile >= ntiles) return;  // uniform over the wavefront
     const int band = tile / strips_x, sx = tile - band * strips_x;
     // element-aligned accesses: the last strip ends at column nx - 1 (see sweep_tile)
-    const bool shift_last = AM == AM_UNAL && sx == strips_x - 1 && nx > G::S;
-    const int xl = (shift_last ? nx - G::S : sx * G::S) - G::P * CPL + CPL * lane;
+    const bool shift_last = (AM == AM_UNAL || AM == AM_SEAM) && sx == strips_x - 1 && nx > G::S;
+    const int xl = (shift_last ? nx - G::S : sx * stride) - G::P * CPL + CPL * lane;
     const LaneCols<CPL, AM> lc = make_lane_cols<T, CPL, AM>(xl, nx, lane >= G::P && lane < 64 - G::P);
     const int y0 = band * rows, y1 = min(y0 + rows, ny);
     // stage s collides rows max(y0 - (K-1-s), 0 with walls) .. min(y1-1 + (K-1-s), ny-1 with walls)
@@ -557,6 +557,94 @@ __global__ void __launch_bounds__(256, K > 1 ? 2 : 1) mrt_fused_kernel(const T *
     }
 }
 
+// Small and medium grids: a block of 16 wavefronts keeps a tile of 64 columns by 16 R rows in
+// registers (R rows per wavefront) for K steps, as fd_tile_kernel does for FD-LBM.  Every step
+// loses one row and one column on each side of the tile.  Columns come from the adjacent lanes;
+// the populations that cross to the wavefronts above and below go through LDS, in two buffers used
+// in turn, so one barrier a step is enough.
+constexpr int MRT_TW = 16;  // wavefronts per block
+
+template <typename T, int R, bool WALLS>
+__global__ void __launch_bounds__(64 * MRT_TW) mrt_tile_kernel(const T *__restrict__ in, T *__restrict__ out, int nx,
+                                                               int ny, int steps, int tiles_x,
+                                                               MrtCoef<typename Storage<T>::C> k)
+{
+    using C = typename Storage<T>::C;
+    using sweep::from_left;
+    using sweep::from_right;
+    __shared__ C cross[2][MRT_TW][6][64];  // 2, 5, 6 of the last row, 4, 7, 8 of the first
+    const int lane = threadIdx.x & 63;
+    const int wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int ty = blockIdx.x / tiles_x, tx = blockIdx.x - ty * tiles_x;
+    const int cols = 64 - 2 * steps, rows = MRT_TW * R - 2 * steps;  // stored by a tile
+    const int x = tx * cols - steps + lane, y0 = ty * rows - steps + wv * R;
+    const size_t col = (size_t)((x % nx + nx) % nx);
+    C f[R][9];
+#pragma unroll
+    for (int i = 0; i < R; ++i) {
+        const int y = y0 + i, yy = WALLS ? min(max(y, 0), ny - 1) : (y % ny + ny) % ny;
+#pragma unroll
+        for (int q = 0; q < 9; ++q) f[i][q] = Storage<T>::load(in[pop_elem(col, yy, q, nx)]);
+    }
+    const int rising[3] = {2, 5, 6}, falling[3] = {4, 7, 8};
+    for (int step = 0; step < steps; ++step) {
+        C b[R][3];  // with walls: the populations that return into their row
+#pragma unroll
+        for (int i = 0; i < R; ++i) {
+            collide<C>(f[i], k);
+            if (WALLS) {
+                const bool bottom = y0 + i == 0;
+#pragma unroll
+                for (int t = 0; t < 3; ++t) {
+                    const C lo = f[i][falling[t]], hi = f[i][rising[t]];
+                    b[i][t] = bottom ? lo : hi;
+                }
+            }
+            f[i][1] = from_left(f[i][1]);
+            f[i][5] = from_left(f[i][5]);
+            f[i][8] = from_left(f[i][8]);
+            f[i][3] = from_right(f[i][3]);
+            f[i][6] = from_right(f[i][6]);
+            f[i][7] = from_right(f[i][7]);
+        }
+        C(&lds)[MRT_TW][6][64] = cross[step & 1];
+#pragma unroll
+        for (int t = 0; t < 3; ++t) {
+            lds[wv][t][lane] = f[R - 1][rising[t]];
+            lds[wv][3 + t][lane] = f[0][falling[t]];
+        }
+        __syncthreads();
+        const int wb = max(wv - 1, 0), wa = min(wv + 1, MRT_TW - 1);
+#pragma unroll
+        for (int t = 0; t < 3; ++t) {
+#pragma unroll
+            for (int i = R - 1; i > 0; --i) f[i][rising[t]] = f[i - 1][rising[t]];
+            f[0][rising[t]] = lds[wb][t][lane];
+#pragma unroll
+            for (int i = 0; i < R - 1; ++i) f[i][falling[t]] = f[i + 1][falling[t]];
+            f[R - 1][falling[t]] = lds[wa][3 + t][lane];
+        }
+        if (WALLS)
+#pragma unroll
+            for (int i = 0; i < R; ++i) {
+                if (y0 + i == 0)
+#pragma unroll
+                    for (int t = 0; t < 3; ++t) f[i][rising[t]] = b[i][t];
+                if (y0 + i == ny - 1)
+#pragma unroll
+                    for (int t = 0; t < 3; ++t) f[i][falling[t]] = b[i][t];
+            }
+    }
+    if (lane < steps || lane >= 64 - steps || x >= nx) return;
+#pragma unroll
+    for (int i = 0; i < R; ++i) {
+        const int j = wv * R + i, y = y0 + i;
+        if (j < steps || j >= MRT_TW * R - steps || y >= ny) continue;
+#pragma unroll
+        for (int q = 0; q < 9; ++q) out[pop_elem(x, y, q, nx)] = Storage<T>::store(f[i][q]);
+    }
+}
+
 // Equilibrium populations of host-order FP64 planes (drho, Jx, Jy; node (i, j) at j nx + i),
 // stored row-interleaved; one block row of columns per grid row.
 template <typename T>
@@ -624,24 +712,35 @@ hipError_t run_fused(const MrtArgs &a, MrtCoef<typename Storage<T>::C> k, const 
     // one step: 1 row per wavefront measured best at 8192^2 (1 % over 2)
     const int rows = K == 1 ? (a.tile_rows > 0 ? a.tile_rows : 1) : fused_rows(strips_x, a.ny, K);
     const int ntiles = strips_x * ((a.ny + rows - 1) / rows);
+    const int stride = AM == sweep::AM_SEAM ? sweep::seam_stride(a.nx, S, MrtStrip<T, CPL, K>::P, CPL, sizeof(T)) : S;
     hipLaunchKernelGGL((mrt_fused_kernel<T, CPL, AM, K, WALLS>), (ntiles + 3) / 4, 256, 0, s, static_cast<const T *>(src),
-                       static_cast<T *>(dst), a.nx, a.ny, rows, strips_x, ntiles, k);
+                       static_cast<T *>(dst), a.nx, a.ny, rows, strips_x, stride, ntiles, k);
     return hipGetLastError();
 }
 
-template <typename T, int CPL, int AM>
+template <typename T, int CPL, int K>
+hipError_t run_width(const MrtArgs &a, MrtCoef<typename Storage<T>::C> k, const void *src, void *dst, hipStream_t s)
+{
+    using namespace sweep;
+    using G = MrtStrip<T, CPL, K>;
+    if (a.nx % CPL == 0)
+        return a.walls ? run_fused<T, CPL, AM_VEC, K, true>(a, k, src, dst, s)
+                       : run_fused<T, CPL, AM_VEC, K, false>(a, k, src, dst, s);
+    // 1021 x 770 FP64 in threes: 9.1 us per step through AM_UNAL's edge branches
+    if (seam_stride(a.nx, G::S, G::P, CPL, sizeof(T)) > 0)
+        return a.walls ? run_fused<T, CPL, AM_SEAM, K, true>(a, k, src, dst, s)
+                       : run_fused<T, CPL, AM_SEAM, K, false>(a, k, src, dst, s);
+    return a.walls ? run_fused<T, CPL, AM_UNAL, K, true>(a, k, src, dst, s)
+                   : run_fused<T, CPL, AM_UNAL, K, false>(a, k, src, dst, s);
+}
+
+template <typename T, int CPL>
 hipError_t run_steps(const MrtArgs &a, MrtCoef<typename Storage<T>::C> k, int steps, const void *src, void *dst, hipStream_t s)
 {
-    if (a.walls) switch (steps) {
-        case 1: return run_fused<T, CPL, AM, 1, true>(a, k, src, dst, s);
-        case 3: return run_fused<T, CPL, AM, 3, true>(a, k, src, dst, s);
-        case 5: return run_fused<T, CPL, AM, 5, true>(a, k, src, dst, s);
-        default: return hipErrorInvalidValue;
-        }
     switch (steps) {
-    case 1: return run_fused<T, CPL, AM, 1, false>(a, k, src, dst, s);
-    case 3: return run_fused<T, CPL, AM, 3, false>(a, k, src, dst, s);
-    case 5: return run_fused<T, CPL, AM, 5, false>(a, k, src, dst, s);
+    case 1: return run_width<T, CPL, 1>(a, k, src, dst, s);
+    case 3: return run_width<T, CPL, 3>(a, k, src, dst, s);
+    case 5: return run_width<T, CPL, 5>(a, k, src, dst, s);
     default: return hipErrorInvalidValue;
     }
 }
@@ -660,6 +759,32 @@ hipError_t run_xi(const MrtArgs &a, MrtCoef<typename Storage<T>::C> k, const voi
     return hipGetLastError();
 }
 
+template <typename T, int R>
+hipError_t run_tile(const MrtArgs &a, MrtCoef<typename Storage<T>::C> k, int steps, const void *src, void *dst, hipStream_t s)
+{
+    const int cols = 64 - 2 * steps, rows = MRT_TW * R - 2 * steps;
+    if (steps < 1 || cols < 1 || rows < 1) return hipErrorInvalidValue;
+    const int tiles_x = (a.nx + cols - 1) / cols, tiles = tiles_x * ((a.ny + rows - 1) / rows);
+    if (a.walls)
+        hipLaunchKernelGGL((mrt_tile_kernel<T, R, true>), tiles, 64 * MRT_TW, 0, s, static_cast<const T *>(src),
+                           static_cast<T *>(dst), a.nx, a.ny, steps, tiles_x, k);
+    else
+        hipLaunchKernelGGL((mrt_tile_kernel<T, R, false>), tiles, 64 * MRT_TW, 0, s, static_cast<const T *>(src),
+                           static_cast<T *>(dst), a.nx, a.ny, steps, tiles_x, k);
+    return hipGetLastError();
+}
+
+template <typename T> hipError_t run_tile(const MrtArgs &a, const TilePlan &p, const void *src, void *dst, hipStream_t s)
+{
+    using C = typename Storage<T>::C;
+    const MrtCoef<C> k{C(a.s_e), C(a.s_xx), C(a.s_q), C(a.s_eps), C(0.5 * a.fx), C(0.5 * a.fy), C(a.fx), C(a.fy)};
+    if (p.rows == 1) return run_tile<T, 1>(a, k, p.steps, src, dst, s);
+    if (p.rows == 2) return run_tile<T, 2>(a, k, p.steps, src, dst, s);
+    if constexpr (sizeof(T) < 8)
+        if (p.rows == 4) return run_tile<T, 4>(a, k, p.steps, src, dst, s);
+    return hipErrorInvalidValue;
+}
+
 template <typename T> hipError_t run(const MrtArgs &a, int steps, const void *src, void *dst, hipStream_t s)
 {
     using C = typename Storage<T>::C;
@@ -671,8 +796,7 @@ template <typename T> hipError_t run(const MrtArgs &a, int steps, const void *sr
             if (a.nx % 2 == 0) return run_xi<T, 2>(a, k, src, dst, s);
             return run_xi<T, 1>(a, k, src, dst, s);
         }
-        if (a.nx % CPL == 0) return run_steps<T, CPL, sweep::AM_VEC>(a, k, steps, src, dst, s);
-        return run_steps<T, CPL, sweep::AM_UNAL>(a, k, steps, src, dst, s);
+        return run_steps<T, CPL>(a, k, steps, src, dst, s);
     }
     dim3 blk(64, 4), grd((a.nx + 63) / 64, (a.ny + 3) / 4);
     if (a.walls)
@@ -696,6 +820,30 @@ int mrt_max_fused(const MrtArgs &a)
 {
     if (a.kernel == FDLBM_KERNEL_REFERENCE || (a.walls && a.xi != 0.5)) return 1;
     return 9 * (size_t)a.nx * (size_t)a.ny * dtype_bytes(a.dtype) >= (size_t(80) << 20) ? 5 : 3;
+}
+
+// Time of one step in launches of K = mrt_max_fused(a), in us (see fd_fused_us()); one stage of one
+// row of 64 CPL columns takes 0.9 us in FP32, 0.74 in FP64 (512^2, 1024^2, 2048^2).
+static double mrt_fused_us(const MrtArgs &a)
+{
+    const int K = mrt_max_fused(a), CPL = a.dtype == FDLBM_F64 ? 2 : 4;
+    const int P = (K + CPL - 1) / CPL, S = (64 - 2 * P) * CPL, strips = (a.nx + S - 1) / S;
+    const int rows = fused_rows(strips, a.ny, K);
+    const long each = ((long)strips * ((a.ny + rows - 1) / rows) + 1023) / 1024;
+    return 3.0 / K + double(each) * (rows + K - 1) * (a.dtype == FDLBM_F64 ? 0.74 : 0.9);
+}
+
+TilePlan mrt_tile_plan(const MrtArgs &a)
+{
+    if (a.kernel != FDLBM_KERNEL_AUTO || (a.walls && a.xi != 0.5)) return TilePlan();
+    const TileShape shapes[] = {{1, 1}, {1, 2}, {1, 4}};
+    const bool f64 = a.dtype == FDLBM_F64;
+    return plan_tiles(a.nx, a.ny, 1, f64 ? 8 : 4, f64 ? 0.9 : 0.7, shapes, f64 ? 2 : 3, mrt_fused_us(a));
+}
+
+hipError_t launch_mrt_tile(const MrtArgs &a, const TilePlan &p, const void *src, void *dst, hipStream_t s)
+{
+    return a.dtype == FDLBM_F64 ? run_tile<double>(a, p, src, dst, s) : run_tile<float>(a, p, src, dst, s);
 }
 
 hipError_t launch_mrt(const MrtArgs &a, int steps, const void *src, void *dst, hipStream_t s)

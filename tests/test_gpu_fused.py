@@ -1,8 +1,9 @@
 """Several steps in one launch against the one-step reference kernels, bit for bit.
 
-A call of n steps is dealt to launches of up to three steps; the state after it, and the buffer
-it lies in, are those of n single steps for every n, on grids whose widths and heights leave
-partial strips, bands shorter than the rows a fused launch reads beyond them, and halo rows
+A call of n steps is dealt to launches of several steps: of tiles held in registers on small grids
+(kernel "auto"), else of the fused sweep (which kernel "sweep" asks for).  The state after it, and
+the buffer it lies in, are those of n single steps for every n, on grids whose widths and heights
+leave partial strips, bands shorter than the rows a fused launch reads beyond them, and halo rows
 that wrap around the grid."""
 import numpy as np
 import pytest
@@ -26,20 +27,21 @@ def F():
 MRT_SHAPES = [(8, 8), (9, 13), (64, 4), (250, 45), (496, 17), (263, 8), (1021, 70), (37, 300), (240, 130)]
 
 
+@pytest.mark.parametrize("kernel", ["auto", "sweep"])
 @pytest.mark.parametrize("dtype", ["f32", "f64"])
 @pytest.mark.parametrize("bc", ["periodic", "walls"])
 @pytest.mark.parametrize("nx,ny", MRT_SHAPES)
-def test_mrt_steps_in_one_launch_equal_reference(F, nx, ny, bc, dtype):
+def test_mrt_steps_in_one_launch_equal_reference(F, nx, ny, bc, dtype, kernel):
     if bc == "periodic" and ny < 8:
         pytest.skip("periodic grids have at least eight rows")
     init = W.random_state(nx, ny, seed=nx + ny, amp=0.02)
     kw = dict(scheme="mrt", dtype=dtype, bc=bc, s_xx=1.3, s_e=1.1, s_eps=1.2, s_q=1.4, force=(2e-5, -1e-5))
     ref = F.FdLbm(nx, ny, kernel="reference", **kw)
-    got = F.FdLbm(nx, ny, **kw)
+    got = F.FdLbm(nx, ny, kernel=kernel, **kw)
     ref.set_state(*init)
     got.set_state(*init)
-    for n in (3, 1, 2, 4, 5, 8, 14):
-        print(f"  mrt fused {nx}x{ny} {bc} {dtype} +{n}", flush=True)
+    for n in (3, 1, 2, 4, 5, 8, 14, 37):
+        print(f"  mrt {kernel} {nx}x{ny} {bc} {dtype} +{n}", flush=True)
         ref.step(n)
         got.step(n)
         assert got.steps == ref.steps
@@ -76,11 +78,12 @@ FD_SHAPES = [(8, 8), (9, 13), (64, 12), (250, 45), (240, 17), (263, 9), (502, 16
 FD_KINDS = [("fd", 3, "periodic", 0.5), ("fd", 3, "walls", 0.5), ("fd", 3, "walls", 0.8), ("fd", 5, "periodic", 0.5), ("lwacm", 3, "periodic", 0.5)]
 
 
+@pytest.mark.parametrize("kernel", ["auto", "sweep"])
 @pytest.mark.parametrize("dtype", ["f32", "f64", "f16"])
 @pytest.mark.parametrize("scheme,stencil,bc,xi", FD_KINDS)
 @pytest.mark.parametrize("forced", [False, True])
 @pytest.mark.parametrize("nx,ny", FD_SHAPES)
-def test_fd_steps_in_one_launch_equal_reference(F, nx, ny, scheme, stencil, bc, xi, dtype, forced):
+def test_fd_steps_in_one_launch_equal_reference(F, nx, ny, scheme, stencil, bc, xi, dtype, forced, kernel):
     if forced and scheme == "lwacm":
         pytest.skip("the LW-ACM step has no body force")
     init = W.random_state(nx, ny, seed=nx + ny, amp=0.02)
@@ -88,11 +91,11 @@ def test_fd_steps_in_one_launch_equal_reference(F, nx, ny, scheme, stencil, bc, 
     if scheme == "fd":
         kw.update(stencil=stencil, wall_xi=xi, force=(2e-5, -1e-5) if forced else (0.0, 0.0))
     ref = F.FdLbm(nx, ny, kernel="reference", **kw)
-    got = F.FdLbm(nx, ny, **kw)
+    got = F.FdLbm(nx, ny, kernel=kernel, **kw)
     ref.set_state(*init)
     got.set_state(*init)
-    for n in (3, 1, 2, 4, 8):
-        print(f"  {scheme}{stencil} fused {nx}x{ny} {bc} xi {xi} {dtype} +{n}", flush=True)
+    for n in (3, 1, 2, 4, 8, 21):
+        print(f"  {scheme}{stencil} {kernel} {nx}x{ny} {bc} xi {xi} {dtype} +{n}", flush=True)
         ref.step(n)
         got.step(n)
         name = "state_b" if got.steps % 2 else "state_a"
