@@ -42,10 +42,11 @@ struct Plan {
     std::vector<BatchInstance> inst;
     std::vector<BatchBlock> blocks;
     std::vector<BatchChunk> chunks;
+    std::vector<BatchWave> waves[BATCH_FUSED];
     int class_begin[BATCH_CLASSES] = {}, class_blocks[BATCH_CLASSES] = {};
     size_t state_elems = 0, mode_elems = 0, max_n = 0;
     // scratch offsets (bytes)
-    size_t o_inst, o_blocks, o_chunks, o_partials, o_counter, o_amps, o_mode, o_staging, total;
+    size_t o_inst, o_blocks, o_chunks, o_waves[BATCH_FUSED], o_partials, o_counter, o_amps, o_mode, o_staging, total;
 };
 
 int validate(const fdlbm_instance *in, int32_t count, int32_t dtype, int32_t max_samples)
@@ -99,6 +100,45 @@ void tile_tables(Plan &P, int rows)
     }
 }
 
+// The wavefronts of the launch that takes `steps` steps.  Rows per wavefront: a wavefront of R rows
+// forms R + 2 + 2 (steps - 1) per step, and the launch ends with the last wavefront, so the work per
+// SIMD plus one wavefront's own is least; an instance's rows are dealt evenly to its bands, and
+// the tallest wavefronts start first.
+void wave_table(Plan &P, int dtype, int steps)
+{
+    const int extra = 2 * steps;
+    std::vector<BatchStrips> strips;
+    for (const BatchInstance &I : P.inst) strips.push_back(batch_strips(I.nx, dtype, steps));
+    int best = 8;
+    double best_cost = -1.0;
+    for (int rows = 4; rows <= 128; rows += rows < 32 ? 2 : 8) {
+        double work = 0.0;
+        for (size_t i = 0; i < P.inst.size(); ++i) {
+            const double bands = (P.inst[i].ny + rows - 1) / rows;
+            work += strips[i].count * (0.4 + 0.6 * strips[i].cols / 2) * (P.inst[i].ny + bands * extra);
+        }
+        const double cost = work / 1024.0 + (rows + extra);
+        if (best_cost < 0.0 || cost < best_cost) {
+            best_cost = cost;
+            best = rows;
+        }
+    }
+    std::vector<BatchWave> &W = P.waves[steps - BATCH_FUSED_MIN];
+    W.clear();
+    for (size_t i = 0; i < P.inst.size(); ++i) {
+        const int ny = P.inst[i].ny, bands = (ny + best - 1) / best;
+        for (int b = 0; b < bands; ++b) {
+            const int y0 = (int)((int64_t)ny * b / bands), y1 = (int)((int64_t)ny * (b + 1) / bands);
+            for (int t = 0; t < strips[i].count; ++t)
+                W.push_back(BatchWave{(int)i, t == strips[i].count - 1 ? strips[i].last : t * strips[i].stride, y0,
+                                      (short)(y1 - y0), (short)strips[i].cols});
+        }
+    }
+    std::stable_sort(W.begin(), W.end(), [](const BatchWave &a, const BatchWave &b) {
+        return a.cols != b.cols ? a.cols > b.cols : a.rows > b.rows;
+    });
+}
+
 // Point a launch description at the block table the plan holds.
 void use_tables(BatchLaunch &L, const Plan &P, int rows)
 {
@@ -128,7 +168,8 @@ Plan plan(const fdlbm_instance *in, int32_t count, int32_t dtype, int32_t max_sa
         const int S = batch_strip_stride(batch_class_cpl(I.cls, dtype));
         I.strips_x = (I.nx + S - 1) / S;
         I.first_chunk = chunk0;
-        I.nchunks = (int)((n + BATCH_CHUNK - 1) / BATCH_CHUNK);
+        I.chunk = (int)std::max<size_t>(BATCH_CHUNK, (n + 4095) / 4096);
+        I.nchunks = (int)((n + I.chunk - 1) / I.chunk);
         chunk0 += I.nchunks;
         I.ke = 0.5 * (1.0 - 1.0 / in[i].s_e);
         I.kxx = 0.5 * (1.0 - 1.0 / in[i].s_xx);
@@ -139,6 +180,7 @@ Plan plan(const fdlbm_instance *in, int32_t count, int32_t dtype, int32_t max_sa
     tile_tables(P, BATCH_MIN_ROWS);
     const size_t max_blocks = P.blocks.size();
     tile_tables(P, BATCH_ROWS);
+    for (int k = BATCH_FUSED_MIN; k <= BATCH_FUSED_MAX; ++k) wave_table(P, dtype, k);
     size_t off = 0;
     auto take = [&](size_t bytes) {
         const size_t o = off;
@@ -148,6 +190,7 @@ Plan plan(const fdlbm_instance *in, int32_t count, int32_t dtype, int32_t max_sa
     P.o_inst = take(sizeof(BatchInstance) * P.inst.size());
     P.o_blocks = take(sizeof(BatchBlock) * max_blocks);
     P.o_chunks = take(sizeof(BatchChunk) * P.chunks.size());
+    for (int q = 0; q < BATCH_FUSED; ++q) P.o_waves[q] = take(sizeof(BatchWave) * P.waves[q].size());
     P.o_partials = take(2 * sizeof(double) * P.chunks.size());
     P.o_counter = take(sizeof(int));
     P.o_amps = take(sizeof(double) * (size_t)count * (size_t)std::max(max_samples, 1));
@@ -191,11 +234,28 @@ template <typename Body> int guarded(Body &&body)
     }
 }
 
+// Steps in launches of three, two and one.  Every launch changes the buffer, so with twos in pairs
+// the current buffer is that of as many single steps.
 int launch_chunk(fdlbm_batch *b, int steps, bool sample)
 {
-    for (int s = 0; s < steps; ++s) {
-        BHIPCHK(launch_batch_step(b->L, b->buf[b->cur], b->buf[b->cur ^ 1], b->stream), "batch step launch");
+    int threes = steps / 3, twos = 0;
+    const int rest = steps % 3;
+    if (rest == 1 && threes >= 1) {
+        threes -= 1;
+        twos = 2;
+    } else if (rest == 2 && threes >= 1) {
+        twos = threes >= 2 ? 4 : 2;
+        threes -= threes >= 2 ? 2 : 1;
+    }
+    for (int left = steps; left > 0;) {
+        const int k = threes > 0 ? 3 : twos > 0 ? 2 : 1;
+        (k == 3 ? threes : twos) -= k > 1;
+        const void *src = b->buf[b->cur];
+        void *dst = b->buf[b->cur ^ 1];
+        BHIPCHK(k > 1 ? launch_batch_fused(b->L, k, src, dst, b->stream) : launch_batch_step(b->L, src, dst, b->stream),
+                "batch step launch");
         b->cur ^= 1;
+        left -= k;
     }
     if (sample) BHIPCHK(launch_batch_sample(b->L, b->buf[b->cur], b->stream), "batch sample launch");
     return FDLBM_OK;
@@ -253,6 +313,10 @@ int fdlbm_batch_create(const fdlbm_instance *instances, int32_t count, int32_t d
         L.inst = reinterpret_cast<const BatchInstance *>(b->scratch + P.o_inst);
         L.blocks = reinterpret_cast<const BatchBlock *>(b->scratch + P.o_blocks);
         L.chunks = reinterpret_cast<const BatchChunk *>(b->scratch + P.o_chunks);
+        for (int q = 0; q < BATCH_FUSED; ++q) {
+            L.waves[q] = reinterpret_cast<const BatchWave *>(b->scratch + P.o_waves[q]);
+            L.nwaves[q] = (int)P.waves[q].size();
+        }
         L.mode = b->scratch + P.o_mode;
         L.partials = reinterpret_cast<double *>(b->scratch + P.o_partials);
         L.counter = reinterpret_cast<int *>(b->scratch + P.o_counter);
@@ -265,6 +329,9 @@ int fdlbm_batch_create(const fdlbm_instance *instances, int32_t count, int32_t d
                                                 hipMemcpyHostToDevice, b->stream);
         if (e == hipSuccess) e = hipMemcpyAsync(b->scratch + P.o_chunks, P.chunks.data(), sizeof(BatchChunk) * P.chunks.size(),
                                                 hipMemcpyHostToDevice, b->stream);
+        for (int q = 0; q < BATCH_FUSED && e == hipSuccess; ++q)
+            e = hipMemcpyAsync(b->scratch + P.o_waves[q], P.waves[q].data(), sizeof(BatchWave) * P.waves[q].size(),
+                               hipMemcpyHostToDevice, b->stream);
         if (e == hipSuccess) e = hipMemsetAsync(state_a, 0, sb, b->stream);
         if (e == hipSuccess) e = hipMemsetAsync(state_b, 0, sb, b->stream);
         if (e == hipSuccess) e = hipMemsetAsync(b->scratch + P.o_counter, 0, sizeof(int), b->stream);

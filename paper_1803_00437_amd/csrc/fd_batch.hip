@@ -7,8 +7,10 @@
 // Each block looks up (instance, tile) in a table built on the host and runs the same
 // tile body as the single-grid kernel, so every instance evolves exactly as it would
 // alone.  Instances are grouped by lane class (vector or per-column accesses, see
-// BATCH_CLASSES); each class is one launch.
-#include "fd_sweep_body.hpp"
+// BATCH_CLASSES); each class is one launch of the one-step kernel.
+//
+// Two or three steps together take one launch for every instance (fd_batch_fused_kernel).
+#include "fd_fused_body.hpp"
 #include "internal.hpp"
 
 namespace fdlbm {
@@ -44,6 +46,51 @@ __global__ void __launch_bounds__(64 * WV) fd_batch_kernel(const T *__restrict__
     const int band = b.tile / I.strips_x;
     const int sx = b.tile - band * I.strips_x;
     sweep_tile<T, CPL, 3, false, false, AM>(t, band, sx * Strip<CPL, 1>::S, sx == I.strips_x - 1);
+}
+
+// K steps of every instance: each wavefront looks up its instance, columns and rows and runs the
+// body of fd_fused_kernel.  Two columns per lane where the width allows, else one: a strip of 512
+// four-column lanes fits the widths of small grids badly (32 .. 512 columns: 62 % of the columns
+// computed are stored, 81 % with two), and two leave registers for more wavefronts.  128 grids of
+// 32 .. 512 columns (12 M nodes), FP32: 97 us per step one by one in two classes.
+template <typename T, int CPL, int AM, int K, typename L>
+__device__ __forceinline__ void batch_wave(const FusedArgs<T, K> &a, const BatchWave &b, L *lds, int lane)
+{
+    using C = typename Storage<T>::C;
+    using G = FusedStrip<CPL, 1, K>;
+    const int xl = b.x0 - G::P * CPL + CPL * lane;
+    const LaneCols<CPL, AM> lc = make_lane_cols<T, CPL, AM>(xl, a.nx, lane >= G::P && lane < 64 - G::P);
+    fused_tile<1, T, CPL, 3, false, false, AM, K, 1, K>(a, reinterpret_cast<Group<C, CPL>(*)[64]>(lds), lane, xl, lc, b.y0,
+                                                        b.y0 + b.rows);
+}
+
+template <typename T, int K>
+__global__ void __launch_bounds__(64 * WV, sizeof(T) == 8 ? 2 : 3)
+    fd_batch_fused_kernel(const T *__restrict__ in, T *__restrict__ out, const BatchInstance *__restrict__ inst,
+                          const BatchWave *__restrict__ waves, int nwaves)
+{
+    using C = typename Storage<T>::C;
+    __shared__ Group<C, 2> lds[WV][fused_lds_slots<1, false, K, 1, K>()][64];
+    const int lane = threadIdx.x & 63, wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int i = blockIdx.x * WV + wv;
+    if (i >= nwaves) return;  // uniform over the wavefront; there is no barrier
+    const BatchWave b = waves[i];
+    const BatchInstance I = inst[b.instance];
+    FusedArgs<T, K> a;
+    a.in = in + I.offset;
+    a.out = out + I.offset;
+    a.nx = I.nx;
+    a.ny = I.ny;
+    a.k.eax = C(-2.0 * I.ke / 36.0);
+    a.k.edg = C(2.0 * I.ke / 18.0);
+    a.k.e0 = C(-2.0 * I.ke / 9.0);
+    a.k.kxx = C(I.kxx);
+    a.k.kxx2 = C(2.0 * I.kxx);
+    a.k.hfx = a.k.hfy = a.k.qfx = a.k.qfy = a.k.dfx = a.k.dfy = C(0);
+    if (b.cols == 2)
+        batch_wave<T, 2, AM_SEAM, K>(a, b, lds[wv], lane);
+    else
+        batch_wave<T, 1, AM_VEC, K>(a, b, lds[wv], lane);
 }
 
 // Single instance in the same tiling: the one-launch-per-grid path of the comparison.
@@ -92,7 +139,7 @@ __global__ void __launch_bounds__(PROJ_TPB) proj_partials(const T *__restrict__ 
     const BatchChunk ch = chunks[blockIdx.x];
     const BatchInstance I = inst[ch.instance];
     const size_t n = (size_t)I.nx * (size_t)I.ny;
-    const size_t p0 = (size_t)ch.chunk * BATCH_CHUNK, p1 = p0 + BATCH_CHUNK < n ? p0 + BATCH_CHUNK : n;
+    const size_t p0 = (size_t)ch.chunk * I.chunk, p1 = p0 + I.chunk < n ? p0 + I.chunk : n;
     const T *st = state + I.offset;
     const T *mx = mode + I.mode_offset, *my = mx + n;  // the mode: two planes
     const unsigned nx = (unsigned)I.nx;
@@ -122,22 +169,26 @@ __global__ void __launch_bounds__(PROJ_TPB) proj_partials(const T *__restrict__ 
     }
 }
 
-// A = sum num / sum den per instance, written to sample slot *counter (dropped once the
-// slots are full).
-__global__ void proj_final(const BatchInstance *__restrict__ inst, int count, const double *__restrict__ partials,
-                           const int *__restrict__ counter, int max_samples, double *__restrict__ amps)
+// A = sum num / sum den per instance (one wavefront each, fixed order), written to sample slot
+// *counter (dropped once the slots are full).
+__global__ void __launch_bounds__(PROJ_TPB) proj_final(const BatchInstance *__restrict__ inst, int count,
+                                                       const double *__restrict__ partials,
+                                                       const int *__restrict__ counter, int max_samples,
+                                                       double *__restrict__ amps)
 {
-    const int i = blockIdx.x * blockDim.x + threadIdx.x;
+    const int i = blockIdx.x * (PROJ_TPB / 64) + (threadIdx.x >> 6), lane = threadIdx.x & 63;
     if (i >= count) return;
     const int s = *counter;
     if (s >= max_samples) return;
     const BatchInstance I = inst[i];
     double num = 0.0, den = 0.0;
-    for (int c = 0; c < I.nchunks; ++c) {
+    for (int c = lane; c < I.nchunks; c += 64) {
         num += partials[2 * (I.first_chunk + c)];
         den += partials[2 * (I.first_chunk + c) + 1];
     }
-    amps[(size_t)i * max_samples + s] = den > 0.0 ? num / den : 0.0;
+    num = wave_sum(num);
+    den = wave_sum(den);
+    if (lane == 0) amps[(size_t)i * max_samples + s] = den > 0.0 ? num / den : 0.0;
 }
 
 __global__ void advance_counter(int *counter) { *counter += 1; }
@@ -185,7 +236,7 @@ template <typename T> hipError_t sample(const BatchLaunch &L, const void *state,
                        static_cast<const T *>(L.mode), L.inst, L.chunks, L.partials);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(proj_final, (L.count + 255) / 256, 256, 0, s, L.inst, L.count, L.partials, L.counter,
+    hipLaunchKernelGGL(proj_final, (L.count + PROJ_TPB / 64 - 1) / (PROJ_TPB / 64), PROJ_TPB, 0, s, L.inst, L.count, L.partials, L.counter,
                        L.max_samples, L.amps);
     e = hipGetLastError();
     if (e != hipSuccess) return e;
@@ -194,6 +245,45 @@ template <typename T> hipError_t sample(const BatchLaunch &L, const void *state,
 }
 
 }  // namespace
+
+// Strips of an instance for the fused kernel: two columns per lane if no lane then crosses the
+// periodic edge, else one.
+BatchStrips batch_strips(int nx, int dtype, int steps)
+{
+    const int S2 = steps == 3 ? FusedStrip<2, 1, 3>::S : FusedStrip<2, 1, 2>::S,
+              P2 = steps == 3 ? FusedStrip<2, 1, 3>::P : FusedStrip<2, 1, 2>::P,
+              S1 = steps == 3 ? FusedStrip<1, 1, 3>::S : FusedStrip<1, 1, 2>::S;
+    const int seam = seam_stride(nx, S2, P2, 2, (int)dtype_bytes(dtype));
+    if (seam > 0) return BatchStrips{2, (nx + S2 - 1) / S2, seam, nx - S2};
+    if (nx % 2 == 0) return BatchStrips{2, (nx + S2 - 1) / S2, S2, ((nx + S2 - 1) / S2 - 1) * S2};
+    return BatchStrips{1, (nx + S1 - 1) / S1, S1, ((nx + S1 - 1) / S1 - 1) * S1};
+}
+
+hipError_t launch_batch_fused(const BatchLaunch &L, int steps, const void *src, void *dst, hipStream_t s)
+{
+    const int q = steps - BATCH_FUSED_MIN, n = L.nwaves[q], blocks = (n + WV - 1) / WV;
+    const BatchWave *w = L.waves[q];
+    switch (L.dtype) {
+    case FDLBM_F64:
+        if (steps == 3)
+            hipLaunchKernelGGL((fd_batch_fused_kernel<double, 3>), blocks, 64 * WV, 0, s, (const double *)src, (double *)dst, L.inst, w, n);
+        else
+            hipLaunchKernelGGL((fd_batch_fused_kernel<double, 2>), blocks, 64 * WV, 0, s, (const double *)src, (double *)dst, L.inst, w, n);
+        break;
+    case FDLBM_F32:
+        if (steps == 3)
+            hipLaunchKernelGGL((fd_batch_fused_kernel<float, 3>), blocks, 64 * WV, 0, s, (const float *)src, (float *)dst, L.inst, w, n);
+        else
+            hipLaunchKernelGGL((fd_batch_fused_kernel<float, 2>), blocks, 64 * WV, 0, s, (const float *)src, (float *)dst, L.inst, w, n);
+        break;
+    default:
+        if (steps == 3)
+            hipLaunchKernelGGL((fd_batch_fused_kernel<__half, 3>), blocks, 64 * WV, 0, s, (const __half *)src, (__half *)dst, L.inst, w, n);
+        else
+            hipLaunchKernelGGL((fd_batch_fused_kernel<__half, 2>), blocks, 64 * WV, 0, s, (const __half *)src, (__half *)dst, L.inst, w, n);
+    }
+    return hipGetLastError();
+}
 
 int batch_strip_stride(int cpl) { return cpl == 4 ? Strip<4, 1>::S : cpl == 2 ? Strip<2, 1>::S : Strip<1, 1>::S; }
 int batch_rows_per_block(int rows) { return WV * rows; }

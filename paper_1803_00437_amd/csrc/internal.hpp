@@ -95,13 +95,15 @@ double fd_fused_us(const FdArgs &a);
 hipError_t launch_fd_tile(const FdArgs &a, const TilePlan &p, const void *src, void *dst, hipStream_t s);
 
 // Batch of independent periodic FD-LBM grids (3-point differences) -------------------
-constexpr int BATCH_CHUNK = 65536;  // nodes per block of the A(t) reduction
+// Nodes per block of the A(t) reduction (more for an instance that would make over 4096 blocks):
+// 65536 left most of the device idle (158 us for 12 M nodes).
+constexpr int BATCH_CHUNK = 8192;
 struct BatchInstance {
     size_t offset;       // element offset of the instance's state (row-interleaved) in the state buffers
     size_t mode_offset;  // element offset of its J0 planes (jx, jy) in the mode buffer
     int nx, ny, strips_x, nbands;
     int cls;             // lane class of its tiles (BATCH_CLASSES)
-    int first_chunk, nchunks;
+    int first_chunk, nchunks, chunk;  // chunk: nodes each
     double ke, kxx;      // (1 - 1/s_e) / 2 and (1 - 1/s_xx) / 2 (3-point scale folded in)
 };
 struct BatchBlock {
@@ -110,6 +112,17 @@ struct BatchBlock {
 struct BatchChunk {
     int instance, chunk;
 };
+// Several steps in one launch, BATCH_FUSED_MIN .. BATCH_FUSED_MAX: one wavefront's part, columns from x0
+// on (cols per lane) of rows y0 .. y0 + rows - 1.
+constexpr int BATCH_FUSED_MIN = 2, BATCH_FUSED_MAX = 3, BATCH_FUSED = BATCH_FUSED_MAX - BATCH_FUSED_MIN + 1;
+struct BatchWave {
+    int instance, x0, y0;
+    short rows, cols;
+};
+struct BatchStrips {
+    int cols, count, stride, last;  // columns per lane; strips, `stride` columns apart, the last one at `last`
+};
+BatchStrips batch_strips(int nx, int dtype, int steps);
 // Lane classes of the batched step, one launch each; W = 4 columns per lane (FP32, FP16)
 // or 2 (FP64):
 //   0: W columns as one vector access (nx a multiple of W)
@@ -126,6 +139,8 @@ struct BatchLaunch {
     const BatchInstance *inst;
     const BatchBlock *blocks;
     const BatchChunk *chunks;
+    const BatchWave *waves[BATCH_FUSED];
+    int nwaves[BATCH_FUSED];
     const void *mode;
     double *partials;
     int *counter;
@@ -134,6 +149,7 @@ struct BatchLaunch {
 int batch_strip_stride(int cpl);  // columns stored per strip at `cpl` columns per lane
 int batch_rows_per_block(int rows);
 hipError_t launch_batch_step(const BatchLaunch &L, const void *src, void *dst, hipStream_t s);
+hipError_t launch_batch_fused(const BatchLaunch &L, int steps, const void *src, void *dst, hipStream_t s);
 hipError_t launch_batch_single(const BatchLaunch &L, int i, int cls, int nblocks, const void *src, void *dst,
                                hipStream_t s);
 hipError_t launch_batch_sample(const BatchLaunch &L, const void *state, hipStream_t s);

@@ -105,6 +105,31 @@ def test_fd_steps_in_one_launch_equal_reference(F, nx, ny, scheme, stencil, bc, 
     ref.close()
 
 
+@pytest.mark.parametrize("dtype", ["f32", "f64", "f16"])
+def test_batch_steps_in_one_launch_equal_reference(F, dtype):
+    """Widths around the strips of two and three steps (116, 120 and 52, 56 columns), odd and even."""
+    sizes = [(8, 8), (9, 30), (52, 9), (57, 120), (115, 11), (116, 64), (121, 45), (123, 123), (124, 17), (129, 8),
+             (236, 33), (239, 70), (241, 240), (512, 100)]
+    specs = [(nx, ny, 1.2 + 0.01 * i, 1.1) for i, (nx, ny) in enumerate(sizes)]
+    batch = F.FdLbmBatch(specs, dtype=dtype, max_samples=4)
+    refs = []
+    for i, (nx, ny, s_xx, s_e) in enumerate(specs):
+        init = W.random_state(nx, ny, seed=i, amp=0.02)
+        batch.set_state(i, *init)
+        refs.append(F.FdLbm(nx, ny, dtype=dtype, s_xx=s_xx, s_e=s_e, kernel="reference"))
+        refs[-1].set_state(*init)
+    for n, every in ((1, 0), (2, 0), (5, 0), (10, 5), (7, 7), (13, 0)):
+        print(f"  batch {dtype} +{n} every {every}", flush=True)
+        batch.step(n, sample_every=every)
+        batch.stream.synchronize()
+        for i, ref in enumerate(refs):
+            ref.step(n)
+            assert all(np.array_equal(a, b) for a, b in zip(batch.get_state(i), ref.get_state())), sizes[i]
+    batch.close()
+    for ref in refs:
+        ref.close()
+
+
 @pytest.mark.parametrize("dtype", ["f32", "f64"])
 @pytest.mark.parametrize("nx,ny,nz", [(3, 3, 3), (61, 11, 5), (64, 10, 2 * 37 + 1), (120, 21, 130), (256, 130, 9)])
 def test_d3_planes_chosen_from_the_grid_equal_reference(F, nx, ny, nz, dtype):
