@@ -42,6 +42,7 @@ double quartic(double s_xx) { return 1.0 / (0.5 + 1.0 / (6.0 * (1.0 / s_xx - 0.5
 struct Layout {
     size_t partials, out, mode, staging, fstar;
     size_t disk_dst, disk_src, disk_w, disk_span, disk_ring;  // ghost-node table (FDLBM_BC_DISK)
+    size_t disk_map;                                          // per node, where tiles take the steps
     size_t mdisk_node, mdisk_kb, mdisk_q, mdisk_ring, mdisk_fspan;  // MRT boundary links (FDLBM_BC_DISK)
     size_t total;
 };
@@ -89,9 +90,10 @@ int max_fused(const fdlbm_params &p, double s_q)
 // Tiles that stay in registers for several steps, where they are the faster way.
 TilePlan tile_plan(const fdlbm_params &p, double s_q)
 {
-    if (p.bc == FDLBM_BC_DISK || p.kernel != FDLBM_KERNEL_AUTO || uses_reference(p) || p.tile_rows != 0 || p.lane_cols != 0)
-        return TilePlan();
-    return three_words(p.scheme) ? fd_tile_plan(fd_args(p)) : mrt_tile_plan(mrt_args(p, s_q));
+    const bool disk = p.bc == FDLBM_BC_DISK;
+    if (p.kernel != FDLBM_KERNEL_AUTO || uses_reference(p) || p.tile_rows != 0 || p.lane_cols != 0) return TilePlan();
+    if (three_words(p.scheme)) return fd_tile_plan(fd_args(p), disk);
+    return disk ? TilePlan() : mrt_tile_plan(mrt_args(p, s_q));
 }
 
 int validate(const fdlbm_params *p)
@@ -171,6 +173,8 @@ Layout layout(const fdlbm_params &p)
     off += p.bc == FDLBM_BC_DISK && three_words(p.scheme) ? align256(sizeof(int32_t) * 2 * size_t(p.ny)) : 0;
     L.disk_ring = off;
     off += align256(sizeof(int32_t) * nr);
+    L.disk_map = off;
+    if (p.bc == FDLBM_BC_DISK && tile_plan(p, p.s_q).steps > 0) off += align256(sizeof(int32_t) * n);
     L.mdisk_node = off;
     off += align256(sizeof(int32_t) * nl);
     L.mdisk_kb = off;
@@ -216,6 +220,7 @@ struct fdlbm_ctx {
     bool disk_full;  // the next fill sets every rest node to rest (the state was just set)
     int most;        // steps that one launch may take
     TilePlan tile;   // tile.steps > 0: launches of tiles, up to so many steps each
+    TileDisk tdisk;  // FDLBM_BC_DISK: the tiles' view of the ghost-node table
 
     size_t n() const { return (size_t)p.nx * (size_t)p.ny; }
     double *sd(size_t off) const { return reinterpret_cast<double *>(scratch + off); }
@@ -268,6 +273,7 @@ int fdlbm_create(const fdlbm_params *p, void *state_a, void *state_b, void *scra
         if (e == hipSuccess) e = hipMemsetAsync(state_a, 0, sb, c->stream);
         if (e == hipSuccess) e = hipMemsetAsync(state_b, 0, sb, c->stream);
         DiskTable t;  // outlives the uploads: the stream is synchronised below
+        std::vector<int32_t> map;
         if (e == hipSuccess && p->bc == FDLBM_BC_DISK && !three_words(p->scheme)) {
             if (!disk_table(*p, &t)) {
                 delete c;
@@ -308,7 +314,19 @@ int fdlbm_create(const fdlbm_params *p, void *state_a, void *state_b, void *scra
             c->disk.nring = int(t.ring.size());
             c->disk.ring = reinterpret_cast<const int32_t *>(sc + L.disk_ring);
             const size_t ng = t.dst.size(), nr = t.ring.size();
-            if (ng) e = hipMemcpyAsync(sc + L.disk_dst, t.dst.data(), ng * sizeof(int32_t), hipMemcpyHostToDevice, c->stream);
+            if (c->tile.steps > 0) {
+                map.assign(c->n(), DISK_REST);
+                for (int j = 0; j < p->ny; ++j)
+                    for (int i = t.span[2 * size_t(j)]; i <= t.span[2 * size_t(j) + 1]; ++i)
+                        map[size_t(j) * p->nx + i] = DISK_FLUID;
+                for (size_t g = 0; g < ng; ++g) map[size_t(t.dst[g])] = int32_t(g);
+                c->tdisk.map = reinterpret_cast<const int32_t *>(sc + L.disk_map);
+                c->tdisk.src = c->disk.src;
+                c->tdisk.w = c->disk.w;
+                e = hipMemcpyAsync(sc + L.disk_map, map.data(), map.size() * sizeof(int32_t), hipMemcpyHostToDevice,
+                                   c->stream);
+            }
+            if (e == hipSuccess && ng) e = hipMemcpyAsync(sc + L.disk_dst, t.dst.data(), ng * sizeof(int32_t), hipMemcpyHostToDevice, c->stream);
             if (e == hipSuccess && ng)
                 e = hipMemcpyAsync(sc + L.disk_src, t.src.data(), ng * sizeof(int32_t), hipMemcpyHostToDevice, c->stream);
             if (e == hipSuccess && ng)
@@ -519,7 +537,9 @@ static int advance(fdlbm_ctx *c, int64_t nsteps)
                 tile.steps = i < l.high ? l.low + 2 : l.low;
                 const void *src = c->buf[c->cur];
                 void *dst = c->buf[c->cur ^ 1];
-                HIPCHK(fd ? launch_fd_tile(fa, tile, src, dst, c->stream) : launch_mrt_tile(ma, tile, src, dst, c->stream),
+                fa.step = uint32_t(c->steps);
+                HIPCHK(fd ? launch_fd_tile(fa, tile, c->tdisk, src, dst, c->stream)
+                          : launch_mrt_tile(ma, tile, src, dst, c->stream),
                        "step launch");
                 c->cur ^= 1;
                 c->steps += tile.steps;

@@ -125,13 +125,24 @@ int fd_max_fused(const FdArgs &a)
 // Time of one step in launches of K = fd_max_fused(a), in us: the wavefronts each SIMD gets times the
 // rows each takes through K stages of us_row each, and 3 us per launch.  us_row is measured (one
 // stage of one row of 64 CPL columns: 256^2, 1024^2, 2048^2).
+static double fused_row_us(const FdArgs &a)
+{
+    const bool f64 = a.dtype == FDLBM_F64;
+    return a.stencil == 1 ? (f64 ? 0.27 : 0.37) : a.stencil == 3 ? (f64 ? 0.52 : 0.62) : (f64 ? 0.7 : 0.68);
+}
+// the one-step kernel: blocks of 4 x 8 (FP64 6) rows, two or three at once on a compute unit
+double fd_single_us(const FdArgs &a)
+{
+    const int rows = a.dtype == FDLBM_F64 ? 6 : 8, S = a.dtype == FDLBM_F64 ? 124 : 248;
+    const long blocks = (long)((a.nx + S - 1) / S) * ((a.ny + 4 * rows - 1) / (4 * rows)), each = (blocks + 255) / 256;
+    return 3.0 + double((rows + 4) * each) * fused_row_us(a);
+}
 double fd_fused_us(const FdArgs &a)
 {
     const int K = fd_max_fused(a), H = a.stencil == 1 ? 0 : a.stencil == 3 ? 1 : 2, CPL = a.dtype == FDLBM_F64 ? 2 : 4;
-    const bool f64 = a.dtype == FDLBM_F64;
-    const double us_row = H == 0 ? (f64 ? 0.27 : 0.37) : H == 1 ? (f64 ? 0.52 : 0.62) : (f64 ? 0.7 : 0.68);
+    const double us_row = fused_row_us(a);
     const int P = (K * (H + 1) + CPL - 1) / CPL, S = (64 - 2 * P) * CPL, strips = (a.nx + S - 1) / S;
-    if (K == 1) return 3.0 + 14.0 * us_row * ((strips * ((a.ny + 7) / 8) + 1023) / 1024);
+    if (K == 1) return fd_single_us(a);
     const int rows = fused_rows(strips, a.ny, K, H, a.walls != 0, a.stencil == 5 ? 1 : 2);
     const long each = ((long)strips * ((a.ny + rows - 1) / rows) + 1023) / 1024;
     return 3.0 / K + double(each) * (rows + 2 * K * (H + 1)) * us_row;

@@ -29,11 +29,13 @@ template <typename T> struct TileStepArgs {
     const T *in;
     T *out;
     int nx, ny, steps, tiles_x, halo;  // halo = steps (H + 1)
+    uint32_t step0;     // stochastic rounding: the step count before the first step
+    TileDisk disk;      // DISK
     FdCoef<typename Storage<T>::C> k;
     GhostRules<typename Storage<T>::C> gr;
 };
 
-template <typename T, int CPL, int R, int ST, bool WALLS, bool FORCE>
+template <typename T, int CPL, int R, int ST, bool WALLS, bool FORCE, bool DISK>
 __global__ void __launch_bounds__(64 * TW) fd_tile_kernel(TileStepArgs<T> a)
 {
     using C = typename Storage<T>::C;
@@ -60,11 +62,33 @@ __global__ void __launch_bounds__(64 * TW) fd_tile_kernel(TileStepArgs<T> a)
     C v[R][3][CPL];
 #pragma unroll
     for (int i = 0; i < R; ++i) {
-        const T *row = a.in + fd_elem(0, grid_row(y0 + i), 0, nx);
+        const int y = grid_row(y0 + i);
+        const T *row = a.in + fd_elem(0, y, 0, nx);
 #pragma unroll
-        for (int f = 0; f < 3; ++f)
+        for (int c = 0; c < CPL; ++c) {
+            // the curved wall: ghost nodes from the fluid, as disk_fill_kernel sets them, and rest
+            // nodes at rest (the fill and the step in one launch)
+            const int g = DISK ? a.disk.map[(size_t)y * nx + col[c]] : DISK_FLUID;
+            if (g == DISK_FLUID) {
 #pragma unroll
-            for (int c = 0; c < CPL; ++c) v[i][f][c] = Storage<T>::load(row[(size_t)f * nx + col[c]]);
+                for (int f = 0; f < 3; ++f) v[i][f][c] = Storage<T>::load(row[(size_t)f * nx + col[c]]);
+            } else if (g == DISK_REST) {
+#pragma unroll
+                for (int f = 0; f < 3; ++f) v[i][f][c] = C(0);
+            } else {
+                const unsigned src = (unsigned)a.disk.src[g], sy = src / (unsigned)nx, sx = src - sy * (unsigned)nx;
+                const C wx = C(a.disk.w[3 * g]), wy = C(a.disk.w[3 * g + 1]), sj = C(a.disk.w[3 * g + 2]);
+                const C ux = C(1) - wx, uy = C(1) - wy;
+#pragma unroll
+                for (int f = 0; f < 3; ++f) {
+                    const T *q = a.in + fd_elem(sx, sy, f, nx);  // the cell's corners
+                    const C lower = ux * Storage<T>::load(q[0]) + wx * Storage<T>::load(q[1]);
+                    const C upper = ux * Storage<T>::load(q[3 * (size_t)nx]) + wx * Storage<T>::load(q[3 * (size_t)nx + 1]);
+                    const C m = uy * lower + wy * upper;
+                    v[i][f][c] = Storage<T>::load(Storage<T>::store(f == 0 ? m : sj * m));
+                }
+            }
+        }
     }
     // ghost row y beyond a wall, from the rows next to the wall
     auto ghost_row = [&](int y, C(&g)[3][CPL]) __attribute__((always_inline)) {
@@ -241,9 +265,12 @@ __global__ void __launch_bounds__(64 * TW) fd_tile_kernel(TileStepArgs<T> a)
                 fd_finish<C, FORCE>(fd_partial<C>(pc[i][c], pcx[i][c], pu[i][c], pux[i][c]), fd - ld[i][c], fdx - ldx[i][c],
                                     old[0][c], old[1][c], old[2][c], a.k.dfx, a.k.dfy, r, x, y);
                 // rounded for storage, as a step of its own would (FP16)
-                v[i][0][c] = Storage<T>::load(Storage<T>::store(r));
-                v[i][1][c] = Storage<T>::load(Storage<T>::store(x));
-                v[i][2][c] = Storage<T>::load(Storage<T>::store(y));
+                uint32_t rb[3] = {0u, 0u, 0u};
+                if constexpr (Storage<T>::STOCHASTIC)
+                    sr_draw(uint32_t(grid_row(y0 + i)) * uint32_t(nx) + uint32_t(col[c]), pcg_hash(a.step0 + uint32_t(step)), rb);
+                v[i][0][c] = Storage<T>::load(Storage<T>::store_r(r, rb[0]));
+                v[i][1][c] = Storage<T>::load(Storage<T>::store_r(x, rb[1]));
+                v[i][2][c] = Storage<T>::load(Storage<T>::store_r(y, rb[2]));
             }
         if constexpr (H == 0) __syncthreads();  // the sums are read before the next step's are written
     }
@@ -264,8 +291,8 @@ __global__ void __launch_bounds__(64 * TW) fd_tile_kernel(TileStepArgs<T> a)
     }
 }
 
-template <typename T, int CPL, int R, int ST, bool WALLS, bool FORCE>
-hipError_t run(const FdArgs &fa, int steps, const void *src, void *dst, hipStream_t s)
+template <typename T, int CPL, int R, int ST, bool WALLS, bool FORCE, bool DISK>
+hipError_t run(const FdArgs &fa, const TilePlan &p, const TileDisk &disk, const void *src, void *dst, hipStream_t s)
 {
     constexpr int H = Stencil<ST>::H;
     TileStepArgs<T> a;
@@ -273,63 +300,82 @@ hipError_t run(const FdArgs &fa, int steps, const void *src, void *dst, hipStrea
     a.out = static_cast<T *>(dst);
     a.nx = fa.nx;
     a.ny = fa.ny;
-    a.steps = steps;
-    a.halo = steps * (H + 1);
+    a.steps = p.steps;
+    a.halo = p.steps * (H + 1);
+    a.step0 = fa.step;
+    a.disk = disk;
     const int cols = 64 * CPL - 2 * a.halo, rows = TW * R - 2 * a.halo;
-    if (cols < 1 || rows < 1) return hipErrorInvalidValue;
+    if (cols < 1 || rows < 1 || (DISK && p.steps != 1)) return hipErrorInvalidValue;
     a.tiles_x = (fa.nx + cols - 1) / cols;
     a.k = sweep::make_coef<typename Storage<T>::C>(ST, fa.s_xx, fa.s_e, fa.fx, fa.fy);
     a.gr = ghost_rules<typename Storage<T>::C>(fa.xi);
     const int tiles = a.tiles_x * ((fa.ny + rows - 1) / rows);
-    hipLaunchKernelGGL((fd_tile_kernel<T, CPL, R, ST, WALLS, FORCE>), tiles, 64 * TW, 0, s, a);
+    hipLaunchKernelGGL((fd_tile_kernel<T, CPL, R, ST, WALLS, FORCE, DISK>), tiles, 64 * TW, 0, s, a);
     return hipGetLastError();
 }
 
-template <typename T, int CPL, int R> hipError_t dispatch(const FdArgs &a, int steps, const void *src, void *dst, hipStream_t s)
+template <typename T, int CPL, int R, int ST, bool WALLS, bool DISK>
+hipError_t force(const FdArgs &a, const TilePlan &p, const TileDisk &disk, const void *src, void *dst, hipStream_t s)
 {
-    const bool force = a.fx != 0.0 || a.fy != 0.0;
-    if (a.stencil == 1) return run<T, CPL, R, 1, false, false>(a, steps, src, dst, s);
-    if (a.stencil == 5)
-        return force ? run<T, CPL, R, 5, false, true>(a, steps, src, dst, s)
-                     : run<T, CPL, R, 5, false, false>(a, steps, src, dst, s);
-    if (a.walls)
-        return force ? run<T, CPL, R, 3, true, true>(a, steps, src, dst, s)
-                     : run<T, CPL, R, 3, true, false>(a, steps, src, dst, s);
-    return force ? run<T, CPL, R, 3, false, true>(a, steps, src, dst, s)
-                 : run<T, CPL, R, 3, false, false>(a, steps, src, dst, s);
+    if constexpr (ST != 1)
+        if (a.fx != 0.0 || a.fy != 0.0) return run<T, CPL, R, ST, WALLS, true, DISK>(a, p, disk, src, dst, s);
+    return run<T, CPL, R, ST, WALLS, false, DISK>(a, p, disk, src, dst, s);
 }
 
-template <typename T> hipError_t shapes(const FdArgs &a, const TilePlan &p, const void *src, void *dst, hipStream_t s)
+template <typename T, int CPL, int R>
+hipError_t dispatch(const FdArgs &a, const TilePlan &p, const TileDisk &disk, const void *src, void *dst, hipStream_t s)
 {
-    if (p.cols == 1 && p.rows == 1) return dispatch<T, 1, 1>(a, p.steps, src, dst, s);
-    if (p.cols == 1 && p.rows == 2) return dispatch<T, 1, 2>(a, p.steps, src, dst, s);
-    if (p.cols == 1 && p.rows == 4) return dispatch<T, 1, 4>(a, p.steps, src, dst, s);
+    if constexpr (CPL == 1)
+        if (disk.map) {
+            if (a.stencil == 1) return force<T, CPL, R, 1, false, true>(a, p, disk, src, dst, s);
+            if (a.stencil == 5) return force<T, CPL, R, 5, false, true>(a, p, disk, src, dst, s);
+            return force<T, CPL, R, 3, false, true>(a, p, disk, src, dst, s);
+        }
+    if (disk.map) return hipErrorInvalidValue;
+    if (a.stencil == 1) return force<T, CPL, R, 1, false, false>(a, p, disk, src, dst, s);
+    if (a.stencil == 5) return force<T, CPL, R, 5, false, false>(a, p, disk, src, dst, s);
+    if (a.walls) return force<T, CPL, R, 3, true, false>(a, p, disk, src, dst, s);
+    return force<T, CPL, R, 3, false, false>(a, p, disk, src, dst, s);
+}
+
+template <typename T>
+hipError_t shapes(const FdArgs &a, const TilePlan &p, const TileDisk &disk, const void *src, void *dst, hipStream_t s)
+{
+    if (p.cols == 1 && p.rows == 1) return dispatch<T, 1, 1>(a, p, disk, src, dst, s);
+    if (p.cols == 1 && p.rows == 2) return dispatch<T, 1, 2>(a, p, disk, src, dst, s);
+    if (p.cols == 1 && p.rows == 4) return dispatch<T, 1, 4>(a, p, disk, src, dst, s);
     if constexpr (sizeof(T) < 8)
-        if (p.cols == 2 && p.rows == 4) return dispatch<T, 2, 4>(a, p.steps, src, dst, s);
+        if (p.cols == 2 && p.rows == 4) return dispatch<T, 2, 4>(a, p, disk, src, dst, s);
     return hipErrorInvalidValue;
 }
 
 }  // namespace
 
-TilePlan fd_tile_plan(const FdArgs &a)
+// In the disk the wall acts between the steps: one step per launch, which spares the launch of the
+// fill (72^2 FP64: 7.0 + 2.8 us).
+TilePlan fd_tile_plan(const FdArgs &a, bool disk)
 {
-    // stochastic rounding keeps to single steps; ghost rows come from the two rows next to a wall
-    if (a.dtype == FDLBM_F16DEV_SR || (a.walls && (a.xi < 0.5 || a.stencil != 3))) return TilePlan();
+    // ghost rows come from the two rows next to a wall
+    if (a.walls && (a.xi < 0.5 || a.stencil != 3)) return TilePlan();
     const TileShape shapes[] = {{1, 1}, {1, 2}, {1, 4}, {2, 4}};
     const bool f64 = a.dtype == FDLBM_F64, force = a.fx != 0.0 || a.fy != 0.0;
-    const double row_us = a.stencil == 1 ? (f64 ? 0.55 : 0.45)
+    double row_us = a.stencil == 1 ? (f64 ? 0.55 : 0.45)
                                          : (a.stencil == 3 ? (f64 ? 0.9 : 0.65) : (f64 ? 1.3 : 0.85)) + (force ? 0.08 : 0.0);
+    if (a.dtype == FDLBM_F16DEV_SR) row_us += 0.12;  // two hashes per node
+    // the disk: the sweep in single steps, and the fill's launch less what the gathers take
+    const double sweep_us = disk ? fd_single_us(a) + 2.0 : fd_fused_us(a);
     return plan_tiles(a.nx, a.ny, a.stencil == 1 ? 1 : a.stencil == 3 ? 2 : 3, int(compute_bytes(a.dtype)), row_us, shapes,
-                      f64 ? 3 : 4, fd_fused_us(a));
+                      f64 || disk ? 3 : 4, disk ? 1 : 25, sweep_us);
 }
 
-hipError_t launch_fd_tile(const FdArgs &a, const TilePlan &p, const void *src, void *dst, hipStream_t s)
+hipError_t launch_fd_tile(const FdArgs &a, const TilePlan &p, const TileDisk &disk, const void *src, void *dst,
+                          hipStream_t s)
 {
     switch (a.dtype) {
-    case FDLBM_F64: return shapes<double>(a, p, src, dst, s);
-    case FDLBM_F32: return shapes<float>(a, p, src, dst, s);
-    case FDLBM_F16DEV: return shapes<__half>(a, p, src, dst, s);
-    default: return hipErrorInvalidValue;
+    case FDLBM_F64: return shapes<double>(a, p, disk, src, dst, s);
+    case FDLBM_F32: return shapes<float>(a, p, disk, src, dst, s);
+    case FDLBM_F16DEV_SR: return shapes<HalfSR>(a, p, disk, src, dst, s);
+    default: return shapes<__half>(a, p, disk, src, dst, s);
     }
 }
 

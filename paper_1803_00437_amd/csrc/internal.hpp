@@ -28,6 +28,7 @@ struct FdArgs {
     double s_xx, s_e, fx, fy;
     double xi;  // walls: their distance beyond the first and last rows (0 < xi <= 1)
     uint32_t seed = 0;  // FDLBM_F16DEV_SR: pcg_hash of the step count (random bits of the rounding)
+    uint32_t step = 0;  // the step count
 };
 
 struct MrtArgs {
@@ -67,12 +68,12 @@ struct TileShape {
 // each side.  Measured against the estimate (us per step): 64^2 FP64 2.3 (2.4), 256^2 FP32 2.3
 // (2.4), 1024^2 6.7 (7.4), 1001 x 777 5-point 9.0 (9.0), where the sweep takes 4.5, 6.1, 10.2 and 12.
 inline TilePlan plan_tiles(int nx, int ny, int reach, int elem_bytes, double row_us, const TileShape *shapes, int count,
-                           double sweep_us)
+                           int most, double sweep_us)
 {
     TilePlan best;
     double best_us = 0.95 * sweep_us;
     for (int i = 0; i < count; ++i)
-        for (int steps = 1; steps <= 25; steps += 2) {
+        for (int steps = 1; steps <= most; steps += 2) {
             const int cols = 64 * shapes[i].cols - 2 * reach * steps, rows = 16 * shapes[i].rows - 2 * reach * steps;
             if (cols < 1 || rows < 1) break;
             const int64_t blocks = (int64_t)((nx + cols - 1) / cols) * ((ny + rows - 1) / rows);
@@ -90,9 +91,18 @@ inline TilePlan plan_tiles(int nx, int ny, int reach, int elem_bytes, double row
     return best;
 }
 // FD-LBM and LW-ACM: the plan (steps = 0 where the tiles do not apply) and a launch of p.steps steps.
-TilePlan fd_tile_plan(const FdArgs &a);
+// In the disk, map gives per node DISK_FLUID, DISK_REST or the index of its ghost in src and w (the
+// table of DiskFill); null elsewhere.
+constexpr int DISK_FLUID = -1, DISK_REST = -2;
+struct TileDisk {
+    const int32_t *map = nullptr, *src = nullptr;
+    const double *w = nullptr;
+};
+TilePlan fd_tile_plan(const FdArgs &a, bool disk);
 double fd_fused_us(const FdArgs &a);
-hipError_t launch_fd_tile(const FdArgs &a, const TilePlan &p, const void *src, void *dst, hipStream_t s);
+double fd_single_us(const FdArgs &a);
+hipError_t launch_fd_tile(const FdArgs &a, const TilePlan &p, const TileDisk &disk, const void *src, void *dst,
+                          hipStream_t s);
 
 // Batch of independent periodic FD-LBM grids (3-point differences) -------------------
 // Nodes per block of the A(t) reduction (more for an instance that would make over 4096 blocks):

@@ -838,7 +838,7 @@ TilePlan mrt_tile_plan(const MrtArgs &a)
     if (a.kernel != FDLBM_KERNEL_AUTO || (a.walls && a.xi != 0.5)) return TilePlan();
     const TileShape shapes[] = {{1, 1}, {1, 2}, {1, 4}};
     const bool f64 = a.dtype == FDLBM_F64;
-    return plan_tiles(a.nx, a.ny, 1, f64 ? 8 : 4, f64 ? 0.9 : 0.7, shapes, f64 ? 2 : 3, mrt_fused_us(a));
+    return plan_tiles(a.nx, a.ny, 1, f64 ? 8 : 4, f64 ? 0.9 : 0.7, shapes, f64 ? 2 : 3, 25, mrt_fused_us(a));
 }
 
 hipError_t launch_mrt_tile(const MrtArgs &a, const TilePlan &p, const void *src, void *dst, hipStream_t s)

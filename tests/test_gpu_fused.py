@@ -79,7 +79,7 @@ FD_KINDS = [("fd", 3, "periodic", 0.5), ("fd", 3, "walls", 0.5), ("fd", 3, "wall
 
 
 @pytest.mark.parametrize("kernel", ["auto", "sweep"])
-@pytest.mark.parametrize("dtype", ["f32", "f64", "f16"])
+@pytest.mark.parametrize("dtype", ["f32", "f64", "f16", "f16sr"])
 @pytest.mark.parametrize("scheme,stencil,bc,xi", FD_KINDS)
 @pytest.mark.parametrize("forced", [False, True])
 @pytest.mark.parametrize("nx,ny", FD_SHAPES)
@@ -101,6 +101,31 @@ def test_fd_steps_in_one_launch_equal_reference(F, nx, ny, scheme, stencil, bc, 
         name = "state_b" if got.steps % 2 else "state_a"
         assert got.steps == ref.steps
         assert bool((getattr(got.buffers, name) == getattr(ref.buffers, name)).all())
+    got.close()
+    ref.close()
+
+
+DISKS = [(72, 72, (35.5, 35.5, 29.9)), (50, 41, (24.3, 19.8, 11.7)), (300, 200, (149.5, 99.5, 80.0))]
+
+
+@pytest.mark.parametrize("dtype", ["f32", "f64", "f16", "f16sr"])
+@pytest.mark.parametrize("scheme,stencil,force", [("fd", 3, 0.0), ("fd", 5, 0.0), ("fd", 3, 2e-5), ("lwacm", 3, 0.0)])
+@pytest.mark.parametrize("nx,ny,disk", DISKS)
+def test_disk_fill_and_step_in_one_launch_equal_reference(F, nx, ny, disk, scheme, stencil, force, dtype):
+    init = W.random_state(nx, ny, seed=nx, amp=2e-3)
+    kw = dict(scheme=scheme, dtype=dtype, bc="disk", disk=disk, s_xx=1.3, s_e=1.1)
+    if scheme == "fd":
+        kw.update(stencil=stencil, force=(force, -force))
+    ref = F.FdLbm(nx, ny, kernel="reference", **kw)
+    got = F.FdLbm(nx, ny, **kw)
+    for start in (0, 7):  # a state set again finds the rest nodes of the last run
+        ref.set_state(*init)
+        got.set_state(*init)
+        for n in (1, 2, 5):
+            print(f"  disk {scheme}{stencil} {nx}x{ny} {dtype} from {start} +{n}", flush=True)
+            ref.step(n)
+            got.step(n)
+            assert all(np.array_equal(a, b) for a, b in zip(got.get_state(), ref.get_state()))
     got.close()
     ref.close()
 
