@@ -6,6 +6,7 @@
 #include <vector>
 #include <cstdio>
 #include <cstring>
+#include <mutex>
 #include <new>
 
 #include "fdlbm_device.hpp"
@@ -189,6 +190,42 @@ Layout layout(const fdlbm_params &p)
     return L;
 }
 
+// Pinned host memory that the diagnostics of a context are written to: slots of one page, which is
+// allocated with the first context, shared by the next ones (an allocation takes about 100 us) and
+// freed with the last.  Contexts beyond its slots, or all if it cannot be had, get null.
+constexpr int HOST_SLOTS = 64;
+std::mutex host_mu;
+double *host_page = nullptr;
+uint64_t host_used = 0;  // one bit per slot
+
+double *host_slot_take()
+{
+    std::lock_guard<std::mutex> lock(host_mu);
+    if (host_used == ~uint64_t(0)) return nullptr;
+    if (!host_page) {
+        void *p = nullptr;
+        if (hipHostMalloc(&p, HOST_SLOTS * DIAG_SLOTS * sizeof(double), hipHostMallocPortable) != hipSuccess) {
+            (void)hipGetLastError();
+            return nullptr;
+        }
+        host_page = static_cast<double *>(p);
+    }
+    const int i = __builtin_ctzll(~host_used);
+    host_used |= uint64_t(1) << i;
+    return host_page + (size_t)i * DIAG_SLOTS;
+}
+
+void host_slot_give(double *slot)
+{
+    if (!slot) return;
+    std::lock_guard<std::mutex> lock(host_mu);
+    host_used &= ~(uint64_t(1) << ((slot - host_page) / DIAG_SLOTS));
+    if (host_used == 0) {
+        (void)hipHostFree(host_page);
+        host_page = nullptr;
+    }
+}
+
 // Runs an entry point's body so that no C++ exception crosses the C ABI: host allocation
 // failure (std::bad_alloc from the tables) becomes FDLBM_ENOMEM, anything else FDLBM_EINVAL.
 template <typename Body> int guarded(Body &&body)
@@ -218,6 +255,7 @@ struct fdlbm_ctx {
     DiskFill disk;   // FDLBM_BC_DISK: the ghost-node table in the scratch buffer
     MrtDisk mdisk;   // FDLBM_BC_DISK, MRT: the boundary-link table in the scratch buffer
     bool disk_full;  // the next fill sets every rest node to rest (the state was just set)
+    double *host = nullptr;  // pinned: DIAG_SLOTS values of the diagnostics (null: copied instead)
     int most;        // steps that one launch may take
     TilePlan tile;   // tile.steps > 0: launches of tiles, up to so many steps each
     TileDisk tdisk;  // FDLBM_BC_DISK: the tiles' view of the ghost-node table
@@ -343,12 +381,17 @@ int fdlbm_create(const fdlbm_params *p, void *state_a, void *state_b, void *scra
             delete c;
             return device_error(e, "fdlbm_create");
         }
+        c->host = host_slot_take();
         *out = c;
         return FDLBM_OK;
     });
 }
 
-void fdlbm_destroy(fdlbm_ctx *c) { delete c; }
+void fdlbm_destroy(fdlbm_ctx *c)
+{
+    if (c) host_slot_give(c->host);
+    delete c;
+}
 
 int64_t fdlbm_step_count(const fdlbm_ctx *c) { return c ? c->steps : -1; }
 
@@ -426,12 +469,17 @@ static int run_diag(fdlbm_ctx *c, double out[DIAG_SLOTS])
     HIPCHK(hipSetDevice(c->device), "hipSetDevice");
     const size_t n = c->n();
     const double *m = c->mode_set ? c->sd(c->L.mode) : nullptr;
+    // the last kernel writes its few numbers to pinned host memory: a copy would be one more
+    // operation on the stream, staged through a buffer of the runtime
+    double *to = c->host ? c->host : c->sd(c->L.out);
     HIPCHK(launch_diag(c->p.scheme, c->p.dtype, c->buf[c->cur], c->p.nx, c->p.ny, m, m ? m + n : nullptr,
-                       c->sd(c->L.partials), c->sd(c->L.out), c->stream),
+                       c->sd(c->L.partials), to, c->stream),
            "diagnostics");
-    HIPCHK(hipMemcpyAsync(out, c->sd(c->L.out), DIAG_SLOTS * sizeof(double), hipMemcpyDeviceToHost, c->stream),
-           "diagnostics download");
+    if (!c->host)
+        HIPCHK(hipMemcpyAsync(out, to, DIAG_SLOTS * sizeof(double), hipMemcpyDeviceToHost, c->stream),
+               "diagnostics download");
     HIPCHK(hipStreamSynchronize(c->stream), "diagnostics");
+    if (c->host) std::memcpy(out, c->host, DIAG_SLOTS * sizeof(double));
     return FDLBM_OK;
 }
 

@@ -1,8 +1,7 @@
 // FP64 diagnostics of a state and the conversions between host-staged FP64 planes and the
 // device storage dtype.
 //
-// The reduction is deterministic: a fixed grid of DIAG_BLOCKS blocks walks the nodes with
-// a grid-stride loop, each block reduces its threads in a fixed tree (wavefront shuffles,
+// The reduction is deterministic: DIAG_BLOCKS blocks (one per row on a lower grid) walk the rows, each block reduces its threads in a fixed tree (wavefront shuffles,
 // then LDS) and writes one partial; a single block then reduces the partials in order.
 // Quantities (section 3-a uses the correlation A(t) = <J(t), J0>/<J0, J0>):
 //   [0] sum drho, [1] sum jx, [2] sum jy, [3] 1/2 sum |J|^2/rho, [4] max |J|,
@@ -150,13 +149,15 @@ hipError_t diag_run(bool mrt, const void *state, int nx, int ny, const double *j
                     double *partials, double *out, hipStream_t s)
 {
     const T *st = static_cast<const T *>(state);
+    // a block without a row would only add zeros
+    const int blocks = ny < DIAG_BLOCKS ? ny : DIAG_BLOCKS;
     if (mrt)
-        hipLaunchKernelGGL((diag_partials<T, true>), DIAG_BLOCKS, TPB, 0, s, st, nx, ny, j0x, j0y, partials);
+        hipLaunchKernelGGL((diag_partials<T, true>), blocks, TPB, 0, s, st, nx, ny, j0x, j0y, partials);
     else
-        hipLaunchKernelGGL((diag_partials<T, false>), DIAG_BLOCKS, TPB, 0, s, st, nx, ny, j0x, j0y, partials);
+        hipLaunchKernelGGL((diag_partials<T, false>), blocks, TPB, 0, s, st, nx, ny, j0x, j0y, partials);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(diag_final, 1, TPB, 0, s, partials, DIAG_BLOCKS, out);
+    hipLaunchKernelGGL(diag_final, 1, TPB, 0, s, partials, blocks, out);
     return hipGetLastError();
 }
 

@@ -172,3 +172,21 @@ def test_d3_planes_chosen_from_the_grid_equal_reference(F, nx, ny, nz, dtype):
     assert bool((got.buffers.state_b[:size] == ref.buffers.state_b[:size]).all())
     got.close()
     ref.close()
+
+
+def test_diagnostics_of_many_contexts(F):
+    """More contexts than there are pinned result slots: every one reads its own numbers."""
+    sims = []
+    for i in range(70):
+        sim = F.FdLbm(16, 8, dtype="f64", s_xx=1.2)
+        sim.set_state(np.full((8, 16), 1e-3 * i), np.zeros((8, 16)), np.zeros((8, 16)))
+        sims.append(sim)
+    for i, sim in enumerate(sims):
+        assert sim.diagnostics()["mass"] == pytest.approx(128 * 1e-3 * i, abs=1e-12)
+    for sim in sims[::2]:
+        sim.close()
+    again = F.FdLbm(16, 8, dtype="f64", s_xx=1.2)
+    again.set_state(np.full((8, 16), 0.5), np.zeros((8, 16)), np.zeros((8, 16)))
+    assert again.diagnostics()["mass"] == pytest.approx(64.0) and sims[1].diagnostics()["mass"] == pytest.approx(0.128)
+    for sim in sims[1::2] + [again]:
+        sim.close()
