@@ -43,7 +43,6 @@ double quartic(double s_xx) { return 1.0 / (0.5 + 1.0 / (6.0 * (1.0 / s_xx - 0.5
 struct Layout {
     size_t partials, out, mode, staging, fstar;
     size_t disk_dst, disk_src, disk_w, disk_span, disk_ring;  // ghost-node table (FDLBM_BC_DISK)
-    size_t disk_map;                                          // per node, where tiles take the steps
     size_t mdisk_node, mdisk_kb, mdisk_q, mdisk_ring, mdisk_fspan;  // MRT boundary links (FDLBM_BC_DISK)
     size_t total;
 };
@@ -174,8 +173,6 @@ Layout layout(const fdlbm_params &p)
     off += p.bc == FDLBM_BC_DISK && three_words(p.scheme) ? align256(sizeof(int32_t) * 2 * size_t(p.ny)) : 0;
     L.disk_ring = off;
     off += align256(sizeof(int32_t) * nr);
-    L.disk_map = off;
-    if (p.bc == FDLBM_BC_DISK && tile_plan(p, p.s_q).steps > 0) off += align256(sizeof(int32_t) * n);
     L.mdisk_node = off;
     off += align256(sizeof(int32_t) * nl);
     L.mdisk_kb = off;
@@ -264,6 +261,19 @@ struct fdlbm_ctx {
     double *sd(size_t off) const { return reinterpret_cast<double *>(scratch + off); }
 };
 
+namespace {
+// Between the calls that move a state through it, the staging area holds the small disk's map of
+// nodes: such a call forms the map again when it ends, however it ends.
+struct StagingUse {
+    fdlbm_ctx *c;
+    explicit StagingUse(fdlbm_ctx *ctx) : c(ctx) {}
+    ~StagingUse()
+    {
+        if (c->tdisk.map) (void)launch_disk_map(c->disk, c->tdisk.map, c->stream);
+    }
+};
+}  // namespace
+
 extern "C" {
 
 int fdlbm_workspace_bytes(const fdlbm_params *p, size_t *state_bytes, size_t *scratch_bytes)
@@ -311,7 +321,6 @@ int fdlbm_create(const fdlbm_params *p, void *state_a, void *state_b, void *scra
         if (e == hipSuccess) e = hipMemsetAsync(state_a, 0, sb, c->stream);
         if (e == hipSuccess) e = hipMemsetAsync(state_b, 0, sb, c->stream);
         DiskTable t;  // outlives the uploads: the stream is synchronised below
-        std::vector<int32_t> map;
         if (e == hipSuccess && p->bc == FDLBM_BC_DISK && !three_words(p->scheme)) {
             if (!disk_table(*p, &t)) {
                 delete c;
@@ -353,16 +362,9 @@ int fdlbm_create(const fdlbm_params *p, void *state_a, void *state_b, void *scra
             c->disk.ring = reinterpret_cast<const int32_t *>(sc + L.disk_ring);
             const size_t ng = t.dst.size(), nr = t.ring.size();
             if (c->tile.steps > 0) {
-                map.assign(c->n(), DISK_REST);
-                for (int j = 0; j < p->ny; ++j)
-                    for (int i = t.span[2 * size_t(j)]; i <= t.span[2 * size_t(j) + 1]; ++i)
-                        map[size_t(j) * p->nx + i] = DISK_FLUID;
-                for (size_t g = 0; g < ng; ++g) map[size_t(t.dst[g])] = int32_t(g);
-                c->tdisk.map = reinterpret_cast<const int32_t *>(sc + L.disk_map);
+                c->tdisk.map = reinterpret_cast<int32_t *>(sc + L.staging);
                 c->tdisk.src = c->disk.src;
                 c->tdisk.w = c->disk.w;
-                e = hipMemcpyAsync(sc + L.disk_map, map.data(), map.size() * sizeof(int32_t), hipMemcpyHostToDevice,
-                                   c->stream);
             }
             if (e == hipSuccess && ng) e = hipMemcpyAsync(sc + L.disk_dst, t.dst.data(), ng * sizeof(int32_t), hipMemcpyHostToDevice, c->stream);
             if (e == hipSuccess && ng)
@@ -375,6 +377,7 @@ int fdlbm_create(const fdlbm_params *p, void *state_a, void *state_b, void *scra
             if (e == hipSuccess && nr)
                 e = hipMemcpyAsync(sc + L.disk_ring, t.ring.data(), nr * sizeof(int32_t), hipMemcpyHostToDevice,
                                    c->stream);
+            if (e == hipSuccess && c->tdisk.map) e = launch_disk_map(c->disk, c->tdisk.map, c->stream);
         }
         if (e == hipSuccess) e = hipStreamSynchronize(c->stream);
         if (e != hipSuccess) {
@@ -407,6 +410,7 @@ int fdlbm_set_state(fdlbm_ctx *c, const double *drho, const double *jx, const do
     if (!c || !drho || !jx || !jy) return FDLBM_EINVAL;
     HIPCHK(hipSetDevice(c->device), "hipSetDevice");
     const size_t n = c->n(), nb = n * sizeof(double);
+    const StagingUse staging(c);
     double *st = c->sd(c->L.staging);
     HIPCHK(hipMemcpyAsync(st, drho, nb, hipMemcpyHostToDevice, c->stream), "set_state upload");
     HIPCHK(hipMemcpyAsync(st + n, jx, nb, hipMemcpyHostToDevice, c->stream), "set_state upload");
@@ -426,6 +430,7 @@ int fdlbm_get_state(fdlbm_ctx *c, double *drho, double *jx, double *jy)
     if (!c || !drho || !jx || !jy) return FDLBM_EINVAL;
     HIPCHK(hipSetDevice(c->device), "hipSetDevice");
     const size_t n = c->n(), nb = n * sizeof(double);
+    const StagingUse staging(c);
     double *st = c->sd(c->L.staging);
     if (three_words(c->p.scheme))
         HIPCHK(launch_unpack_rows(c->p.dtype, 3, c->buf[c->cur], st, c->p.nx, c->p.ny, c->stream), "unpack");
@@ -443,6 +448,7 @@ int fdlbm_set_populations(fdlbm_ctx *c, const double *df)
     if (!c || !df || c->p.scheme != FDLBM_SCHEME_MRT) return FDLBM_EINVAL;
     HIPCHK(hipSetDevice(c->device), "hipSetDevice");
     const size_t n = c->n();
+    const StagingUse staging(c);
     double *st = c->sd(c->L.staging);
     HIPCHK(hipMemcpyAsync(st, df, 9 * n * sizeof(double), hipMemcpyHostToDevice, c->stream), "set_populations");
     HIPCHK(launch_pack_rows(c->p.dtype, 9, st, c->buf[c->cur], c->p.nx, c->p.ny, c->stream), "pack");
@@ -457,6 +463,7 @@ int fdlbm_get_populations(fdlbm_ctx *c, double *df)
     if (!c || !df || c->p.scheme != FDLBM_SCHEME_MRT) return FDLBM_EINVAL;
     HIPCHK(hipSetDevice(c->device), "hipSetDevice");
     const size_t n = c->n();
+    const StagingUse staging(c);
     double *st = c->sd(c->L.staging);
     HIPCHK(launch_unpack_rows(c->p.dtype, 9, c->buf[c->cur], st, c->p.nx, c->p.ny, c->stream), "unpack");
     HIPCHK(hipMemcpyAsync(df, st, 9 * n * sizeof(double), hipMemcpyDeviceToHost, c->stream), "get_populations");

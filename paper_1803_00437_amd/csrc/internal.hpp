@@ -64,8 +64,8 @@ struct TileShape {
 // The fastest shape and number of steps for a grid, or the sweep if its estimate `sweep_us` (per
 // step) is less.  A block's launch, loads and stores take 2.5 us and 0.85 us (FP64 1.2) per row and
 // column of a lane; a step takes 0.3 us and row_us per row and column of a lane.  A compute unit gets
-// one block of 256 after the other, two at once where the shape's registers allow.  reach: rows and columns a step loses on
-// each side.  Measured against the estimate (us per step): 64^2 FP64 2.3 (2.4), 256^2 FP32 2.3
+// one block of 256 after the other, two at once where the shape's registers allow.  reach: rows and
+// columns a step loses on each side.  Measured against the estimate (us per step): 64^2 FP64 2.3 (2.4), 256^2 FP32 2.3
 // (2.4), 1024^2 6.7 (7.4), 1001 x 777 5-point 9.0 (9.0), where the sweep takes 4.5, 6.1, 10.2 and 12.
 inline TilePlan plan_tiles(int nx, int ny, int reach, int elem_bytes, double row_us, const TileShape *shapes, int count,
                            int most, double sweep_us)
@@ -95,7 +95,8 @@ inline TilePlan plan_tiles(int nx, int ny, int reach, int elem_bytes, double row
 // table of DiskFill); null elsewhere.
 constexpr int DISK_FLUID = -1, DISK_REST = -2;
 struct TileDisk {
-    const int32_t *map = nullptr, *src = nullptr;
+    int32_t *map = nullptr;
+    const int32_t *src = nullptr;
     const double *w = nullptr;
 };
 TilePlan fd_tile_plan(const FdArgs &a, bool disk);
@@ -194,6 +195,8 @@ struct DiskFill {
 // full: set every rest node to rest (first step after the state was set, or a body force
 // acts); otherwise the ring only
 hipError_t launch_disk_fill(const DiskFill &f, int dtype, void *state, bool full, hipStream_t s);
+// The map of TileDisk, nx * ny values.  Two launches.
+hipError_t launch_disk_map(const DiskFill &f, int32_t *map, hipStream_t s);
 // MRT in the disk: after the periodic step of the whole grid (populations `pop`, in place),
 // the interpolated bounce-back of every boundary link, then the solid nodes set to rest
 // (full: every non-fluid node; otherwise the solid ring the links reach).  Two launches.
