@@ -22,8 +22,8 @@
  *     (-1,0), (0,-1), e_5..e_8 = (1,1), (-1,1), (-1,-1), (1,-1).
  *   - Device buffers are owned by the caller (allocated e.g. by PyTorch) and must stay
  *     valid until fdlbm_destroy.  The library never allocates or frees device memory (it holds
- *     one page of pinned host memory while contexts exist).
- *   - A step call of several steps may take three or five of them in one launch; the state
+ *     one page of pinned host memory while contexts that read their diagnostics often exist).
+ *   - A step call of several steps may take some of them together in one launch; the state
  *     after it, its buffer and its bits are those of as many single steps.
  *   - All work is issued on the HIP stream given at creation (NULL = the default stream).
  *     Steps return without synchronising; fdlbm_get_state, fdlbm_get_populations,
@@ -228,7 +228,8 @@ int fdlbm_set_step_count(fdlbm_ctx *c, int64_t steps);
 
 /* Tile-shape tuning (not part of the method; the results do not depend on the shape, only
  * the speed does).  Times `reps` launches (1..10000) of this context's step kernel for
- * each candidate shape on its own grid and keeps the fastest in the context: FD-LBM sweep
+ * each candidate shape on its own grid, one step per launch, and keeps the fastest in the
+ * context (launches of several steps choose their own shape): FD-LBM sweep
  * kernel: grid columns per lane (1, 2, 4 where supported) x rows per wavefront (4, 6, 8,
  * 12, 16, 24); MRT sweep kernel: rows per tile (1, 2, 4, 8, 16).  The reference kernels have
  * no shape and are only timed.  The state does not advance: each timed launch reads the
@@ -282,7 +283,7 @@ int fdlbm_batch_create(const fdlbm_instance *instances, int32_t count, int32_t d
 int fdlbm_batch_set_state(fdlbm_batch *b, int32_t i, const double *drho, const double *jx, const double *jy);
 int fdlbm_batch_get_state(fdlbm_batch *b, int32_t i, double *drho, double *jx, double *jy);
 
-/* Advance every instance by nsteps (one launch per step for all instances).  With
+/* Advance every instance by nsteps (launches of two or three steps for all instances).  With
  * sample_every > 0 (nsteps must be a multiple), A(t) of every instance is recorded after
  * each sample_every steps; with use_graph != 0 each chunk of sample_every steps plus its
  * sample is captured once in a HIP graph and replayed.  Asynchronous. */
@@ -291,8 +292,8 @@ int fdlbm_batch_step(fdlbm_batch *b, int64_t nsteps, int32_t sample_every, int32
 /* The same steps with one launch per instance per step (the comparison path). */
 int fdlbm_batch_step_per_instance(fdlbm_batch *b, int64_t nsteps);
 
-/* Tile-height tuning of the batched launch: times `reps` (1..10000) one-launch steps of
- * all instances for 4, 6, 8, 12 and 16 rows per wavefront, keeps the fastest (it is 8
+/* Tile-height tuning of the launches of one step (those left over by launches of two or
+ * three): times `reps` (1..10000) steps of all instances for 4, 6, 8, 12 and 16 rows per wavefront, keeps the fastest (it is 8
  * until tuned) and drops the cached graph replays, which are captured again on the next
  * fdlbm_batch_step.  No step is taken (timed launches write the spare buffer).
  * Synchronises the stream.  *out_rows, *out_ms (may be NULL): the choice and its time

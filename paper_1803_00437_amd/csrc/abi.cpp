@@ -188,12 +188,22 @@ Layout layout(const fdlbm_params &p)
 }
 
 // Pinned host memory that the diagnostics of a context are written to: slots of one page, which is
-// allocated with the first context, shared by the next ones (an allocation takes about 100 us) and
-// freed with the last.  Contexts beyond its slots, or all if it cannot be had, get null.
+// allocated for the first context that wants one, shared by the next ones and freed with the last.
+// Contexts beyond its slots, or all if it cannot be had, get null.  A slot saves 13 us a read and the
+// page takes 100 .. 250 us, so a context asks for one with its HOST_READS-th read: programs that
+// look at their state a few times do without.
+constexpr int HOST_READS = 4;
 constexpr int HOST_SLOTS = 64;
 std::mutex host_mu;
 double *host_page = nullptr;
 uint64_t host_used = 0;  // one bit per slot
+
+// Another thread may be recording a stream: allocating and freeing here are no part of its graph.
+struct RelaxedCapture {
+    hipStreamCaptureMode mode = hipStreamCaptureModeRelaxed;
+    RelaxedCapture() { (void)hipThreadExchangeStreamCaptureMode(&mode); }
+    ~RelaxedCapture() { (void)hipThreadExchangeStreamCaptureMode(&mode); }
+};
 
 double *host_slot_take()
 {
@@ -201,6 +211,7 @@ double *host_slot_take()
     if (host_used == ~uint64_t(0)) return nullptr;
     if (!host_page) {
         void *p = nullptr;
+        RelaxedCapture relaxed;
         if (hipHostMalloc(&p, HOST_SLOTS * DIAG_SLOTS * sizeof(double), hipHostMallocPortable) != hipSuccess) {
             (void)hipGetLastError();
             return nullptr;
@@ -218,6 +229,7 @@ void host_slot_give(double *slot)
     std::lock_guard<std::mutex> lock(host_mu);
     host_used &= ~(uint64_t(1) << ((slot - host_page) / DIAG_SLOTS));
     if (host_used == 0) {
+        RelaxedCapture relaxed;
         (void)hipHostFree(host_page);
         host_page = nullptr;
     }
@@ -253,6 +265,7 @@ struct fdlbm_ctx {
     MrtDisk mdisk;   // FDLBM_BC_DISK, MRT: the boundary-link table in the scratch buffer
     bool disk_full;  // the next fill sets every rest node to rest (the state was just set)
     double *host = nullptr;  // pinned: DIAG_SLOTS values of the diagnostics (null: copied instead)
+    int reads = 0;           // of the diagnostics, up to HOST_READS
     int most;        // steps that one launch may take
     TilePlan tile;   // tile.steps > 0: launches of tiles, up to so many steps each
     TileDisk tdisk;  // FDLBM_BC_DISK: the tiles' view of the ghost-node table
@@ -384,7 +397,6 @@ int fdlbm_create(const fdlbm_params *p, void *state_a, void *state_b, void *scra
             delete c;
             return device_error(e, "fdlbm_create");
         }
-        c->host = host_slot_take();
         *out = c;
         return FDLBM_OK;
     });
@@ -478,6 +490,7 @@ static int run_diag(fdlbm_ctx *c, double out[DIAG_SLOTS])
     const double *m = c->mode_set ? c->sd(c->L.mode) : nullptr;
     // the last kernel writes its few numbers to pinned host memory: a copy would be one more
     // operation on the stream, staged through a buffer of the runtime
+    if (c->reads < HOST_READS && ++c->reads == HOST_READS) c->host = host_slot_take();
     double *to = c->host ? c->host : c->sd(c->L.out);
     HIPCHK(launch_diag(c->p.scheme, c->p.dtype, c->buf[c->cur], c->p.nx, c->p.ny, m, m ? m + n : nullptr,
                        c->sd(c->L.partials), to, c->stream),
