@@ -1,15 +1,13 @@
 // Many independent FD-LBM grids (periodic, 3-point differences) of different sizes and
-// viscosities advanced together: one launch per lane class (at most three) per time step
-// covers every tile of every instance, and the FP64 correlation A(t) = <J(t), J0> / <J0, J0> of each instance with its
-// initial state (section 3-a) is sampled on the device.  A chunk of steps plus one sample
-// is captured once in a HIP graph and replayed.
+// viscosities advanced together: one launch takes all of them two or three steps further
+// (fd_batch_fused_kernel), and the FP64 correlation A(t) = <J(t), J0> / <J0, J0> of each
+// instance with its initial state (section 3-a) is sampled on the device.  A chunk of steps
+// plus one sample is captured once in a HIP graph and replayed.
 //
-// Each block looks up (instance, tile) in a table built on the host and runs the same
-// tile body as the single-grid kernel, so every instance evolves exactly as it would
-// alone.  Instances are grouped by lane class (vector or per-column accesses, see
-// BATCH_CLASSES); each class is one launch of the one-step kernel.
-//
-// Two or three steps together take one launch for every instance (fd_batch_fused_kernel).
+// Each wavefront looks up its instance and its part of it in a table built on the host and
+// runs the same body as the single-grid kernels, so every instance evolves exactly as it
+// would alone.  A step left over takes one launch per lane class (at most three: vector or
+// per-column accesses, see BATCH_CLASSES) of the one-step kernel, a block per tile.
 #include "fd_fused_body.hpp"
 #include "internal.hpp"
 

@@ -107,9 +107,6 @@ hipError_t dispatch(const FdArgs &a, const void *src, void *dst, hipStream_t s)
 
 }  // namespace
 
-#ifndef FENCE
-#define FENCE 1
-#endif
 // Two steps per launch with differences, three without (LW-ACM): more take two halo lanes a side
 // or registers that are not there (FP32 8192^2 188 us per step in threes against 190, but walls,
 // body forces and smaller grids lose).  Stochastic rounding is bound by its hashes: 127 us per step
