@@ -7,12 +7,12 @@ FP32 storage and arithmetic.  One step is one FD-LBM time step of the whole grid
 timed region also runs the FP64 diagnostics reduction every 100 steps.
 
 Prints ONE JSON line: value = FD-LBM FP32 MLUPS (million lattice-node updates per
-second), the HBM roofline of the step kernel (algorithmic bytes: 3 FP32 words read and 3
-written per node), the CPU oracle timed on a bounded band of the same workload, the
-relative L2 error of each GPU dtype against that oracle band, and the same measurements
-for the MRT step, the FP64 and FP16-storage FD-LBM steps and the 5-point stencil.  The
-FD-LBM step on the D3Q19 lattice is timed beside them on a 512^3 periodic decaying flow
-(object "d3q19").
+second), the roofline of the step kernel (instruction issue, with the HBM bytes beside it:
+a launch reads 3 FP32 words per node and writes 3, and takes two steps), the CPU oracle
+timed on a bounded band of the same workload, the relative L2 error of each GPU dtype
+against that oracle band, and the same measurements for the MRT step, the FP64 and
+FP16-storage FD-LBM steps and the 5-point stencil.  The FD-LBM step on the D3Q19 lattice is
+timed beside them on a 512^3 periodic decaying flow (object "d3q19").
 
     python bench.py [--steps K] [--warmup W] [--n 8192] [--no-compare] [--no-cpu]
 """
@@ -43,6 +43,15 @@ def kernel_source_sha():
 def bytes_per_node(scheme, dtype):
     words = 9 if scheme == "mrt" else 3
     return 2 * words * {"f64": 8, "f32": 4, "f16": 2, "f16sr": 2}[dtype]
+
+
+def steps_per_launch(scheme, dtype, stencil, nodes):
+    """Time steps that one launch takes of a grid of the sizes below (the periodic ones and those
+    between walls): its state crosses HBM once for all of them.  Smaller grids stay in registers
+    for several steps: 1 then, the bytes of one step."""
+    if nodes < 2048 * 2048 or dtype == "f16sr":
+        return 1
+    return {"mrt": 5, "lwacm": 3, "fd": 2}[scheme]
 
 
 def run_case(F, torch, init, scheme, dtype, stencil, steps, warmup, kernel, with_diag, tile_rows=0, lane_cols=0,
@@ -87,12 +96,14 @@ def run_case(F, torch, init, scheme, dtype, stencil, steps, warmup, kernel, with
     diag = sim.diagnostics()
     sim.close()
     nodes = nx * ny
+    per_launch = 1 if bc == "disk" or kernel == "reference" else steps_per_launch(scheme, dtype, stencil, nodes)
     return {
         "ms_per_step": wall_ms,
         "kernel_ms": kernel_ms,
         "mlups": nodes / (wall_ms * 1e3),
         "kernel_mlups": nodes / (kernel_ms * 1e3),
-        "alg_gbs": bytes_per_node(scheme, dtype) * nodes / (kernel_ms * 1e6),
+        "steps_per_launch": per_launch,
+        "alg_gbs": bytes_per_node(scheme, dtype) * nodes / (per_launch * kernel_ms * 1e6),
         "nonfinite": diag["nonfinite"],
         "tile": {"lane_cols": shape[0], "tile_rows": shape[1]} if shape else None,
     }
@@ -105,21 +116,25 @@ VALU_JSON = os.path.join(ROOT, "profiles", "valu_busy_8192.json")
 VALU_PEAK = 256 * 4 * 16 * 2.4e9
 
 
-def d3_alu_roofline(kernel_ms, nodes):
-    """The D3Q19 sweep is bound by instruction issue: VALU lane-instructions per second against
-    the chip's issue rate, with the instructions per node the rocprofv3 VALU pass measured on
-    the same kernel sources (None when the counters were taken on other sources)."""
+def alu_roofline(name, kernel_ms, nodes):
+    """The step kernels of several steps and the D3Q19 sweep are bound by instruction issue: VALU
+    lane-instructions per second against the chip's issue rate, with the instructions per node
+    and step that the rocprofv3 VALU pass `name` measured on the same kernel sources (None when
+    the counters were taken on other sources)."""
     if not os.path.exists(VALU_JSON):
         return None
     from paper_1803_00437_amd.profiling import VALU_SOURCES, sources_sha
 
     with open(VALU_JSON) as f:
-        v = json.load(f).get("d3_f32")
-    if not v or v.get("kernel_source_sha") != sources_sha(VALU_SOURCES["d3_f32"], ROOT):
+        v = json.load(f).get(name)
+    if not v or v.get("kernel_source_sha") != sources_sha(VALU_SOURCES[name], ROOT):
         return None
-    achieved = v["insts_per_node"] * nodes / (kernel_ms * 1e-3)
+    insts = v["insts_per_node_step"]
+    achieved = insts * nodes / (kernel_ms * 1e-3)
     return {"bound": "alu", "achieved": achieved, "peak": VALU_PEAK, "unit": "VALU lane-instructions/s",
-            "frac": achieved / VALU_PEAK, "insts_per_node": v["insts_per_node"], "valu_busy_counter": v["busy"]}
+            "frac": round(achieved / VALU_PEAK, 4), "insts_per_node": insts, "valu_busy_counter": v["busy"]}
+
+
 D3_WORKLOAD = ("{n}^3 periodic decaying flow, random Fourier modes 0<|k|<=8 per field, max|field|=0.02, seed 6; "
                "FD-LBM D3Q19 3-point finite differences, nu=0.02, s_e=1")
 
@@ -201,8 +216,8 @@ def measure_copy(F, torch, probe=False, nbytes=1 << 30, reps=10):
 
 def run_batch(F, torch, W, steps, per_instance_steps, every=10, autotune=True):
     """The 512-instance shear-wave sweep: N ~ U{32..1024}, nu ~ U[0.005, 0.1], m ~ U{1..4},
-    FP32, 3-point differences; one launch per step for all instances with A(t) sampled every
-    `every` steps (graph-replayed), against one launch per instance per step."""
+    FP32, 3-point differences; launches of two or three steps of all instances with A(t) sampled
+    every `every` steps (graph-replayed), against one launch per instance per step."""
     insts = W.batch_instances(512, seed=5)
     specs = [(d["n"], d["n"], F.fdlbm_rate_from_viscosity(d["nu"]), 1.0) for d in insts]
     b = F.FdLbmBatch(specs, dtype="f32", max_samples=(steps + 20) // every + 1)
@@ -440,7 +455,7 @@ def main():
         for dtype in ("f32", "f64"):
             d3[dtype] = run_d3(F, torch, init3, dtype, args.d3_steps, 5)
             print(f"# d3q19 {dtype}: {d3[dtype]}", file=sys.stderr, flush=True)
-        d3["roofline_f32"] = d3_alu_roofline(d3["f32"]["kernel_ms"], D3_N ** 3)
+        d3["roofline_f32"] = alu_roofline("d3_f32", d3["f32"]["kernel_ms"], D3_N ** 3)
         del init3
         if not args.no_cpu:
             from oracle import d3q19 as O3
@@ -485,6 +500,22 @@ def main():
     ms = main_case["ms_per_step"]
     kernel_ms = main_case["kernel_ms"]
     achieved = main_case["alg_gbs"]
+    per_launch = main_case["steps_per_launch"]
+    hbm = {
+        "bound": "hbm",
+        "achieved": round(achieved, 1),
+        "peak": HBM_PEAK_GBS,
+        "unit": "GB/s",
+        "frac": round(achieved / HBM_PEAK_GBS, 4),
+        "traffic": (round(counters["hbm_bytes_per_launch"] / (per_launch * kernel_ms * 1e6), 1) if counters else None),
+        "traffic_bytes_per_launch": (counters["hbm_bytes_per_launch"] if counters else None),
+        "kernel_ms": round(kernel_ms, 5),
+        "steps_per_launch": per_launch,
+        "alg_bytes_per_launch": bytes_per_node("fd", "f32") * n * n,
+        # the rate that one step per launch would need at this speed: above the copy's, so memory is no longer the bound
+        "one_step_equivalent_gbs": round(achieved * per_launch, 1),
+    }
+    alu = alu_roofline("fd3_f32", kernel_ms, n * n) if per_launch == 2 else None
     line = {
         "metric": METRIC,
         "value": round(main_case["mlups"], 1),
@@ -504,17 +535,8 @@ def main():
                         f"{DIAG_EVERY} steps",
             "nx": n, "ny": n, "stencil": 3, "kernel": args.kernel, "tile": main_case["tile"],
         },
-        "roofline": {
-            "bound": "hbm",
-            "achieved": round(achieved, 1),
-            "peak": HBM_PEAK_GBS,
-            "unit": "GB/s",
-            "frac": round(achieved / HBM_PEAK_GBS, 4),
-            "traffic": (round(counters["hbm_bytes_per_launch"] / (kernel_ms * 1e6), 1) if counters else None),
-            "traffic_bytes_per_launch": (counters["hbm_bytes_per_launch"] if counters else None),
-            "kernel_ms": round(kernel_ms, 5),
-            "alg_bytes_per_launch": bytes_per_node("fd", "f32") * n * n,
-        },
+        "roofline": alu or hbm,
+        "hbm": hbm,
         "hbm_copy": {"gbs": round(copy_gbs, 1), "frac_of_peak": round(copy_gbs / HBM_PEAK_GBS, 4),
                      "kernel_frac_of_copy": round(achieved / copy_gbs, 4),
                      "what": "fdlbm_device_copy of 1 GiB: read + write bytes / time"},

@@ -8,7 +8,7 @@ counter passes of their own) and write one summary per kernel:
 Summarise an existing set of rocprofv3 directories (``--output-format csv``) for one kernel:
 
     python -m paper_1803_00437_amd.profiling summarise --trace DIR [--fetch DIR --write DIR] \\
-        --kernel "fd_sweep_kernel<float, 4, 3, false, false, 0>" --launch-alg-bytes 1610612736 \\
+        --kernel "fd_fused_kernel<float, 4, 3, false, false, 0, 2, 1, 2>" --launch-alg-bytes 1610612736 \\
         --out profiles/NAME.md [--json profiles/NAME.json --sources a.hip b.hpp]
 
 The HBM counters are scaled by what they read for the library's streaming copy kernel
@@ -31,8 +31,11 @@ from collections import defaultdict
 
 ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 CSRC = "paper_1803_00437_amd/csrc"
-FD_SOURCES = [f"{CSRC}/fd_sweep.hip", f"{CSRC}/fd_sweep_body.hpp", f"{CSRC}/fdlbm_device.hpp"]
-MRT_SOURCES = [f"{CSRC}/mrt.hip", f"{CSRC}/fdlbm_device.hpp"]
+FD_SOURCES = [f"{CSRC}/fd_sweep.hip", f"{CSRC}/fd_fused.hip", f"{CSRC}/fd_fused_body.hpp", f"{CSRC}/fd_sweep_body.hpp",
+              f"{CSRC}/fdlbm_device.hpp"]
+MRT_SOURCES = [f"{CSRC}/mrt.hip", f"{CSRC}/fd_sweep_body.hpp", f"{CSRC}/fdlbm_device.hpp"]
+BATCH_SOURCES = [f"{CSRC}/fd_batch.hip", f"{CSRC}/fd_fused_body.hpp", f"{CSRC}/fd_sweep_body.hpp",
+                 f"{CSRC}/fdlbm_device.hpp"]
 D3_SOURCES = [f"{CSRC}/fd3d.hip", f"{CSRC}/fd3d_device.hpp", f"{CSRC}/fdlbm_device.hpp", f"{CSRC}/fd_sweep_body.hpp"]
 N3 = 512
 COPY_BYTES = 1 << 30
@@ -112,10 +115,11 @@ def sources_sha(paths, root=ROOT):
 
 def summarise(trace, kernel, alg, out_md, *, fetch=None, write=None, json_out=None, sources=(), command="",
               counter_command="", workload="", n=N, copy_kernel="copy_kernel", copy_bytes=COPY_BYTES, generator="",
-              group=False):
+              group=False, steps=1):
     """group=True: every kernel matching `kernel` is launched once per unit of work (the
-    batched step launches one kernel per lane-width class); their average durations add up
-    to the unit's time and `alg` is the bytes of the whole unit."""
+    batch: one launch of three steps and one of two); their average durations add up to the
+    unit's time and `alg` is the bytes of the whole unit.  `steps`: time steps per launch (or
+    unit)."""
     stats = kernel_stats(trace)
     names = {r["Name"]: r for r in stats}
     if group:
@@ -139,12 +143,13 @@ def summarise(trace, kernel, alg, out_md, *, fetch=None, write=None, json_out=No
     for r in sorted(stats, key=lambda r: -float(r["TotalDurationNs"]))[:14]:
         lines.append(f"| `{r['Name'][:110]}` | {r['Calls']} | {float(r['AverageNs']):.0f} | {r['MinNs']} | {r['MaxNs']} |")
     lines += ["", f"Summarised kernel: `{kname}`", f"- calls: {k['Calls']}",
-              f"- average duration: {avg_ns:.0f} ns" + (" (sum of the kernels' averages: one launch of each per step)"
+              f"- average duration: {avg_ns:.0f} ns" + (" (sum of the kernels' averages: one launch of each)"
                                                         if group else ""),
+              f"- time steps per launch: {steps} ({avg_ns / steps:.0f} ns per step)",
               f"- algorithmic bytes per launch: {alg} ({alg / avg_ns:.1f} GB/s at the average duration, "
               f"{alg / avg_ns / 8000:.3f} of 8 TB/s)"]
     out = {"kernel": kname, "avg_ns": avg_ns, "calls": int(k["Calls"]), "alg_bytes_per_launch": alg, "n": n,
-           "alg_gbs": alg / avg_ns}
+           "steps_per_launch": steps, "alg_gbs": alg / avg_ns}
     if group:
         g = launch_gaps(trace, kernel)
         if g:
@@ -202,50 +207,55 @@ D3_COUNTER_ARGS = ["--only", "d3_f32", "--d3-steps", "20", "--copy-probe"]
 # issuing them, per dispatch of the step kernel
 VALU_COUNTERS = ["SQ_INSTS_VALU", "SQ_ACTIVE_INST_VALU", "GRBM_GUI_ACTIVE", "SQ_WAVES"]
 VALU_SOURCES = {"fd3_f32": FD_SOURCES, "fd3_f16": FD_SOURCES, "mrt_f32": MRT_SOURCES,
-                "batch512": [f"{CSRC}/fd_batch.hip", f"{CSRC}/fd_sweep_body.hpp", f"{CSRC}/fdlbm_device.hpp"],
+                "batch512": BATCH_SOURCES,
                 "d3_f32": D3_SOURCES}
 VALU_PASSES = [
-    # name, bench arguments, kernel name pattern, nodes updated per dispatch (summed over the
-    # matching kernels of one step)
+    # name, bench arguments, kernel name pattern, nodes of the grid (of all instances of the batch)
     ("fd3_f32", ["--only", "fd3_f32", "--steps", "20", "--warmup", "2", "--no-autotune"],
-     "fd_sweep_kernel<float, 4, 3, false, false, 0>", N * N),
+     "fd_fused_kernel<float, 4, 3, false, false, 0, 2, 1, 2>", N * N),
     ("fd3_f16", ["--only", "fd3_f16", "--steps", "20", "--warmup", "2", "--no-autotune"],
-     "fd_sweep_kernel<__half, 4, 3, false, false, 0>", N * N),
+     "fd_fused_kernel<__half, 4, 3, false, false, 0, 2, 1, 2>", N * N),
     ("mrt_f32", ["--only", "mrt_f32", "--steps", "20", "--warmup", "2", "--no-autotune"],
-     "mrt_sweep_kernel<float, 4, 0>", N * N),
-    ("batch512", ["--only", "batch", "--batch-steps", "20", "--no-autotune"], "fd_batch_kernel<float, ", BATCH_NODES),
+     "mrt_fused_kernel<float, 4, 0, 5, false>", N * N),
+    ("batch512", ["--only", "batch", "--batch-steps", "20", "--no-autotune"], "fd_batch_fused_kernel<float, ",
+     BATCH_NODES),
     ("d3_f32", ["--only", "d3_f32", "--d3-steps", "20"], "d3_sweep_kernel<float, 12>", N3 ** 3),
 ]
+# time steps that one dispatch of each takes; for the batch, those of a launch of three steps and one of two
+VALU_STEPS = {"fd3_f32": 2, "fd3_f16": 2, "mrt_f32": 5, "batch512": 5, "d3_f32": 1}
 SIMDS = 1024  # 256 compute units x 4 SIMDs
 XCDS = 8
 
 DECAY = "8192 x 8192 periodic decaying flow (modes 0<|k|<=32, max|field| 0.02), nu 0.02"
 KERNELS = [
     # file stem, kernel name pattern, algorithmic bytes per launch, counter pair, sources, workload
-    # (the batch stem sums its per-class kernels, see summarise(group=True))
-    ("fd3_f32_8192", "fd_sweep_kernel<float, 4, 3, false, false, 0>", 24 * N * N, "fd", FD_SOURCES,
+    # (the batch stem sums its kernels of three and of two steps, see summarise(group=True));
+    # a launch reads and writes the state once, whatever the number of steps it takes (STEPS)
+    ("fd3_f32_8192", "fd_fused_kernel<float, 4, 3, false, false, 0, 2, 1, 2>", 24 * N * N, "fd", FD_SOURCES,
      f"{DECAY}; FD-LBM 3-point, FP32 (3 words read + 3 written per node)"),
-    ("mrt_f32_8192", "mrt_sweep_kernel<float, 4, 0>", 72 * N * N, "mrt", MRT_SOURCES,
+    ("mrt_f32_8192", "mrt_fused_kernel<float, 4, 0, 5, false>", 72 * N * N, "mrt", MRT_SOURCES,
      f"{DECAY}; MRT D2Q9, FP32 (9 words read + 9 written per node)"),
-    ("fd3_f64_8192", "fd_sweep_kernel<double, 2, 3, false, false, 0>", 48 * N * N, None, FD_SOURCES,
+    ("fd3_f64_8192", "fd_fused_kernel<double, 2, 3, false, false, 0, 2, 1, 2>", 48 * N * N, None, FD_SOURCES,
      f"{DECAY}; FD-LBM 3-point, FP64"),
-    ("fd3_f16_8192", "fd_sweep_kernel<__half, 4, 3, false, false, 0>", 12 * N * N, None, FD_SOURCES,
+    ("fd3_f16_8192", "fd_fused_kernel<__half, 4, 3, false, false, 0, 2, 1, 2>", 12 * N * N, None, FD_SOURCES,
      f"{DECAY}; FD-LBM 3-point, FP16 storage, FP32 arithmetic"),
     ("fd3_f16sr_8192", "fd_sweep_kernel<fdlbm::HalfSR, 4, 3, false, false, 0>", 12 * N * N, None, FD_SOURCES,
      f"{DECAY}; FD-LBM 3-point, FP16 storage rounded stochastically, FP32 arithmetic"),
-    ("fd5_f32_8192", "fd_sweep_kernel<float, 4, 5, false, false, 0>", 24 * N * N, None, FD_SOURCES,
+    ("fd5_f32_8192", "fd_fused_kernel<float, 4, 5, false, false, 0, 2, 1, 2>", 24 * N * N, None, FD_SOURCES,
      f"{DECAY}; FD-LBM 5-point, FP32"),
-    ("lwacm_f32_8192", "fd_sweep_kernel<float, 4, 1, false, false, 0>", 24 * N * N, None, FD_SOURCES,
+    ("lwacm_f32_8192", "fd_fused_kernel<float, 4, 1, false, false, 0, 3, 1, 3>", 24 * N * N, None, FD_SOURCES,
      f"{DECAY}; LW-ACM (section 1-b), FP32, the same 3 words per node as FD-LBM"),
-    ("mrt_f64_8192", "mrt_sweep_kernel<double, 2, 0>", 144 * N * N, None, MRT_SOURCES,
+    ("mrt_f64_8192", "mrt_fused_kernel<double, 2, 0, 5, false>", 144 * N * N, None, MRT_SOURCES,
      f"{DECAY}; MRT D2Q9, FP64"),
-    ("fd3_f32_channel_16384x1024", "fd_sweep_kernel<float, 4, 3, true, true, 0>", 24 * CHANNEL, None, FD_SOURCES,
+    ("fd3_f32_channel_16384x1024", "fd_fused_kernel<float, 4, 3, true, true, 0, 2, 1, 2>", 24 * CHANNEL, None,
+     FD_SOURCES,
      "Poiseuille channel 16384 x 1024, walls at y=-1/2 and ny-1/2, body force; FD-LBM 3-point, FP32"),
-    ("mrt_f32_channel_16384x1024", "mrt_sweep_kernel<float, 4, 1>", 72 * CHANNEL, None, MRT_SOURCES,
+    ("mrt_f32_channel_16384x1024", "mrt_fused_kernel<float, 4, 0, 5, true>", 72 * CHANNEL, None, MRT_SOURCES,
      "Poiseuille channel 16384 x 1024, halfway bounce-back walls, body force; MRT D2Q9, FP32"),
-    ("fd3_f32_batch512", "fd_batch_kernel<float, ", 24 * BATCH_NODES, None,
-     [f"{CSRC}/fd_batch.hip", f"{CSRC}/fd_sweep_body.hpp", f"{CSRC}/fdlbm_device.hpp"],
-     "512 periodic shear-wave instances N x N, N ~ U{32..1024}, one launch per step for all; FP32"),
+    ("fd3_f32_batch512", "fd_batch_fused_kernel<float, ", 2 * 24 * BATCH_NODES, None,
+     BATCH_SOURCES,
+     "512 periodic shear-wave instances N x N, N ~ U{32..1024}, A(t) every 10 steps, which launches of 3, 3, 2 and 2 "
+     "steps of all of them take; per launch of three and one of two; FP32"),
     ("fd3d_f32_512", "d3_sweep_kernel<float, 12>", 32 * N3 ** 3, "d3", D3_SOURCES,
      "512^3 periodic decaying flow (modes 0<|k|<=8, max|field| 0.02), nu 0.02; FD-LBM D3Q19 sweep kernel, FP32 "
      "(4 words read + 4 written per node)"),
@@ -258,6 +268,12 @@ KERNELS = [
     ("copy_1gib", "copy_kernel", 2 * COPY_BYTES, None, [f"{CSRC}/diag.hip"],
      "fdlbm_device_copy of 1 GiB (the achievable-bandwidth probe)"),
 ]
+
+
+# time steps per launch where it is not one (the batch: per launch of three steps and one of two)
+STEPS = {"fd3_f32_8192": 2, "mrt_f32_8192": 5, "fd3_f64_8192": 2, "fd3_f16_8192": 2, "fd5_f32_8192": 2,
+         "lwacm_f32_8192": 3, "mrt_f64_8192": 5, "fd3_f32_channel_16384x1024": 2, "mrt_f32_channel_16384x1024": 5,
+         "fd3_f32_batch512": 5}
 
 
 def _run(cmd, log, limit, kill_signal):
@@ -273,8 +289,8 @@ def _run(cmd, log, limit, kill_signal):
 def valu_summary(raw, out_md, command):
     """VALU busy of each pass: SQ_ACTIVE_INST_VALU x 4 cycles (a wave64 VALU instruction holds
     a SIMD for 4 cycles; packed FP32 is not used) over the SIMD-cycles of the dispatch
-    (GRBM_GUI_ACTIVE is summed over the XCDs), and VALU instructions per node update
-    (SQ_INSTS_VALU x 64 lanes / nodes)."""
+    (GRBM_GUI_ACTIVE is summed over the XCDs), and VALU instructions per node of a launch
+    (SQ_INSTS_VALU x 64 lanes / nodes) and per node and step."""
     lines = ["# rocprofv3 VALU counters of the step kernels", "",
              "Written by: `python -m paper_1803_00437_amd.profiling collect --raw <dir> --out profiles`", "",
              "Commands (one counter pass each, nothing else collected):", ""]
@@ -292,19 +308,21 @@ def valu_summary(raw, out_md, command):
         waves = sum(means["SQ_WAVES"][k][1] for k in hits)
         calls = min(means["SQ_INSTS_VALU"][k][0] for k in hits)
         busy = active * 4 / (SIMDS * cycles)
-        rows.append((pattern if len(hits) == 1 else pattern + " (" + str(len(hits)) + " kernels per step)", calls,
-                     insts, active, cycles * XCDS, waves, busy, insts * 64 / nodes))
-    lines += ["", "Per dispatch of the step kernel (per step, summed over its kernels, for the batch), averaged "
+        rows.append((pattern if len(hits) == 1 else pattern + " (" + str(len(hits)) + " kernels)", calls,
+                     insts, active, cycles * XCDS, waves, busy, insts * 64 / nodes, VALU_STEPS[name]))
+    lines += ["", "Per dispatch of the step kernel (for the batch, summed over one of each of its kernels), averaged "
               "over the dispatches. VALU busy = SQ_ACTIVE_INST_VALU x 4 / (1024 SIMDs x GRBM_GUI_ACTIVE / 8); "
-              "per node = SQ_INSTS_VALU x 64 / nodes updated.", "",
+              "per node = SQ_INSTS_VALU x 64 / nodes of the grid; a dispatch takes `steps` time steps.", "",
               "| kernel | dispatches | SQ_INSTS_VALU | SQ_ACTIVE_INST_VALU | GRBM_GUI_ACTIVE (sum of 8 XCDs) | "
-              "SQ_WAVES | VALU busy | VALU instructions per node |", "|---|---|---|---|---|---|---|---|"]
+              "SQ_WAVES | VALU busy | VALU instructions per node | steps | per node and step |",
+              "|---|---|---|---|---|---|---|---|---|---|"]
     for r in rows:
         lines.append(f"| `{r[0]}` | {r[1]} | {r[2]:.4g} | {r[3]:.4g} | {r[4]:.4g} | {r[5]:.0f} | {100 * r[6]:.0f} % | "
-                     f"{r[7]:.1f} |")
+                     f"{r[7]:.1f} | {r[8]} | {r[7] / r[8]:.1f} |")
     with open(out_md, "w") as f:
         f.write("\n".join(lines) + "\n")
     summary = {name: {"kernel": r[0], "valu_insts": r[2], "busy": r[6], "insts_per_node": r[7],
+                      "insts_per_node_step": r[7] / r[8],
                       "kernel_source_sha": sources_sha(VALU_SOURCES[name])}
                for (name, _, _, _), r in zip(VALU_PASSES, rows)}
     with open(os.path.splitext(out_md)[0] + ".json", "w") as f:
@@ -345,7 +363,7 @@ def collect(raw, out, run=True):
             _run(valu_cmd + ["-d", d, "--"] + py + args, f"{d}.log", 120, "KILL")
     valu = valu_summary(raw, os.path.join(out, "valu_busy_8192.md"), "cd /tmp && TMPDIR=/tmp " + " ".join(valu_cmd))
     for r in valu:
-        print(f"valu {r[0]}: {r[2]:.4g} instructions, {100 * r[6]:.0f} % busy, {r[7]:.1f} per node")
+        print(f"valu {r[0]}: {r[2]:.4g} instructions, {100 * r[6]:.0f} % busy, {r[7] / r[8]:.1f} per node and step")
     trace_str = "cd /tmp && TMPDIR=/tmp " + " ".join(["rocprofv3"] + trace_opts + ["-d", "<dir>", "--"] + py + TRACE_ARGS)
     results = {}
     for stem, pattern, alg, counters, sources, workload in KERNELS:
@@ -355,6 +373,7 @@ def collect(raw, out, run=True):
             kw = dict(fetch=f, write=w, counter_command=cc, json_out=os.path.join(out, f"{stem}_counters.json"))
         results[stem] = summarise(f"{raw}/trace", pattern, alg, os.path.join(out, f"{stem}.md"), sources=sources,
                                   command=trace_str, workload=workload, group=stem.endswith("batch512"),
+                                  steps=STEPS.get(stem, 1),
                                   n=N3 if stem.startswith("fd3d") else N,
                                   generator="python -m paper_1803_00437_amd.profiling collect --raw <dir> --out profiles",
                                   **kw)
