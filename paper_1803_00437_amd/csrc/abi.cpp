@@ -276,13 +276,16 @@ struct fdlbm_ctx {
 
 namespace {
 // Between the calls that move a state through it, the staging area holds the small disk's map of
-// nodes: such a call forms the map again when it ends, however it ends.
+// nodes: such a call forms the map again when it ends, however it ends, and waits for it (the steps
+// that read it may have been recorded into a graph that runs on another stream).
 struct StagingUse {
     fdlbm_ctx *c;
     explicit StagingUse(fdlbm_ctx *ctx) : c(ctx) {}
     ~StagingUse()
     {
-        if (c->tdisk.map) (void)launch_disk_map(c->disk, c->tdisk.map, c->stream);
+        if (!c->tdisk.map) return;
+        (void)launch_disk_map(c->disk, c->tdisk.map, c->stream);
+        (void)hipStreamSynchronize(c->stream);
     }
 };
 }  // namespace

@@ -193,3 +193,35 @@ def test_diagnostics_of_many_contexts(F):
     assert sims[1].diagnostics()["mass"] == pytest.approx(0.128)
     for sim in sims[1::2] + [again]:
         sim.close()
+
+
+@pytest.mark.parametrize("nx,ny,n,kw", [
+    (72, 72, 10, dict(dtype="f64", bc="disk", disk=(35.5, 35.5, 29.9))),
+    (64, 64, 10, dict(dtype="f64")),
+    (1030, 520, 8, dict(dtype="f32", kernel="sweep")),
+    (191, 100, 12, dict(dtype="f64", scheme="lwacm")),
+    (333, 200, 10, dict(dtype="f32", scheme="mrt")),
+])
+def test_recorded_steps_replay(F, nx, ny, n, kw):
+    """Steps recorded into a graph, which then runs on another stream, with the state read (through
+    the staging area) between its replays: the bits of the same steps issued one call at a time."""
+    import torch
+
+    init = W.random_state(nx, ny, seed=3, amp=2e-3)
+    eager = F.FdLbm(nx, ny, s_xx=1.3, s_e=1.1, **kw)
+    sim = F.FdLbm(nx, ny, s_xx=1.3, s_e=1.1, stream=torch.cuda.Stream(), **kw)
+    for s in (eager, sim):
+        s.set_state(*init)
+        s.step(n)
+    torch.cuda.synchronize()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph, stream=sim.stream):
+        sim.step(n)
+    for r in range(3):
+        print(f"  replay {r} of {nx}x{ny} {kw}", flush=True)
+        graph.replay()
+        torch.cuda.synchronize()
+        eager.step(n)
+        assert all(np.array_equal(a, b) for a, b in zip(sim.get_state(), eager.get_state()))
+    eager.close()
+    sim.close()
