@@ -274,22 +274,6 @@ struct fdlbm_ctx {
     double *sd(size_t off) const { return reinterpret_cast<double *>(scratch + off); }
 };
 
-namespace {
-// Between the calls that move a state through it, the staging area holds the small disk's map of
-// nodes: such a call forms the map again when it ends, however it ends, and waits for it (the steps
-// that read it may have been recorded into a graph that runs on another stream).
-struct StagingUse {
-    fdlbm_ctx *c;
-    explicit StagingUse(fdlbm_ctx *ctx) : c(ctx) {}
-    ~StagingUse()
-    {
-        if (!c->tdisk.map) return;
-        (void)launch_disk_map(c->disk, c->tdisk.map, c->stream);
-        (void)hipStreamSynchronize(c->stream);
-    }
-};
-}  // namespace
-
 extern "C" {
 
 int fdlbm_workspace_bytes(const fdlbm_params *p, size_t *state_bytes, size_t *scratch_bytes)
@@ -377,12 +361,15 @@ int fdlbm_create(const fdlbm_params *p, void *state_a, void *state_b, void *scra
             c->disk.nring = int(t.ring.size());
             c->disk.ring = reinterpret_cast<const int32_t *>(sc + L.disk_ring);
             const size_t ng = t.dst.size(), nr = t.ring.size();
-            if (c->tile.steps > 0) {
-                c->tdisk.map = reinterpret_cast<int32_t *>(sc + L.staging);
-                c->tdisk.src = c->disk.src;
-                c->tdisk.w = c->disk.w;
+            // tiles find a row's ghosts by their columns and never launch the fill, which alone reads
+            // dst: their rows lie in its place
+            const bool tiles = c->tile.steps > 0;
+            const std::vector<int32_t> &dst = tiles ? t.rows : t.dst;
+            if (tiles) {
+                c->tdisk = TileDisk{c->disk.dst, t.row0, int(t.rows.size() / DISK_ROW), c->disk.src, c->disk.w};
+                c->disk.dst = nullptr;
             }
-            if (e == hipSuccess && ng) e = hipMemcpyAsync(sc + L.disk_dst, t.dst.data(), ng * sizeof(int32_t), hipMemcpyHostToDevice, c->stream);
+            if (ng) e = hipMemcpyAsync(sc + L.disk_dst, dst.data(), dst.size() * sizeof(int32_t), hipMemcpyHostToDevice, c->stream);
             if (e == hipSuccess && ng)
                 e = hipMemcpyAsync(sc + L.disk_src, t.src.data(), ng * sizeof(int32_t), hipMemcpyHostToDevice, c->stream);
             if (e == hipSuccess && ng)
@@ -393,7 +380,6 @@ int fdlbm_create(const fdlbm_params *p, void *state_a, void *state_b, void *scra
             if (e == hipSuccess && nr)
                 e = hipMemcpyAsync(sc + L.disk_ring, t.ring.data(), nr * sizeof(int32_t), hipMemcpyHostToDevice,
                                    c->stream);
-            if (e == hipSuccess && c->tdisk.map) e = launch_disk_map(c->disk, c->tdisk.map, c->stream);
         }
         if (e == hipSuccess) e = hipStreamSynchronize(c->stream);
         if (e != hipSuccess) {
@@ -425,7 +411,6 @@ int fdlbm_set_state(fdlbm_ctx *c, const double *drho, const double *jx, const do
     if (!c || !drho || !jx || !jy) return FDLBM_EINVAL;
     HIPCHK(hipSetDevice(c->device), "hipSetDevice");
     const size_t n = c->n(), nb = n * sizeof(double);
-    const StagingUse staging(c);
     double *st = c->sd(c->L.staging);
     HIPCHK(hipMemcpyAsync(st, drho, nb, hipMemcpyHostToDevice, c->stream), "set_state upload");
     HIPCHK(hipMemcpyAsync(st + n, jx, nb, hipMemcpyHostToDevice, c->stream), "set_state upload");
@@ -445,7 +430,6 @@ int fdlbm_get_state(fdlbm_ctx *c, double *drho, double *jx, double *jy)
     if (!c || !drho || !jx || !jy) return FDLBM_EINVAL;
     HIPCHK(hipSetDevice(c->device), "hipSetDevice");
     const size_t n = c->n(), nb = n * sizeof(double);
-    const StagingUse staging(c);
     double *st = c->sd(c->L.staging);
     if (three_words(c->p.scheme))
         HIPCHK(launch_unpack_rows(c->p.dtype, 3, c->buf[c->cur], st, c->p.nx, c->p.ny, c->stream), "unpack");
@@ -463,7 +447,6 @@ int fdlbm_set_populations(fdlbm_ctx *c, const double *df)
     if (!c || !df || c->p.scheme != FDLBM_SCHEME_MRT) return FDLBM_EINVAL;
     HIPCHK(hipSetDevice(c->device), "hipSetDevice");
     const size_t n = c->n();
-    const StagingUse staging(c);
     double *st = c->sd(c->L.staging);
     HIPCHK(hipMemcpyAsync(st, df, 9 * n * sizeof(double), hipMemcpyHostToDevice, c->stream), "set_populations");
     HIPCHK(launch_pack_rows(c->p.dtype, 9, st, c->buf[c->cur], c->p.nx, c->p.ny, c->stream), "pack");
@@ -478,7 +461,6 @@ int fdlbm_get_populations(fdlbm_ctx *c, double *df)
     if (!c || !df || c->p.scheme != FDLBM_SCHEME_MRT) return FDLBM_EINVAL;
     HIPCHK(hipSetDevice(c->device), "hipSetDevice");
     const size_t n = c->n();
-    const StagingUse staging(c);
     double *st = c->sd(c->L.staging);
     HIPCHK(launch_unpack_rows(c->p.dtype, 9, c->buf[c->cur], st, c->p.nx, c->p.ny, c->stream), "unpack");
     HIPCHK(hipMemcpyAsync(df, st, 9 * n * sizeof(double), hipMemcpyDeviceToHost, c->stream), "get_populations");

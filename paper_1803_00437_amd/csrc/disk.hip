@@ -97,6 +97,12 @@ bool build_disk_table(int nx, int ny, double cx, double cy, double r, DiskTable 
         }
         t.span[2 * size_t(j)] = int32_t(a);
         t.span[2 * size_t(j) + 1] = int32_t(b);
+        if (a <= b) {
+            if (t.rows.empty()) t.row0 = j;
+            const bool fluid = flo[j] <= fhi[j];
+            for (long v : {a, b, fluid ? flo[j] : b + 1, fluid ? fhi[j] : b, long(t.dst.size())})
+                t.rows.push_back(int32_t(v));
+        }
         for (long i = a; i <= b; ++i) {
             if (i >= flo[j] && i <= fhi[j]) continue;
             const double rr = std::hypot(double(i) - cx, double(j) - cy);
@@ -225,20 +231,6 @@ __global__ __launch_bounds__(TPB) void disk_fill_kernel(DiskFill f, T *state, in
     }
 }
 
-// The tiles' map of nodes: fluid or rest by the spans, then the ghosts by their index.
-__global__ __launch_bounds__(TPB) void disk_map_kernel(DiskFill f, int32_t *map)
-{
-    const size_t t = size_t(blockIdx.x) * TPB + threadIdx.x, nx = size_t(f.nx);
-    if (t >= nx * size_t(f.ny)) return;
-    const int j = int(t / nx), i = int(t - size_t(j) * nx);
-    map[t] = i >= f.span[2 * j] && i <= f.span[2 * j + 1] ? DISK_FLUID : DISK_REST;
-}
-__global__ __launch_bounds__(TPB) void disk_map_ghosts_kernel(DiskFill f, int32_t *map)
-{
-    const int g = blockIdx.x * TPB + threadIdx.x;
-    if (g < f.nghost) map[f.dst[g]] = g;
-}
-
 // MRT: one thread per boundary link.  The population re-entering the fluid node x along
 // k' = -e_k is rebuilt from post-collision values still present in the streamed grid:
 // f*_k(x) at the solid node x + e_k, f*_k(x - e_k) at x itself, f*_k'(x) at x - e_k:
@@ -323,16 +315,6 @@ hipError_t launch_mrt_disk(const MrtDisk &d, int dtype, void *pop, bool full, hi
     case FDLBM_F32: return mrt_disk_run<float>(d, static_cast<float *>(pop), full, s);
     default: return hipErrorInvalidValue;
     }
-}
-
-hipError_t launch_disk_map(const DiskFill &f, int32_t *map, hipStream_t s)
-{
-    const size_t n = size_t(f.nx) * size_t(f.ny);
-    hipLaunchKernelGGL(disk_map_kernel, (n + TPB - 1) / TPB, TPB, 0, s, f, map);
-    hipError_t e = hipGetLastError();
-    if (e != hipSuccess || f.nghost == 0) return e;
-    hipLaunchKernelGGL(disk_map_ghosts_kernel, (f.nghost + TPB - 1) / TPB, TPB, 0, s, f, map);
-    return hipGetLastError();
 }
 
 hipError_t launch_disk_fill(const DiskFill &f, int dtype, void *state, bool full, hipStream_t s)

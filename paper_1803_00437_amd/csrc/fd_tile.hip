@@ -64,18 +64,30 @@ __global__ void __launch_bounds__(64 * TW) fd_tile_kernel(TileStepArgs<T> a)
     for (int i = 0; i < R; ++i) {
         const int y = grid_row(y0 + i);
         const T *row = a.in + fd_elem(0, y, 0, nx);
+        // the curved wall: ghost nodes from the fluid, as disk_fill_kernel sets them, and rest
+        // nodes at rest (the fill and the step in one launch)
+        const int dr = DISK ? y - a.disk.row0 : 0;
+        const bool drow = DISK && dr >= 0 && dr < a.disk.nrows;  // this row has ghosts
+        int ga = 0, gb = -1, glo = 0, ghi = -1, g0 = 0;
+        if (drow) {
+            const int32_t *d = a.disk.rows + DISK_ROW * dr;
+            ga = d[0];
+            gb = d[1];
+            glo = d[2];
+            ghi = d[3];
+            g0 = d[4];
+        }
 #pragma unroll
         for (int c = 0; c < CPL; ++c) {
-            // the curved wall: ghost nodes from the fluid, as disk_fill_kernel sets them, and rest
-            // nodes at rest (the fill and the step in one launch)
-            const int g = DISK ? a.disk.map[(size_t)y * nx + col[c]] : DISK_FLUID;
-            if (g == DISK_FLUID) {
+            const int x = (int)col[c];
+            if (!DISK || (x >= glo && x <= ghi)) {
 #pragma unroll
                 for (int f = 0; f < 3; ++f) v[i][f][c] = Storage<T>::load(row[(size_t)f * nx + col[c]]);
-            } else if (g == DISK_REST) {
+            } else if (x < ga || x > gb) {
 #pragma unroll
                 for (int f = 0; f < 3; ++f) v[i][f][c] = C(0);
             } else {
+                const int g = g0 + (x < glo ? x - ga : (glo - ga) + (x - ghi - 1));
                 const unsigned src = (unsigned)a.disk.src[g], sy = src / (unsigned)nx, sx = src - sy * (unsigned)nx;
                 const C wx = C(a.disk.w[3 * g]), wy = C(a.disk.w[3 * g + 1]), sj = C(a.disk.w[3 * g + 2]);
                 const C ux = C(1) - wx, uy = C(1) - wy;
@@ -326,12 +338,12 @@ template <typename T, int CPL, int R>
 hipError_t dispatch(const FdArgs &a, const TilePlan &p, const TileDisk &disk, const void *src, void *dst, hipStream_t s)
 {
     if constexpr (CPL == 1)
-        if (disk.map) {
+        if (disk.rows) {
             if (a.stencil == 1) return force<T, CPL, R, 1, false, true>(a, p, disk, src, dst, s);
             if (a.stencil == 5) return force<T, CPL, R, 5, false, true>(a, p, disk, src, dst, s);
             return force<T, CPL, R, 3, false, true>(a, p, disk, src, dst, s);
         }
-    if (disk.map) return hipErrorInvalidValue;
+    if (disk.rows) return hipErrorInvalidValue;
     if (a.stencil == 1) return force<T, CPL, R, 1, false, false>(a, p, disk, src, dst, s);
     if (a.stencil == 5) return force<T, CPL, R, 5, false, false>(a, p, disk, src, dst, s);
     if (a.walls) return force<T, CPL, R, 3, true, false>(a, p, disk, src, dst, s);

@@ -91,11 +91,11 @@ inline TilePlan plan_tiles(int nx, int ny, int reach, int elem_bytes, double row
     return best;
 }
 // FD-LBM and LW-ACM: the plan (steps = 0 where the tiles do not apply) and a launch of p.steps steps.
-// In the disk, map gives per node DISK_FLUID, DISK_REST or the index of its ghost in src and w (the
-// table of DiskFill); null elsewhere.
-constexpr int DISK_FLUID = -1, DISK_REST = -2;
+// In the disk, rows describes the grid rows row0 .. row0 + nrows - 1, those with ghost nodes
+// (DiskTable), whose sources and weights are src and w (the table of DiskFill); null elsewhere.
 struct TileDisk {
-    int32_t *map = nullptr;
+    const int32_t *rows = nullptr;
+    int row0 = 0, nrows = 0;
     const int32_t *src = nullptr;
     const double *w = nullptr;
 };
@@ -172,8 +172,14 @@ hipError_t launch_batch_sample(const BatchLaunch &L, const void *state, hipStrea
 // row j, the nodes [span[2j], span[2j+1]] are fluid or ghost; the others are set to rest.
 // ring: the rest nodes within the step's reach (3) of a fluid or ghost node, periodic images
 // included: without a body force the only rest nodes a step can move.
+// rows: for the grid rows from row0 on that have ghosts, DISK_ROW numbers each: the columns a and b of
+// the first and last fluid or ghost node, those lo and hi of the fluid (none: lo = b + 1, hi = b),
+// and the index of the row's first ghost (ghosts are numbered row by row, from left to right).  A
+// row has at least GHOST_REACH ghosts on each side, so the rows take less room than dst.
+constexpr int DISK_ROW = 5;
 struct DiskTable {
-    std::vector<int32_t> dst, src, span, ring;
+    std::vector<int32_t> dst, src, span, ring, rows;
+    int row0 = 0;
     std::vector<double> w;  // 3 per ghost
     size_t nfluid = 0;
     // MRT D2Q9 (interpolated bounce-back on the circle): per boundary link its fluid node,
@@ -195,8 +201,6 @@ struct DiskFill {
 // full: set every rest node to rest (first step after the state was set, or a body force
 // acts); otherwise the ring only
 hipError_t launch_disk_fill(const DiskFill &f, int dtype, void *state, bool full, hipStream_t s);
-// The map of TileDisk, nx * ny values.  Two launches.
-hipError_t launch_disk_map(const DiskFill &f, int32_t *map, hipStream_t s);
 // MRT in the disk: after the periodic step of the whole grid (populations `pop`, in place),
 // the interpolated bounce-back of every boundary link, then the solid nodes set to rest
 // (full: every non-fluid node; otherwise the solid ring the links reach).  Two launches.
