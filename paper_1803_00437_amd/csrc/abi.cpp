@@ -79,21 +79,32 @@ bool uses_reference(const fdlbm_params &p)
     return !fd_sweep_supported(fd_args(p), p.lane_cols);
 }
 
-// Steps that one launch of a context may take.  The disk's wall acts between the steps; a tile
-// shape asked for is that of one-step launches.
-int max_fused(const fdlbm_params &p, double s_q)
+// How a context's steps are dealt to launches (launch_plan.hpp).  The disk's wall acts between the steps;
+// a tile shape asked for is that of one-step launches.
+struct StepPlan {
+    LaunchTimes times;
+    TilePlan tile;  // steps > 0: tiles, where they are the faster way
+    TileCost cost;
+};
+StepPlan step_plan(const fdlbm_params &p, double s_q)
 {
-    if (p.bc == FDLBM_BC_DISK || uses_reference(p) || p.tile_rows != 0 || p.lane_cols != 0) return 1;
-    return three_words(p.scheme) ? fd_max_fused(fd_args(p)) : mrt_max_fused(mrt_args(p, s_q));
-}
-
-// Tiles that stay in registers for several steps, where they are the faster way.
-TilePlan tile_plan(const fdlbm_params &p, double s_q)
-{
-    const bool disk = p.bc == FDLBM_BC_DISK;
-    if (p.kernel != FDLBM_KERNEL_AUTO || uses_reference(p) || p.tile_rows != 0 || p.lane_cols != 0) return TilePlan();
-    if (three_words(p.scheme)) return fd_tile_plan(fd_args(p), disk);
-    return disk ? TilePlan() : mrt_tile_plan(mrt_args(p, s_q));
+    StepPlan plan;
+    const bool disk = p.bc == FDLBM_BC_DISK, fd = three_words(p.scheme);
+    if (uses_reference(p) || p.tile_rows != 0 || p.lane_cols != 0 || (disk && !fd)) return plan;
+    const bool tiles = p.kernel == FDLBM_KERNEL_AUTO;
+    if (fd) {
+        const FdArgs a = fd_args(p);
+        plan.times = fd_launch_times(a);
+        plan.cost = fd_tile_cost(a);
+        if (tiles) plan.tile = fd_tile_plan(a, plan.times, disk);
+    } else {
+        const MrtArgs a = mrt_args(p, s_q);
+        plan.times = mrt_launch_times(a);
+        plan.cost = mrt_tile_cost(a);
+        if (tiles) plan.tile = mrt_tile_plan(a, plan.times);
+    }
+    if (disk) plan.times.most = 1;
+    return plan;
 }
 
 int validate(const fdlbm_params *p)
@@ -266,8 +277,7 @@ struct fdlbm_ctx {
     bool disk_full;  // the next fill sets every rest node to rest (the state was just set)
     double *host = nullptr;  // pinned: DIAG_SLOTS values of the diagnostics (null: copied instead)
     int reads = 0;           // of the diagnostics, up to HOST_READS
-    int most;        // steps that one launch may take
-    TilePlan tile;   // tile.steps > 0: launches of tiles, up to so many steps each
+    StepPlan plan;   // how steps are dealt to launches
     TileDisk tdisk;  // FDLBM_BC_DISK: the tiles' view of the ghost-node table
 
     size_t n() const { return (size_t)p.nx * (size_t)p.ny; }
@@ -313,8 +323,7 @@ int fdlbm_create(const fdlbm_params *p, void *state_a, void *state_b, void *scra
         c->disk = DiskFill{p->nx, p->ny, 0, 0, nullptr, nullptr, nullptr, nullptr, nullptr};
         c->mdisk = MrtDisk{p->nx, p->ny, 0, 0, nullptr, nullptr, nullptr, nullptr, nullptr};
         c->disk_full = true;
-        c->most = max_fused(*p, c->s_q);
-        c->tile = tile_plan(*p, c->s_q);
+        c->plan = step_plan(*p, c->s_q);
         hipError_t e = hipGetDevice(&c->device);
         size_t sb = 0;
         fdlbm_workspace_bytes(p, &sb, nullptr);
@@ -363,7 +372,7 @@ int fdlbm_create(const fdlbm_params *p, void *state_a, void *state_b, void *scra
             const size_t ng = t.dst.size(), nr = t.ring.size();
             // tiles find a row's ghosts by their columns and never launch the fill, which alone reads
             // dst: their rows lie in its place
-            const bool tiles = c->tile.steps > 0;
+            const bool tiles = c->plan.tile.steps > 0;
             const std::vector<int32_t> &dst = tiles ? t.rows : t.dst;
             if (tiles) {
                 c->tdisk = TileDisk{c->disk.dst, t.row0, int(t.rows.size() / DISK_ROW), c->disk.src, c->disk.w};
@@ -488,51 +497,6 @@ static int run_diag(fdlbm_ctx *c, double out[DIAG_SLOTS])
     return FDLBM_OK;
 }
 
-// How `n` consecutive steps are dealt to launches of up to `most` steps.  A launch reads one state
-// buffer and writes the other whatever its steps, and the current state has to lie in state_a
-// after an even number of steps: launches of five, three and one steps keep that, those of two
-// come in pairs.  One or two fives give way where that leaves no single steps.
-struct Launches {
-    int64_t fives = 0, threes = 0, twos = 0, ones = 0;
-    int64_t count() const { return fives + threes + twos + ones; }
-    int steps(int64_t i) const { return i < fives ? 5 : i < fives + threes ? 3 : i < fives + threes + twos ? 2 : 1; }
-};
-static Launches deal_steps(int64_t n, int most)
-{
-    Launches l;
-    if (most >= 5) {
-        l.fives = n / 5;
-        for (int64_t back = 0; back <= 2 && back <= n / 5; ++back)
-            if ((n % 5 + 5 * back) % 3 == 0) {
-                l.fives -= back;
-                break;
-            }
-        n -= 5 * l.fives;
-    }
-    if (most >= 3) l.threes = n / 3;
-    if (most == 2) l.twos = n / 4 * 2;
-    l.ones = n - 3 * l.threes - 2 * l.twos;
-    return l;
-}
-
-// `n` consecutive steps in launches of tiles of up to `most` steps (an odd number): odd numbers of
-// steps, as even as they can be (`high` launches of `low` + 2 steps, the others of `low`), and as
-// many launches as keep the buffer's parity.
-struct TileLaunches {
-    int64_t count, high;
-    int low;
-};
-static TileLaunches deal_tiles(int64_t n, int most)
-{
-    TileLaunches l;
-    l.count = (n + most - 1) / most;
-    l.count += (l.count ^ n) & 1;
-    l.low = int(n / l.count);
-    l.low -= l.low % 2 == 0;
-    l.high = (n - l.count * l.low) / 2;
-    return l;
-}
-
 static int advance(fdlbm_ctx *c, int64_t nsteps)
 {
     HIPCHK(hipSetDevice(c->device), "hipSetDevice");
@@ -541,7 +505,6 @@ static int advance(fdlbm_ctx *c, int64_t nsteps)
     const bool disk = c->p.bc == FDLBM_BC_DISK;
     FdArgs fa = fd_args(c->p);
     const MrtArgs ma = mrt_args(c->p, c->s_q);
-    const int most = c->most;
     // one launch of k steps from the current buffer into the other one
     auto take = [&](int k) -> int {
         // stochastic rounding draws fresh bits every step, reproducibly from the step count
@@ -557,13 +520,13 @@ static int advance(fdlbm_ctx *c, int64_t nsteps)
         }
         hipError_t e;
         if (!fd)
-            e = launch_mrt(ma, k, src, dst, c->stream);
+            e = launch_mrt(ma, k, c->plan.times.rows[k], src, dst, c->stream);
         else if (ref)
             e = launch_fd_reference(fa, src, dst, c->scratch + c->L.fstar, c->stream);
         else if (k == 1)
             e = launch_fd_sweep(fa, c->p.tile_rows, c->p.lane_cols, src, dst, c->stream);
         else
-            e = launch_fd_fused(fa, src, dst, c->stream);
+            e = launch_fd_fused(fa, c->plan.times.rows[k], src, dst, c->stream);
         if (e != hipSuccess)
             return device_error(e, c->p.scheme == FDLBM_SCHEME_FD    ? "fdlbm_step launch"
                                    : c->p.scheme == FDLBM_SCHEME_MRT ? "mrt_step launch"
@@ -583,11 +546,12 @@ static int advance(fdlbm_ctx *c, int64_t nsteps)
         // up to the next check of the state
         const int64_t every = c->p.check_every;
         const int64_t n = every > 0 ? std::min<int64_t>(left, every - c->steps % every) : left;
-        if (c->tile.steps > 0) {
-            const TileLaunches l = deal_tiles(n, c->tile.steps);
-            for (int64_t i = 0; i < l.count; ++i) {
-                TilePlan tile = c->tile;
-                tile.steps = i < l.high ? l.low + 2 : l.low;
+        // in the disk, tiles take the place of the fill as well: every step or none
+        const Deal l = disk && c->plan.tile.steps > 0 ? deal_tiles(n, 1) : deal(n, c->plan.times, c->plan.tile, c->plan.cost);
+        for (int64_t i = 0; i < l.count(); ++i) {
+            if (l.tiles) {
+                TilePlan tile = c->plan.tile;
+                tile.steps = l.steps(i);
                 const void *src = c->buf[c->cur];
                 void *dst = c->buf[c->cur ^ 1];
                 fa.step = uint32_t(c->steps);
@@ -596,10 +560,7 @@ static int advance(fdlbm_ctx *c, int64_t nsteps)
                        "step launch");
                 c->cur ^= 1;
                 c->steps += tile.steps;
-            }
-        } else {
-            const Launches l = deal_steps(n, most);
-            for (int64_t i = 0; i < l.count(); ++i) {
+            } else {
                 const int rc = take(l.steps(i));
                 if (rc) return rc;
             }
@@ -721,7 +682,7 @@ int fdlbm_autotune(fdlbm_ctx *c, int32_t reps, int32_t *out_lane_cols, int32_t *
             if (fd) return launch_fd_sweep(fa, sh.rows, sh.cols, src, dst, c->stream);
             MrtArgs ma = mrt_args(c->p, c->s_q);
             ma.tile_rows = sh.rows;
-            return launch_mrt(ma, 1, src, dst, c->stream);
+            return launch_mrt(ma, 1, 0, src, dst, c->stream);
         };
         Shape best{0, 0};
         float best_ms = 0.0f;

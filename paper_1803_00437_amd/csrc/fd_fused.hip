@@ -66,7 +66,7 @@ int fused_rows(int strips_x, int ny, int K, int H, bool walls, int waves_per_sim
 }
 
 template <typename T, int CPL, int ST, bool WALLS, bool FORCE, int AM, int K, int KR, int KC>
-hipError_t run(const FdArgs &fa, const void *src, void *dst, hipStream_t s)
+hipError_t run(const FdArgs &fa, int rows, const void *src, void *dst, hipStream_t s)
 {
     constexpr int H = Stencil<ST>::H;
     using G = FusedStrip<CPL, H, K>;
@@ -78,7 +78,9 @@ hipError_t run(const FdArgs &fa, const void *src, void *dst, hipStream_t s)
     a.strips_x = (fa.nx + G::S - 1) / G::S;
     a.stride = G::S;
     if (AM == AM_SEAM) a.stride = seam_stride(fa.nx, G::S, G::P, CPL, sizeof(T));
-    a.rows = fused_rows(a.strips_x, fa.ny, K, H, WALLS, fused_waves<ST>());
+    // no band may reach both walls: see fused_rows()
+    if (rows < 1 || (WALLS && (rows < K * (H + 1) || rows > fa.ny - K * (H + 1)))) return hipErrorInvalidValue;
+    a.rows = rows;
     a.ntiles = a.strips_x * ((fa.ny + a.rows - 1) / a.rows);
     a.k = make_coef<typename Storage<T>::C>(ST, fa.s_xx, fa.s_e, fa.fx, fa.fy);
     a.gr = ghost_rules<typename Storage<T>::C>(fa.xi);
@@ -88,21 +90,21 @@ hipError_t run(const FdArgs &fa, const void *src, void *dst, hipStream_t s)
 }
 
 template <typename T, int CPL, int ST, bool WALLS, bool FORCE, int K, int KR, int KC>
-hipError_t dispatch_width(const FdArgs &a, const void *src, void *dst, hipStream_t s)
+hipError_t dispatch_width(const FdArgs &a, int rows, const void *src, void *dst, hipStream_t s)
 {
-    if (a.nx % CPL == 0) return run<T, CPL, ST, WALLS, FORCE, AM_VEC, K, KR, KC>(a, src, dst, s);
+    if (a.nx % CPL == 0) return run<T, CPL, ST, WALLS, FORCE, AM_VEC, K, KR, KC>(a, rows, src, dst, s);
     using G = FusedStrip<CPL, Stencil<ST>::H, K>;
     if (seam_stride(a.nx, G::S, G::P, CPL, sizeof(T)) > 0)
-        return run<T, CPL, ST, WALLS, FORCE, AM_SEAM, K, KR, KC>(a, src, dst, s);
-    return run<T, CPL, ST, WALLS, FORCE, sizeof(T) >= 4 ? AM_UNAL : AM_COL, K, KR, KC>(a, src, dst, s);
+        return run<T, CPL, ST, WALLS, FORCE, AM_SEAM, K, KR, KC>(a, rows, src, dst, s);
+    return run<T, CPL, ST, WALLS, FORCE, sizeof(T) >= 4 ? AM_UNAL : AM_COL, K, KR, KC>(a, rows, src, dst, s);
 }
 
 template <typename T, int CPL, int ST, bool WALLS, int K, int KR, int KC>
-hipError_t dispatch(const FdArgs &a, const void *src, void *dst, hipStream_t s)
+hipError_t dispatch(const FdArgs &a, int rows, const void *src, void *dst, hipStream_t s)
 {
     if constexpr (ST != 1)
-        if (a.fx != 0.0 || a.fy != 0.0) return dispatch_width<T, CPL, ST, WALLS, true, K, KR, KC>(a, src, dst, s);
-    return dispatch_width<T, CPL, ST, WALLS, false, K, KR, KC>(a, src, dst, s);
+        if (a.fx != 0.0 || a.fy != 0.0) return dispatch_width<T, CPL, ST, WALLS, true, K, KR, KC>(a, rows, src, dst, s);
+    return dispatch_width<T, CPL, ST, WALLS, false, K, KR, KC>(a, rows, src, dst, s);
 }
 
 }  // namespace
@@ -119,46 +121,55 @@ int fd_max_fused(const FdArgs &a)
     return 2;
 }
 
-// Time of one step in launches of K = fd_max_fused(a), in us: the wavefronts each SIMD gets times the
-// rows each takes through K stages of us_row each, and 3 us per launch.  us_row is measured (one
-// stage of one row of 64 CPL columns: 256^2, 1024^2, 2048^2).
-static double fused_row_us(const FdArgs &a)
+// Times of a launch.  One step: blocks of 4 x R rows (the defaults of fd_sweep.hip), one of 256 after
+// the other on a compute unit, R + 4 rows of `one` us each and 3 us; or the state's bytes at 6 TB/s.
+// K steps: the wavefronts each SIMD gets times the rows each takes through K stages of `row` us each,
+// and 3 us.  By stencil and dtype, fitted to 40 grids of 8 to 2048 nodes a side and narrow ones, which they
+// meet within 10 % (the middle half of them), widths that are no multiple of a lane's columns included.
+LaunchTimes fd_launch_times(const FdArgs &a)
 {
-    const bool f64 = a.dtype == FDLBM_F64;
-    return a.stencil == 1 ? (f64 ? 0.27 : 0.37) : a.stencil == 3 ? (f64 ? 0.52 : 0.62) : (f64 ? 0.7 : 0.68);
-}
-// the one-step kernel: blocks of 4 x 8 (FP64 6) rows, two or three at once on a compute unit
-double fd_single_us(const FdArgs &a)
-{
-    const int rows = a.dtype == FDLBM_F64 ? 6 : 8, S = a.dtype == FDLBM_F64 ? 124 : 248;
-    const long blocks = (long)((a.nx + S - 1) / S) * ((a.ny + 4 * rows - 1) / (4 * rows)), each = (blocks + 255) / 256;
-    return 3.0 + double((rows + 4) * each) * fused_row_us(a);
-}
-double fd_fused_us(const FdArgs &a)
-{
-    const int K = fd_max_fused(a), H = a.stencil == 1 ? 0 : a.stencil == 3 ? 1 : 2, CPL = a.dtype == FDLBM_F64 ? 2 : 4;
-    const double us_row = fused_row_us(a);
-    const int P = (K * (H + 1) + CPL - 1) / CPL, S = (64 - 2 * P) * CPL, strips = (a.nx + S - 1) / S;
-    if (K == 1) return fd_single_us(a);
-    const int rows = fused_rows(strips, a.ny, K, H, a.walls != 0, a.stencil == 5 ? 1 : 2);
-    const long each = ((long)strips * ((a.ny + rows - 1) / rows) + 1023) / 1024;
-    return 3.0 / K + double(each) * (rows + 2 * K * (H + 1)) * us_row;
+    const bool f64 = a.dtype == FDLBM_F64, force = a.fx != 0.0 || a.fy != 0.0;
+    const int st = a.stencil == 1 ? 0 : a.stencil == 3 ? 1 : 2, CPL = f64 ? 2 : 4, eb = int(dtype_bytes(a.dtype));
+    // FP64, FP32, FP16, FP16 rounded stochastically
+    static const double one_us[3][4] = {{0.33, 0.40, 0.50, 0.66}, {0.52, 0.63, 0.78, 0.76}, {0.57, 0.82, 0.83, 0.90}};
+    static const double row_us[3][4] = {{0.31, 0.40, 0.40, 0.0}, {0.49, 0.61, 0.61, 0.0}, {0.56, 0.65, 0.65, 0.0}};
+    const double extra = a.walls ? 1.15 : force && !f64 ? 1.05 : 1.0;
+    const double bytes_us = 6.0 * eb * a.nx * a.ny / 6e6;
+    LaunchTimes t;
+    {
+        const int rows = f64 ? 6 : is_f16(a.dtype) || a.stencil == 5 ? 16 : a.stencil == 1 ? 4 : 8, S = f64 ? 124 : 248;
+        const long blocks = (long)((a.nx + S - 1) / S) * ((a.ny + 4 * rows - 1) / (4 * rows)), each = (blocks + 255) / 256;
+        double us = one_us[st][a.dtype] * extra;
+        if (a.nx % CPL != 0 && !f64) us *= a.dtype == FDLBM_F32 ? 1.17 : a.nx % 2 ? 1.27 : 0.75;
+        t.one = 3.0 + std::max(double((rows + 4) * each) * us, bytes_us);
+    }
+    t.most = fd_max_fused(a);
+    if (t.most > 1) {
+        const int K = t.most, H = st, P = (K * (H + 1) + CPL - 1) / CPL, S = (64 - 2 * P) * CPL, strips = (a.nx + S - 1) / S;
+        const int rows = fused_rows(strips, a.ny, K, H, a.walls != 0, a.stencil == 5 ? 1 : 2);
+        const long each = ((long)strips * ((a.ny + rows - 1) / rows) + 1023) / 1024;
+        double us = row_us[st][a.dtype] * extra;
+        if (a.nx % CPL != 0 && seam_stride(a.nx, S, P, CPL, eb) == 0) us *= 1.4;
+        t.rows[K] = rows;
+        t.fused[K] = 3.0 + std::max(double(K * each) * (rows + 2 * K * (H + 1)) * us, bytes_us);
+    }
+    return t;
 }
 
-template <typename T, int CPL> static hipError_t launch(const FdArgs &a, const void *src, void *dst, hipStream_t s)
+template <typename T, int CPL> static hipError_t launch(const FdArgs &a, int rows, const void *src, void *dst, hipStream_t s)
 {
-    if (a.stencil == 1) return dispatch<T, CPL, 1, false, 3, 1, sizeof(T) == 8 ? 2 : 3>(a, src, dst, s);
-    if (a.stencil == 5) return dispatch<T, CPL, 5, false, 2, 1, 2>(a, src, dst, s);
-    if (a.walls) return dispatch<T, CPL, 3, true, 2, 1, 2>(a, src, dst, s);
-    return dispatch<T, CPL, 3, false, 2, 1, 2>(a, src, dst, s);
+    if (a.stencil == 1) return dispatch<T, CPL, 1, false, 3, 1, sizeof(T) == 8 ? 2 : 3>(a, rows, src, dst, s);
+    if (a.stencil == 5) return dispatch<T, CPL, 5, false, 2, 1, 2>(a, rows, src, dst, s);
+    if (a.walls) return dispatch<T, CPL, 3, true, 2, 1, 2>(a, rows, src, dst, s);
+    return dispatch<T, CPL, 3, false, 2, 1, 2>(a, rows, src, dst, s);
 }
 
-hipError_t launch_fd_fused(const FdArgs &a, const void *src, void *dst, hipStream_t s)
+hipError_t launch_fd_fused(const FdArgs &a, int rows, const void *src, void *dst, hipStream_t s)
 {
     switch (a.dtype) {
-    case FDLBM_F64: return launch<double, 2>(a, src, dst, s);
-    case FDLBM_F32: return launch<float, 4>(a, src, dst, s);
-    case FDLBM_F16DEV: return launch<__half, 4>(a, src, dst, s);
+    case FDLBM_F64: return launch<double, 2>(a, rows, src, dst, s);
+    case FDLBM_F32: return launch<float, 4>(a, rows, src, dst, s);
+    case FDLBM_F16DEV: return launch<__half, 4>(a, rows, src, dst, s);
     default: return hipErrorInvalidValue;
     }
 }

@@ -11,7 +11,7 @@
 // the differences reach, then the sums that cross.  Columns come from the adjacent lanes (DPP).
 //
 // What bounds it: a step is 4 R CPL rows of vector instructions per SIMD plus two barriers, and a
-// launch costs its start, the loads and the stores besides; tile_plan() weighs the rows and columns
+// launch costs its start, the loads and the stores besides; TileCost weighs the rows and columns
 // formed twice against that.
 #include <algorithm>
 
@@ -365,19 +365,30 @@ hipError_t shapes(const FdArgs &a, const TilePlan &p, const TileDisk &disk, cons
 
 // In the disk the wall acts between the steps: one step per launch, which spares the launch of the
 // fill (72^2 FP64: 7.0 + 2.8 us).
-TilePlan fd_tile_plan(const FdArgs &a, bool disk)
+TileCost fd_tile_cost(const FdArgs &a)
+{
+    const bool f64 = a.dtype == FDLBM_F64, force = a.fx != 0.0 || a.fy != 0.0;
+    const int H = a.stencil == 1 ? 0 : a.stencil == 3 ? 1 : 2;
+    TileCost c;
+    c.nx = a.nx;
+    c.ny = a.ny;
+    c.reach = H + 1;
+    c.elem_bytes = int(compute_bytes(a.dtype));
+    c.lds = size_t(6 * TW * std::max(H, 1) + 4 * TW + (a.walls ? 12 : 0)) * 64 * c.elem_bytes;  // edge, cross, wall
+    c.row_us = a.stencil == 1 ? (f64 ? 0.55 : 0.45)
+                              : (a.stencil == 3 ? (f64 ? 0.9 : 0.65) : (f64 ? 1.3 : 0.85)) + (force ? 0.08 : 0.0);
+    if (a.dtype == FDLBM_F16DEV_SR) c.row_us += 0.12;  // two hashes per node
+    return c;
+}
+
+TilePlan fd_tile_plan(const FdArgs &a, const LaunchTimes &t, bool disk)
 {
     // ghost rows come from the two rows next to a wall
     if (a.walls && (a.xi < 0.5 || a.stencil != 3)) return TilePlan();
     const TileShape shapes[] = {{1, 1}, {1, 2}, {1, 4}, {2, 4}};
-    const bool f64 = a.dtype == FDLBM_F64, force = a.fx != 0.0 || a.fy != 0.0;
-    double row_us = a.stencil == 1 ? (f64 ? 0.55 : 0.45)
-                                         : (a.stencil == 3 ? (f64 ? 0.9 : 0.65) : (f64 ? 1.3 : 0.85)) + (force ? 0.08 : 0.0);
-    if (a.dtype == FDLBM_F16DEV_SR) row_us += 0.12;  // two hashes per node
     // the disk: the sweep in single steps, and the fill's launch less what the gathers take
-    const double sweep_us = disk ? fd_single_us(a) + 2.0 : fd_fused_us(a);
-    return plan_tiles(a.nx, a.ny, a.stencil == 1 ? 1 : a.stencil == 3 ? 2 : 3, int(compute_bytes(a.dtype)), row_us, shapes,
-                      f64 || disk ? 3 : 4, disk ? 1 : 25, sweep_us);
+    const double sweep_us = disk ? t.one + 2.0 : std::min(t.one, t.most > 1 ? t.fused[t.most] / t.most : t.one);
+    return plan_tiles(fd_tile_cost(a), shapes, a.dtype == FDLBM_F64 || disk ? 3 : 4, disk ? 1 : 25, sweep_us);
 }
 
 hipError_t launch_fd_tile(const FdArgs &a, const TilePlan &p, const TileDisk &disk, const void *src, void *dst,

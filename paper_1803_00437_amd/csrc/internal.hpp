@@ -9,6 +9,7 @@
 #include <vector>
 
 #include "../../include/fdlbm.h"
+#include "launch_plan.hpp"
 
 namespace fdlbm {
 
@@ -49,47 +50,11 @@ size_t fd_reference_scratch_bytes(const FdArgs &a);
 hipError_t launch_fd_sweep(const FdArgs &a, int tile_rows, int lane_cols, const void *src, void *dst, hipStream_t s);
 bool fd_sweep_supported(const FdArgs &a, int lane_cols);
 // FD-LBM and LW-ACM, several steps in one launch: fd_max_fused(a) of them (1: not offered for these
-// arguments).
+// arguments), `rows` rows per wavefront (LaunchTimes).
 int fd_max_fused(const FdArgs &a);
-hipError_t launch_fd_fused(const FdArgs &a, const void *src, void *dst, hipStream_t s);
+LaunchTimes fd_launch_times(const FdArgs &a);
+hipError_t launch_fd_fused(const FdArgs &a, int rows, const void *src, void *dst, hipStream_t s);
 
-// Small and medium grids: a block advances a tile of 64 cols columns by 16 rows rows up to `steps`
-// steps in registers (an odd number: see advance() in abi.cpp).  steps = 0: the sweep kernels.
-struct TilePlan {
-    int cols = 0, rows = 0, steps = 0;
-};
-struct TileShape {
-    int cols, rows;
-};
-// The fastest shape and number of steps for a grid, or the sweep if its estimate `sweep_us` (per
-// step) is less.  A block's launch, loads and stores take 2.5 us and 0.85 us (FP64 1.2) per row and
-// column of a lane; a step takes 0.3 us and row_us per row and column of a lane.  A compute unit gets
-// one block of 256 after the other, two at once where the shape's registers allow.  reach: rows and
-// columns a step loses on each side.  Measured against the estimate (us per step): 64^2 FP64 2.3 (2.4), 256^2 FP32 2.3
-// (2.4), 1024^2 6.7 (7.4), 1001 x 777 5-point 9.0 (9.0), where the sweep takes 4.5, 6.1, 10.2 and 12.
-inline TilePlan plan_tiles(int nx, int ny, int reach, int elem_bytes, double row_us, const TileShape *shapes, int count,
-                           int most, double sweep_us)
-{
-    TilePlan best;
-    double best_us = 0.95 * sweep_us;
-    for (int i = 0; i < count; ++i)
-        for (int steps = 1; steps <= most; steps += 2) {
-            const int cols = 64 * shapes[i].cols - 2 * reach * steps, rows = 16 * shapes[i].rows - 2 * reach * steps;
-            if (cols < 1 || rows < 1) break;
-            const int64_t blocks = (int64_t)((nx + cols - 1) / cols) * ((ny + rows - 1) / rows);
-            const int area = shapes[i].cols * shapes[i].rows;
-            const int64_t each = (blocks + 255) / 256, rounds = area * elem_bytes <= 8 ? (each + 1) / 2 : each;
-            const double start = 2.5 + 0.2 * area * (elem_bytes == 8 ? 6 : 4.25) + 0.3 * steps;
-            const double us = (double(rounds) * start + double(each) * steps * area * row_us) / steps;
-            if (us < best_us) {
-                best_us = us;
-                best.cols = shapes[i].cols;
-                best.rows = shapes[i].rows;
-                best.steps = steps;
-            }
-        }
-    return best;
-}
 // FD-LBM and LW-ACM: the plan (steps = 0 where the tiles do not apply) and a launch of p.steps steps.
 // In the disk, rows describes the grid rows row0 .. row0 + nrows - 1, those with ghost nodes
 // (DiskTable), whose sources and weights are src and w (the table of DiskFill); null elsewhere.
@@ -99,9 +64,8 @@ struct TileDisk {
     const int32_t *src = nullptr;
     const double *w = nullptr;
 };
-TilePlan fd_tile_plan(const FdArgs &a, bool disk);
-double fd_fused_us(const FdArgs &a);
-double fd_single_us(const FdArgs &a);
+TileCost fd_tile_cost(const FdArgs &a);
+TilePlan fd_tile_plan(const FdArgs &a, const LaunchTimes &t, bool disk);
 hipError_t launch_fd_tile(const FdArgs &a, const TilePlan &p, const TileDisk &disk, const void *src, void *dst,
                           hipStream_t s);
 
@@ -214,8 +178,11 @@ hipError_t launch_mrt_disk(const MrtDisk &d, int dtype, void *pop, bool full, hi
 // MRT D2Q9 stream-collide (push) step.
 // `steps` consecutive steps in one launch, 1 .. mrt_max_fused(a)
 int mrt_max_fused(const MrtArgs &a);
-hipError_t launch_mrt(const MrtArgs &a, int steps, const void *src, void *dst, hipStream_t s);
-TilePlan mrt_tile_plan(const MrtArgs &a);
+LaunchTimes mrt_launch_times(const MrtArgs &a);
+// (rows per wavefront for steps > 1: LaunchTimes)
+hipError_t launch_mrt(const MrtArgs &a, int steps, int rows, const void *src, void *dst, hipStream_t s);
+TileCost mrt_tile_cost(const MrtArgs &a);
+TilePlan mrt_tile_plan(const MrtArgs &a, const LaunchTimes &t);
 hipError_t launch_mrt_tile(const MrtArgs &a, const TilePlan &p, const void *src, void *dst, hipStream_t s);
 
 // Conversions between host-staged FP64 planes and device storage: element by element (the

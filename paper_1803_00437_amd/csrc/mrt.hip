@@ -12,6 +12,8 @@
 // between the last fluid row and the next one, section 3-c), or the interpolated
 // bounce-back of Bouzidi et al. for a wall at another distance xi (all kernels agree bit for
 // bit).  Traffic: 9 values read + 9 written per node and launch.
+#include <algorithm>
+
 #include "fd_sweep_body.hpp"
 #include "fdlbm_device.hpp"
 #include "internal.hpp"
@@ -706,12 +708,13 @@ int fused_rows(int strips_x, int ny, int K)
 }
 
 template <typename T, int CPL, int AM, int K, bool WALLS>
-hipError_t run_fused(const MrtArgs &a, MrtCoef<typename Storage<T>::C> k, const void *src, void *dst, hipStream_t s)
+hipError_t run_fused(const MrtArgs &a, MrtCoef<typename Storage<T>::C> k, int fused_rows, const void *src, void *dst, hipStream_t s)
 {
     constexpr int S = MrtStrip<T, CPL, K>::S;
     const int strips_x = (a.nx + S - 1) / S;
     // one step: 1 row per wavefront measured best at 8192^2 (1 % over 2)
-    const int rows = K == 1 ? (a.tile_rows > 0 ? a.tile_rows : 1) : fused_rows(strips_x, a.ny, K);
+    const int rows = K == 1 ? (a.tile_rows > 0 ? a.tile_rows : 1) : fused_rows;
+    if (rows < 1) return hipErrorInvalidValue;
     const int ntiles = strips_x * ((a.ny + rows - 1) / rows);
     const int stride = AM == sweep::AM_SEAM ? sweep::seam_stride(a.nx, S, MrtStrip<T, CPL, K>::P, CPL, sizeof(T)) : S;
     hipLaunchKernelGGL((mrt_fused_kernel<T, CPL, AM, K, WALLS>), (ntiles + 3) / 4, 256, 0, s, static_cast<const T *>(src),
@@ -720,29 +723,29 @@ hipError_t run_fused(const MrtArgs &a, MrtCoef<typename Storage<T>::C> k, const 
 }
 
 template <typename T, int CPL, int K>
-hipError_t run_width(const MrtArgs &a, MrtCoef<typename Storage<T>::C> k, const void *src, void *dst, hipStream_t s)
+hipError_t run_width(const MrtArgs &a, MrtCoef<typename Storage<T>::C> k, int rows, const void *src, void *dst, hipStream_t s)
 {
     using namespace sweep;
     using G = MrtStrip<T, CPL, K>;
     if (a.nx % CPL == 0)
-        return a.walls ? run_fused<T, CPL, AM_VEC, K, true>(a, k, src, dst, s)
-                       : run_fused<T, CPL, AM_VEC, K, false>(a, k, src, dst, s);
+        return a.walls ? run_fused<T, CPL, AM_VEC, K, true>(a, k, rows, src, dst, s)
+                       : run_fused<T, CPL, AM_VEC, K, false>(a, k, rows, src, dst, s);
     // through AM_UNAL's edge branches 6001 x 4097 FP32 takes 247 us per step, 3001^2 FP64 83, here 103 and
     // 74; 1021 x 770 the same
     if (seam_stride(a.nx, G::S, G::P, CPL, sizeof(T)) > 0)
-        return a.walls ? run_fused<T, CPL, AM_SEAM, K, true>(a, k, src, dst, s)
-                       : run_fused<T, CPL, AM_SEAM, K, false>(a, k, src, dst, s);
-    return a.walls ? run_fused<T, CPL, AM_UNAL, K, true>(a, k, src, dst, s)
-                   : run_fused<T, CPL, AM_UNAL, K, false>(a, k, src, dst, s);
+        return a.walls ? run_fused<T, CPL, AM_SEAM, K, true>(a, k, rows, src, dst, s)
+                       : run_fused<T, CPL, AM_SEAM, K, false>(a, k, rows, src, dst, s);
+    return a.walls ? run_fused<T, CPL, AM_UNAL, K, true>(a, k, rows, src, dst, s)
+                   : run_fused<T, CPL, AM_UNAL, K, false>(a, k, rows, src, dst, s);
 }
 
 template <typename T, int CPL>
-hipError_t run_steps(const MrtArgs &a, MrtCoef<typename Storage<T>::C> k, int steps, const void *src, void *dst, hipStream_t s)
+hipError_t run_steps(const MrtArgs &a, MrtCoef<typename Storage<T>::C> k, int steps, int rows, const void *src, void *dst, hipStream_t s)
 {
     switch (steps) {
-    case 1: return run_width<T, CPL, 1>(a, k, src, dst, s);
-    case 3: return run_width<T, CPL, 3>(a, k, src, dst, s);
-    case 5: return run_width<T, CPL, 5>(a, k, src, dst, s);
+    case 1: return run_width<T, CPL, 1>(a, k, rows, src, dst, s);
+    case 3: return run_width<T, CPL, 3>(a, k, rows, src, dst, s);
+    case 5: return run_width<T, CPL, 5>(a, k, rows, src, dst, s);
     default: return hipErrorInvalidValue;
     }
 }
@@ -787,7 +790,7 @@ template <typename T> hipError_t run_tile(const MrtArgs &a, const TilePlan &p, c
     return hipErrorInvalidValue;
 }
 
-template <typename T> hipError_t run(const MrtArgs &a, int steps, const void *src, void *dst, hipStream_t s)
+template <typename T> hipError_t run(const MrtArgs &a, int steps, int rows, const void *src, void *dst, hipStream_t s)
 {
     using C = typename Storage<T>::C;
     MrtCoef<C> k{C(a.s_e), C(a.s_xx), C(a.s_q), C(a.s_eps), C(0.5 * a.fx), C(0.5 * a.fy), C(a.fx), C(a.fy)};
@@ -798,7 +801,7 @@ template <typename T> hipError_t run(const MrtArgs &a, int steps, const void *sr
             if (a.nx % 2 == 0) return run_xi<T, 2>(a, k, src, dst, s);
             return run_xi<T, 1>(a, k, src, dst, s);
         }
-        return run_steps<T, CPL>(a, k, steps, src, dst, s);
+        return run_steps<T, CPL>(a, k, steps, rows, src, dst, s);
     }
     dim3 blk(64, 4), grd((a.nx + 63) / 64, (a.ny + 3) / 4);
     if (a.walls)
@@ -824,23 +827,47 @@ int mrt_max_fused(const MrtArgs &a)
     return 9 * (size_t)a.nx * (size_t)a.ny * dtype_bytes(a.dtype) >= (size_t(80) << 20) ? 5 : 3;
 }
 
-// Time of one step in launches of K = mrt_max_fused(a), in us (see fd_fused_us()); one stage of one
-// row of 64 CPL columns takes 0.9 us in FP32, 0.74 in FP64 (512^2, 1024^2, 2048^2).
-static double mrt_fused_us(const MrtArgs &a)
+// Times of a launch (as in fd_launch_times()).  One step is bound by the state's bytes at 6 TB/s, on narrow
+// grids by the wavefronts, one per row and strip.  K steps: one stage of one row of 64 CPL columns takes
+// 0.9 us in FP32, 0.74 in FP64 (512^2, 1024^2, 2048^2); through AM_UNAL's edge branches 1.6 times as much.
+LaunchTimes mrt_launch_times(const MrtArgs &a)
 {
-    const int K = mrt_max_fused(a), CPL = a.dtype == FDLBM_F64 ? 2 : 4;
-    const int P = (K + CPL - 1) / CPL, S = (64 - 2 * P) * CPL, strips = (a.nx + S - 1) / S;
-    const int rows = fused_rows(strips, a.ny, K);
-    const long each = ((long)strips * ((a.ny + rows - 1) / rows) + 1023) / 1024;
-    return 3.0 / K + double(each) * (rows + K - 1) * (a.dtype == FDLBM_F64 ? 0.74 : 0.9);
+    const bool f64 = a.dtype == FDLBM_F64;
+    const int CPL = f64 ? 2 : 4, eb = int(dtype_bytes(a.dtype));
+    const double bytes_us = 18.0 * eb * a.nx * a.ny / 6e6;
+    LaunchTimes t;
+    t.most = mrt_max_fused(a);
+    t.one = 3.0 + std::max(bytes_us, 0.9 / 1024.0 * a.ny * ((a.nx + 62 * CPL - 1) / (62 * CPL)));
+    for (int K = 3; K <= t.most; K += 2) {
+        const int P = (K + CPL - 1) / CPL, S = (64 - 2 * P) * CPL, strips = (a.nx + S - 1) / S;
+        const int rows = fused_rows(strips, a.ny, K);
+        const long each = ((long)strips * ((a.ny + rows - 1) / rows) + 1023) / 1024;
+        double us = (f64 ? 0.74 : 0.9) * (a.walls ? 1.15 : 1.0);
+        if (a.nx % CPL != 0 && sweep::seam_stride(a.nx, S, P, CPL, eb) == 0) us *= 1.6;
+        t.rows[K] = rows;
+        t.fused[K] = 3.0 + std::max(double(K * each) * (rows + K - 1) * us, bytes_us);
+    }
+    return t;
 }
 
-TilePlan mrt_tile_plan(const MrtArgs &a)
+TileCost mrt_tile_cost(const MrtArgs &a)
+{
+    TileCost c;
+    c.nx = a.nx;
+    c.ny = a.ny;
+    c.elem_bytes = int(dtype_bytes(a.dtype));
+    c.lds = size_t(2 * MRT_TW * 6) * 64 * c.elem_bytes;
+    c.row_us = a.dtype == FDLBM_F64 ? 0.9 : 0.7;
+    c.floor_us = 3.0 + 1.1 * 18.0 * c.elem_bytes * a.nx * a.ny / 6e6;
+    return c;
+}
+
+TilePlan mrt_tile_plan(const MrtArgs &a, const LaunchTimes &t)
 {
     if (a.kernel != FDLBM_KERNEL_AUTO || (a.walls && a.xi != 0.5)) return TilePlan();
     const TileShape shapes[] = {{1, 1}, {1, 2}, {1, 4}};
-    const bool f64 = a.dtype == FDLBM_F64;
-    return plan_tiles(a.nx, a.ny, 1, f64 ? 8 : 4, f64 ? 0.9 : 0.7, shapes, f64 ? 2 : 3, 25, mrt_fused_us(a));
+    const double sweep_us = std::min(t.one, t.most > 1 ? t.fused[t.most] / t.most : t.one);
+    return plan_tiles(mrt_tile_cost(a), shapes, a.dtype == FDLBM_F64 ? 2 : 3, 25, sweep_us);
 }
 
 hipError_t launch_mrt_tile(const MrtArgs &a, const TilePlan &p, const void *src, void *dst, hipStream_t s)
@@ -848,9 +875,9 @@ hipError_t launch_mrt_tile(const MrtArgs &a, const TilePlan &p, const void *src,
     return a.dtype == FDLBM_F64 ? run_tile<double>(a, p, src, dst, s) : run_tile<float>(a, p, src, dst, s);
 }
 
-hipError_t launch_mrt(const MrtArgs &a, int steps, const void *src, void *dst, hipStream_t s)
+hipError_t launch_mrt(const MrtArgs &a, int steps, int rows, const void *src, void *dst, hipStream_t s)
 {
-    return a.dtype == FDLBM_F64 ? run<double>(a, steps, src, dst, s) : run<float>(a, steps, src, dst, s);
+    return a.dtype == FDLBM_F64 ? run<double>(a, steps, rows, src, dst, s) : run<float>(a, steps, rows, src, dst, s);
 }
 
 hipError_t launch_mrt_init(int dtype, const double *dr, const double *jx, const double *jy, void *pop, int nx, int ny,
