@@ -1,4 +1,7 @@
-"""Launches of register tiles: what they read between the calls that move a state."""
+"""Launches of register tiles: every compiled shape against the one-step reference kernels, bit for bit,
+and what they read between the calls that move a state."""
+import functools
+
 import numpy as np
 import pytest
 
@@ -41,3 +44,48 @@ def test_disk_steps_read_nothing_that_a_state_transfer_writes(F, scheme, dtype):
     assert all(np.array_equal(a, b) for a, b in zip(got.get_state(), ref.get_state()))
     got.close()
     ref.close()
+
+
+# (kind, dtype, boundary, body force); tests/test_launch_plan.py holds the grids to every shape that a
+# plan can give any of them
+TILE_KINDS = [(k, d, bc, force) for k, dtypes in (("fd3", ("f64", "f32", "f16", "f16sr")),
+                                                  ("fd5", ("f64", "f32", "f16", "f16sr")),
+                                                  ("lwacm", ("f64", "f32", "f16", "f16sr")), ("mrt", ("f64", "f32")))
+              for d in dtypes for bc, force in (("periodic", 0), ("periodic", 1), ("walls", 1), ("disk", 0))
+              if not (k == "lwacm" and (force or bc == "walls")) and not (k == "fd5" and bc == "walls")
+              and not (k == "mrt" and bc == "disk")]
+TILE_GRIDS = [(17, 20), (373, 376), (615, 618), (681, 684), (879, 882), (945, 948), (967, 970)]
+TILE_STEPS = 50
+
+
+@functools.lru_cache(maxsize=None)
+def random_state(nx, ny):
+    return W.random_state(nx, ny, seed=nx, amp=2e-3)
+
+
+@pytest.mark.parametrize("kind,dtype,bc,force", TILE_KINDS)
+def test_every_tile_shape_equals_reference(F, kind, dtype, bc, force):
+    """Calls of TILE_STEPS steps and of a few, on grids whose last tiles are partly filled."""
+    for nx, ny in TILE_GRIDS:
+        kw = dict(scheme=kind if kind in ("lwacm", "mrt") else "fd", dtype=dtype, bc=bc, s_xx=1.3, s_e=1.1)
+        if kind.startswith("fd"):
+            kw["stencil"] = int(kind[2])
+        if kind == "mrt":
+            kw.update(s_eps=1.2, s_q=1.4)
+        if force:
+            kw["force"] = (2e-5, -1e-5)
+        if bc == "disk":
+            kw["disk"] = ((nx - 1) / 2 - 0.2, (ny - 1) / 2 + 0.1, min(nx, ny) / 2 - 3.5)
+        ref = F.FdLbm(nx, ny, kernel="reference", **kw)
+        got = F.FdLbm(nx, ny, **kw)
+        ref.set_state(*random_state(nx, ny))
+        got.set_state(*random_state(nx, ny))
+        for n in (TILE_STEPS, 9):
+            print(f"  {kind} {dtype} {bc} force {force} {nx}x{ny} +{n}", flush=True)
+            ref.step(n)
+            got.step(n)
+            assert all(np.array_equal(a, b) for a, b in zip(got.get_state(), ref.get_state())), (nx, ny, n)
+            if kind == "mrt":
+                assert np.array_equal(got.get_populations(), ref.get_populations()), (nx, ny, n)
+        got.close()
+        ref.close()

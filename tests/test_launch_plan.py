@@ -77,3 +77,18 @@ def test_a_call_takes_the_fastest_kind_of_launch(deal, kind, dtype, walls, force
     d, = deal([(kind, dtype, walls, force, 0, nx, ny, n)])
     got = TILES if d["tiles"] else ONE if d["ones"] == n else FUSED
     assert got == want, d
+
+
+def test_the_gpu_tests_grids_take_every_shape_a_plan_can_give(deal):
+    """The bitwise tests of the tiles (test_gpu_tile_routes.py) have to run every shape that grids up to
+    1450 nodes a side take, whatever the constants of the plan."""
+    from test_gpu_tile_routes import TILE_GRIDS, TILE_KINDS, TILE_STEPS
+
+    sizes = [(s, s + t) for s in list(range(16, 64, 6)) + list(range(64, 1450, 14)) for t in (0, 3)]
+    sizes += [(1001, 777), (1021, 770), (500, 2000), (20000, 16), (16, 20000), (8, 3000), (3000, 8)]
+    for k, d, bc, force in TILE_KINDS:
+        def shapes(grids):
+            calls = [(k, d, bc == "walls", force, bc == "disk", nx, ny, TILE_STEPS) for nx, ny in grids]
+            return {(r["cols"], r["rows"]) for r in deal(calls) if r["tiles"]}
+
+        assert shapes(TILE_GRIDS) == shapes(sizes + TILE_GRIDS), (k, d, bc, force)
