@@ -37,7 +37,7 @@ struct TilePlan {
     int cols = 0, rows = 0, steps = 0;
 };
 
-// Time of a launch of tiles.  A block's launch, loads and stores take 2.5 us and 0.85 us (FP64 1.2)
+// Time of a launch of tiles.  A block's launch, loads and stores take start_us and 0.85 us (FP64 1.2)
 // per row and column of a lane; a step takes 0.3 us and row_us per row and column of a lane.  A compute
 // unit gets one block of 256 after the other, two at once where the shape's registers and its LDS
 // (lds bytes per column of a lane, of 160 KB) allow: FP64 with 5-point differences or walls takes one.
@@ -47,7 +47,7 @@ struct TilePlan {
 struct TileCost {
     int nx = 0, ny = 0, reach = 1, elem_bytes = 4;
     size_t lds = 0;
-    double row_us = 1.0, floor_us = 0.0;
+    double row_us = 1.0, start_us = 2.5, floor_us = 0.0;
     // of `steps` steps; negative: the halo leaves nothing to store
     double us(TileShape s, int steps) const
     {
@@ -57,7 +57,7 @@ struct TileCost {
         const int area = s.cols * s.rows;
         const bool two = area * elem_bytes <= 8 && 2 * lds * s.cols <= 160 * 1024;
         const int64_t each = (blocks + 255) / 256, rounds = two ? (each + 1) / 2 : each;
-        const double start = 2.5 + 0.2 * area * (elem_bytes == 8 ? 6 : 4.25) + 0.3 * steps;
+        const double start = start_us + 0.2 * area * (elem_bytes == 8 ? 6 : 4.25) + 0.3 * steps;
         return std::max(floor_us, double(rounds) * start + double(each) * steps * area * row_us);
     }
 };

@@ -476,10 +476,21 @@ __global__ void __launch_bounds__(256, K > 1 ? 2 : 1) mrt_fused_kernel(const T *
 #pragma unroll
                 for (int q = 0; q < 9; ++q) f[q][c] = p[q];
             }
-            // populations returning from a wall, unshifted
+            // populations returning from a wall, unshifted: stored at once by the last stage
             C b[3][CPL];
             const bool bottom = WALLS && y == 0, top = WALLS && y == ny - 1;
-            if (bottom || top)
+            if (s == K - 1) {
+                if (top) {
+                    put(4, y, f[2]);
+                    put(7, y, f[5]);
+                    put(8, y, f[6]);
+                }
+                if (bottom) {
+                    put(2, y, f[4]);
+                    put(5, y, f[7]);
+                    put(6, y, f[8]);
+                }
+            } else if (bottom || top)
 #pragma unroll
                 for (int c = 0; c < CPL; ++c) {
                     b[0][c] = bottom ? f[4][c] : f[2][c];
@@ -525,21 +536,13 @@ __global__ void __launch_bounds__(256, K > 1 ? 2 : 1) mrt_fused_kernel(const T *
                 put(0, y, f[0]);
                 put(1, y, f[1]);
                 put(3, y, f[3]);
-                if (top) {
-                    put(4, y, b[0]);
-                    put(7, y, b[1]);
-                    put(8, y, b[2]);
-                } else {
+                if (!top) {
                     const int yp = !WALLS && y + 1 == ny ? 0 : y + 1;
                     put(2, yp, f[2]);
                     put(5, yp, f[5]);
                     put(6, yp, f[6]);
                 }
-                if (bottom) {
-                    put(2, y, b[0]);
-                    put(5, y, b[1]);
-                    put(6, y, b[2]);
-                } else {
+                if (!bottom) {
                     const int ym = !WALLS && y == 0 ? ny - 1 : y - 1;
                     put(4, ym, f[4]);
                     put(7, ym, f[7]);
@@ -730,13 +733,28 @@ hipError_t run_width(const MrtArgs &a, MrtCoef<typename Storage<T>::C> k, int ro
     if (a.nx % CPL == 0)
         return a.walls ? run_fused<T, CPL, AM_VEC, K, true>(a, k, rows, src, dst, s)
                        : run_fused<T, CPL, AM_VEC, K, false>(a, k, rows, src, dst, s);
-    // through AM_UNAL's edge branches 6001 x 4097 FP32 takes 247 us per step, 3001^2 FP64 83, here 103 and
-    // 74; 1021 x 770 the same
-    if (seam_stride(a.nx, G::S, G::P, CPL, sizeof(T)) > 0)
+    // other widths: element-aligned accesses (through AM_UNAL's edge branches 6001 x 4097 FP32 takes 247 us
+    // per step, 3001^2 FP64 83, here 103 and 74; 1021 x 770 the same), but single steps of a state that the
+    // last-level cache holds take aligned accesses of fewer columns (FP32 1021 x 770 14.2 us and 12.7,
+    // 191^2 6.3 and 3.6; 6001 x 4097 356 and 371)
+    const bool seam = seam_stride(a.nx, G::S, G::P, CPL, sizeof(T)) > 0;
+    if constexpr (K == 1) {
+        if (!seam || 9 * sizeof(T) * (size_t)a.nx * (size_t)a.ny < (size_t(256) << 20)) {
+            if constexpr (CPL > 2)
+                if (a.nx % 2 == 0)
+                    return a.walls ? run_fused<T, 2, AM_VEC, 1, true>(a, k, rows, src, dst, s)
+                                   : run_fused<T, 2, AM_VEC, 1, false>(a, k, rows, src, dst, s);
+            return a.walls ? run_fused<T, 1, AM_VEC, 1, true>(a, k, rows, src, dst, s)
+                           : run_fused<T, 1, AM_VEC, 1, false>(a, k, rows, src, dst, s);
+        }
+    }
+    if (seam)
         return a.walls ? run_fused<T, CPL, AM_SEAM, K, true>(a, k, rows, src, dst, s)
                        : run_fused<T, CPL, AM_SEAM, K, false>(a, k, rows, src, dst, s);
-    return a.walls ? run_fused<T, CPL, AM_UNAL, K, true>(a, k, rows, src, dst, s)
-                   : run_fused<T, CPL, AM_UNAL, K, false>(a, k, rows, src, dst, s);
+    if constexpr (K > 1)
+        return a.walls ? run_fused<T, CPL, AM_UNAL, K, true>(a, k, rows, src, dst, s)
+                       : run_fused<T, CPL, AM_UNAL, K, false>(a, k, rows, src, dst, s);
+    return hipErrorInvalidValue;
 }
 
 template <typename T, int CPL>
@@ -829,7 +847,7 @@ int mrt_max_fused(const MrtArgs &a)
 
 // Times of a launch (as in fd_launch_times()).  One step is bound by the state's bytes at 6 TB/s, on narrow
 // grids by the wavefronts, one per row and strip.  K steps: one stage of one row of 64 CPL columns takes
-// 0.9 us in FP32, 0.74 in FP64 (512^2, 1024^2, 2048^2); through AM_UNAL's edge branches 1.6 times as much.
+// 0.9 us in FP32, 0.74 in FP64 (512^2, 1024^2, 2048^2); through AM_UNAL's edge branches twice as much.
 LaunchTimes mrt_launch_times(const MrtArgs &a)
 {
     const bool f64 = a.dtype == FDLBM_F64;
@@ -843,7 +861,7 @@ LaunchTimes mrt_launch_times(const MrtArgs &a)
         const int rows = fused_rows(strips, a.ny, K);
         const long each = ((long)strips * ((a.ny + rows - 1) / rows) + 1023) / 1024;
         double us = (f64 ? 0.74 : 0.9) * (a.walls ? 1.15 : 1.0);
-        if (a.nx % CPL != 0 && sweep::seam_stride(a.nx, S, P, CPL, eb) == 0) us *= 1.6;
+        if (a.nx % CPL != 0 && sweep::seam_stride(a.nx, S, P, CPL, eb) == 0) us *= 2.0;
         t.rows[K] = rows;
         t.fused[K] = 3.0 + std::max(double(K * each) * (rows + K - 1) * us, bytes_us);
     }
@@ -858,6 +876,7 @@ TileCost mrt_tile_cost(const MrtArgs &a)
     c.elem_bytes = int(dtype_bytes(a.dtype));
     c.lds = size_t(2 * MRT_TW * 6) * 64 * c.elem_bytes;
     c.row_us = a.dtype == FDLBM_F64 ? 0.9 : 0.7;
+    c.start_us = 2.8;
     c.floor_us = 3.0 + 1.1 * 18.0 * c.elem_bytes * a.nx * a.ny / 6e6;
     return c;
 }
