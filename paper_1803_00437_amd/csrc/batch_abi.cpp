@@ -42,7 +42,8 @@ struct Plan {
     std::vector<BatchInstance> inst;
     std::vector<BatchBlock> blocks;
     std::vector<BatchChunk> chunks;
-    std::vector<BatchWave> waves[BATCH_FUSED];
+    std::vector<BatchWave> waves[BATCH_FUSED];  // built for a context only (nwaves counts them always)
+    size_t nwaves[BATCH_FUSED] = {};
     int class_begin[BATCH_CLASSES] = {}, class_blocks[BATCH_CLASSES] = {};
     size_t state_elems = 0, mode_elems = 0, max_n = 0;
     // scratch offsets (bytes)
@@ -100,43 +101,64 @@ void tile_tables(Plan &P, int rows)
     }
 }
 
-// The wavefronts of the launch that takes `steps` steps.  Rows per wavefront: a wavefront of R rows
-// forms R + 2 + 2 (steps - 1) per step, and the launch ends with the last wavefront, so the work per
-// SIMD plus one wavefront's own is least; an instance's rows are dealt evenly to its bands, and
-// the tallest wavefronts start first.
-void wave_table(Plan &P, int dtype, int steps)
+// The wavefronts of the launch that takes `steps` steps, and their number; the table itself only
+// if `build`.  Rows per wavefront: a wavefront of R rows forms R + 2 + 2 (steps - 1) per
+// step, and the launch ends with the last wavefront, so the work per SIMD plus one wavefront's own is
+// least; an instance's rows are dealt evenly to its bands, and the tallest wavefronts start first.
+void wave_table(Plan &P, int dtype, int steps, bool build)
 {
     const int extra = 2 * steps;
-    std::vector<BatchStrips> strips;
-    for (const BatchInstance &I : P.inst) strips.push_back(batch_strips(I.nx, dtype, steps));
+    struct Part {
+        BatchStrips s;
+        double weight;
+        int ny;
+    };
+    std::vector<Part> parts;
+    parts.reserve(P.inst.size());
+    for (const BatchInstance &I : P.inst) {
+        const BatchStrips s = batch_strips(I.nx, dtype, steps);
+        parts.push_back(Part{s, s.count * (0.4 + 0.6 * s.cols / 2), I.ny});
+    }
     int best = 8;
-    double best_cost = -1.0;
+    double best_cost = -1.0, least = 0.0;
+    for (const Part &p : parts) least += p.weight * p.ny;
     for (int rows = 4; rows <= 128; rows += rows < 32 ? 2 : 8) {
+        if (best_cost >= 0.0 && least / 1024.0 + (rows + extra) >= best_cost) break;  // no taller one is better
         double work = 0.0;
-        for (size_t i = 0; i < P.inst.size(); ++i) {
-            const double bands = (P.inst[i].ny + rows - 1) / rows;
-            work += strips[i].count * (0.4 + 0.6 * strips[i].cols / 2) * (P.inst[i].ny + bands * extra);
-        }
+        for (const Part &p : parts) work += p.weight * (p.ny + (p.ny + rows - 1) / rows * extra);
         const double cost = work / 1024.0 + (rows + extra);
         if (best_cost < 0.0 || cost < best_cost) {
             best_cost = cost;
             best = rows;
         }
     }
-    std::vector<BatchWave> &W = P.waves[steps - BATCH_FUSED_MIN];
-    W.clear();
-    for (size_t i = 0; i < P.inst.size(); ++i) {
-        const int ny = P.inst[i].ny, bands = (ny + best - 1) / best;
-        for (int b = 0; b < bands; ++b) {
-            const int y0 = (int)((int64_t)ny * b / bands), y1 = (int)((int64_t)ny * (b + 1) / bands);
-            for (int t = 0; t < strips[i].count; ++t)
-                W.push_back(BatchWave{(int)i, t == strips[i].count - 1 ? strips[i].last : t * strips[i].stride, y0,
-                                      (short)(y1 - y0), (short)strips[i].cols});
+    size_t n = 0;
+    for (const Part &p : parts) n += (size_t)((p.ny + best - 1) / best) * p.s.count;
+    P.nwaves[steps - BATCH_FUSED_MIN] = n;
+    if (!build) return;
+    struct Band {
+        int instance, y0, rows;
+    };
+    std::vector<Band> bands;
+    for (size_t i = 0; i < parts.size(); ++i) {
+        const int ny = parts[i].ny, count = (ny + best - 1) / best;
+        for (int b = 0; b < count; ++b) {
+            const int y0 = (int)((int64_t)ny * b / count), y1 = (int)((int64_t)ny * (b + 1) / count);
+            bands.push_back(Band{(int)i, y0, y1 - y0});
         }
     }
-    std::stable_sort(W.begin(), W.end(), [](const BatchWave &a, const BatchWave &b) {
-        return a.cols != b.cols ? a.cols > b.cols : a.rows > b.rows;
+    std::stable_sort(bands.begin(), bands.end(), [&](const Band &a, const Band &b) {
+        const int ca = parts[a.instance].s.cols, cb = parts[b.instance].s.cols;
+        return ca != cb ? ca > cb : a.rows > b.rows;
     });
+    std::vector<BatchWave> &W = P.waves[steps - BATCH_FUSED_MIN];
+    W.clear();
+    W.reserve(n);
+    for (const Band &b : bands) {
+        const BatchStrips &s = parts[b.instance].s;
+        for (int t = 0; t < s.count; ++t)
+            W.push_back(BatchWave{b.instance, t == s.count - 1 ? s.last : t * s.stride, b.y0, (short)b.rows, (short)s.cols});
+    }
 }
 
 // Point a launch description at the block table the plan holds.
@@ -150,7 +172,7 @@ void use_tables(BatchLaunch &L, const Plan &P, int rows)
     }
 }
 
-Plan plan(const fdlbm_instance *in, int32_t count, int32_t dtype, int32_t max_samples)
+Plan plan(const fdlbm_instance *in, int32_t count, int32_t dtype, int32_t max_samples, bool build)
 {
     Plan P;
     P.inst.resize(count);
@@ -180,7 +202,7 @@ Plan plan(const fdlbm_instance *in, int32_t count, int32_t dtype, int32_t max_sa
     tile_tables(P, BATCH_MIN_ROWS);
     const size_t max_blocks = P.blocks.size();
     tile_tables(P, BATCH_ROWS);
-    for (int k = BATCH_FUSED_MIN; k <= BATCH_FUSED_MAX; ++k) wave_table(P, dtype, k);
+    for (int k = BATCH_FUSED_MIN; k <= BATCH_FUSED_MAX; ++k) wave_table(P, dtype, k, build);
     size_t off = 0;
     auto take = [&](size_t bytes) {
         const size_t o = off;
@@ -189,7 +211,7 @@ Plan plan(const fdlbm_instance *in, int32_t count, int32_t dtype, int32_t max_sa
     };
     P.o_inst = take(sizeof(BatchInstance) * P.inst.size());
     P.o_chunks = take(sizeof(BatchChunk) * P.chunks.size());
-    for (int q = 0; q < BATCH_FUSED; ++q) P.o_waves[q] = take(sizeof(BatchWave) * P.waves[q].size());
+    for (int q = 0; q < BATCH_FUSED; ++q) P.o_waves[q] = take(sizeof(BatchWave) * P.nwaves[q]);
     P.o_blocks = take(sizeof(BatchBlock) * max_blocks);
     P.o_partials = take(2 * sizeof(double) * P.chunks.size());
     P.o_counter = take(sizeof(int));
@@ -271,7 +293,7 @@ int fdlbm_batch_workspace_bytes(const fdlbm_instance *instances, int32_t count, 
     return guarded([&]() -> int {
         int rc = validate(instances, count, dtype, max_samples);
         if (rc) return rc;
-        Plan P = plan(instances, count, dtype, max_samples);
+        Plan P = plan(instances, count, dtype, max_samples, false);
         if (state_bytes) *state_bytes = al256(P.state_elems * dtype_bytes(dtype));
         if (scratch_bytes) *scratch_bytes = P.total;
         return FDLBM_OK;
@@ -289,7 +311,7 @@ int fdlbm_batch_create(const fdlbm_instance *instances, int32_t count, int32_t d
         if (((uintptr_t)state_a | (uintptr_t)state_b | (uintptr_t)scratch) & 255) return FDLBM_EINVAL;
         fdlbm_batch *b = new (std::nothrow) fdlbm_batch;
         if (!b) return FDLBM_ENOMEM;
-        b->P = plan(instances, count, dtype, max_samples);
+        b->P = plan(instances, count, dtype, max_samples, true);
         if (scratch_bytes < b->P.total) {
             delete b;
             return FDLBM_ENOMEM;
