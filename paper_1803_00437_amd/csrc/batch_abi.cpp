@@ -44,6 +44,7 @@ struct Plan {
     std::vector<BatchChunk> chunks;
     std::vector<BatchWave> waves[BATCH_FUSED];  // built for a context only (nwaves counts them always)
     size_t nwaves[BATCH_FUSED] = {};
+    LaunchTimes times;
     int class_begin[BATCH_CLASSES] = {}, class_blocks[BATCH_CLASSES] = {};
     size_t state_elems = 0, mode_elems = 0, max_n = 0;
     // scratch offsets (bytes)
@@ -101,8 +102,8 @@ void tile_tables(Plan &P, int rows)
     }
 }
 
-// The wavefronts of the launch that takes `steps` steps, and their number; the table itself only
-// if `build`.  Rows per wavefront: a wavefront of R rows forms R + 2 + 2 (steps - 1) per
+// The wavefronts of the launch that takes `steps` steps, their number and the launch's time; the table
+// itself only if `build`.  Rows per wavefront: a wavefront of R rows forms R + 2 + 2 (steps - 1) per
 // step, and the launch ends with the last wavefront, so the work per SIMD plus one wavefront's own is
 // least; an instance's rows are dealt evenly to its bands, and the tallest wavefronts start first.
 void wave_table(Plan &P, int dtype, int steps, bool build)
@@ -132,8 +133,19 @@ void wave_table(Plan &P, int dtype, int steps, bool build)
             best = rows;
         }
     }
+    // time: a row of a wavefront takes `us` through all its stages, one column per lane about half
     size_t n = 0;
-    for (const Part &p : parts) n += (size_t)((p.ny + best - 1) / best) * p.s.count;
+    double work = 0.0, full = 0.0;
+    for (const Part &p : parts) {
+        const int bands = (p.ny + best - 1) / best;
+        const size_t w = (size_t)bands * p.s.count;
+        n += w;
+        work += (p.s.cols == 2 ? 1.0 : 0.5) * p.s.count * (p.ny + (double)bands * extra);
+        full += (p.s.cols == 2 ? 1.0 : steps == 3 ? 0.5 : 0.6) * (double)w;
+    }
+    const double us = dtype == FDLBM_F64 ? (steps == 3 ? 1.5 : 1.1) : dtype == FDLBM_F32 ? (steps == 3 ? 0.94 : 0.63)
+                                                                                        : (steps == 3 ? 1.02 : 0.66);
+    P.times.fused[steps] = 5.0 + us * ((best + extra) * full / (double)n + (n > 1024 ? work / 1024.0 : 0.0));
     P.nwaves[steps - BATCH_FUSED_MIN] = n;
     if (!build) return;
     struct Band {
@@ -159,6 +171,21 @@ void wave_table(Plan &P, int dtype, int steps, bool build)
         for (int t = 0; t < s.count; ++t)
             W.push_back(BatchWave{b.instance, t == s.count - 1 ? s.last : t * s.stride, b.y0, (short)b.rows, (short)s.cols});
     }
+}
+
+// Time of a launch of one step: in FP64 bound by memory; else by the rows of each lane class, where a
+// strip that is partly filled takes less.
+double one_step_us(const Plan &P, int dtype)
+{
+    double bytes = 0.0, us = 0.0;
+    for (const BatchInstance &I : P.inst) {
+        bytes += 48.0 * I.nx * I.ny;
+        const int S = batch_strip_stride(batch_class_cpl(I.cls, dtype));
+        const double fill = double(I.nx) / ((double)I.strips_x * S);
+        us += (I.cls == 2 ? 0.75 : dtype == FDLBM_F32 ? 0.62 : 0.5) * (0.5 + 0.5 * fill) * I.strips_x *
+              (I.ny + 4.0 * ((I.ny + 7) / 8)) / 1024.0;
+    }
+    return dtype == FDLBM_F64 ? 7.0 + bytes / 5.4e6 : 8.0 + us;
 }
 
 // Point a launch description at the block table the plan holds.
@@ -203,6 +230,8 @@ Plan plan(const fdlbm_instance *in, int32_t count, int32_t dtype, int32_t max_sa
     const size_t max_blocks = P.blocks.size();
     tile_tables(P, BATCH_ROWS);
     for (int k = BATCH_FUSED_MIN; k <= BATCH_FUSED_MAX; ++k) wave_table(P, dtype, k, build);
+    P.times.most = BATCH_FUSED_MAX;
+    P.times.one = one_step_us(P, dtype);
     size_t off = 0;
     auto take = [&](size_t bytes) {
         const size_t o = off;
@@ -256,28 +285,16 @@ template <typename Body> int guarded(Body &&body)
     }
 }
 
-// Steps in launches of three, two and one.  Every launch changes the buffer, so with twos in pairs
-// the current buffer is that of as many single steps.
-int launch_chunk(fdlbm_batch *b, int steps, bool sample)
+int launch_chunk(fdlbm_batch *b, int64_t steps, bool sample)
 {
-    int threes = steps / 3, twos = 0;
-    const int rest = steps % 3;
-    if (rest == 1 && threes >= 1) {
-        threes -= 1;
-        twos = 2;
-    } else if (rest == 2 && threes >= 1) {
-        twos = threes >= 2 ? 4 : 2;
-        threes -= threes >= 2 ? 2 : 1;
-    }
-    for (int left = steps; left > 0;) {
-        const int k = threes > 0 ? 3 : twos > 0 ? 2 : 1;
-        (k == 3 ? threes : twos) -= k > 1;
+    const Deal d = deal_batch(steps, b->P.times);
+    for (int64_t i = 0; i < d.count(); ++i) {
+        const int k = d.steps(i);
         const void *src = b->buf[b->cur];
         void *dst = b->buf[b->cur ^ 1];
         BHIPCHK(k > 1 ? launch_batch_fused(b->L, k, src, dst, b->stream) : launch_batch_step(b->L, src, dst, b->stream),
                 "batch step launch");
         b->cur ^= 1;
-        left -= k;
     }
     if (sample) BHIPCHK(launch_batch_sample(b->L, b->buf[b->cur], b->stream), "batch sample launch");
     return FDLBM_OK;
@@ -470,7 +487,7 @@ int fdlbm_batch_step(fdlbm_batch *b, int64_t nsteps, int32_t sample_every, int32
         if (use_graph && (sample_every == 0 || !b->stream)) return FDLBM_EINVAL;  // capture needs a non-default stream
         BHIPCHK(hipSetDevice(b->device), "hipSetDevice");
         if (sample_every == 0) {
-            int rc = launch_chunk(b, (int)nsteps, false);
+            int rc = launch_chunk(b, nsteps, false);
             if (rc) return rc;
             b->steps += nsteps;
             return FDLBM_OK;

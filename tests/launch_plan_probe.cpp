@@ -1,5 +1,6 @@
 // Prints how steps are dealt to launches, for tests/test_launch_plan.py: per line of input
 //   stencil (9: MRT) dtype walls force disk nx ny n
+//   0 and the times of a batch's launches of one, two and three steps, 0 0 0, n
 // one line: tile columns, rows and steps, then the launches of n steps: tiles, fives, threes, twos, ones,
 // and the steps and launches they add up to.
 #include <cstdio>
@@ -17,7 +18,12 @@ int main()
         LaunchTimes t;
         TilePlan p;
         TileCost c;
-        if (st == 9) {
+        Deal d;
+        if (st == 0) {
+            t.one = dt;
+            t.fused[2] = walls;
+            t.fused[3] = force;
+        } else if (st == 9) {
             const MrtArgs a{nx, ny, walls, dt, 1.1, 1.5, 1.2, 1.3, f, 0.0, FDLBM_KERNEL_AUTO, 0, 0.5};
             t = mrt_launch_times(a);
             c = mrt_tile_cost(a);
@@ -29,7 +35,7 @@ int main()
             p = fd_tile_plan(a, t, disk != 0);
         }
         if (disk) t.most = 1;
-        const Deal d = disk && p.steps > 0 ? deal_tiles(n, 1) : deal(n, t, p, c);
+        d = st == 0 ? deal_batch(n, t) : disk && p.steps > 0 ? deal_tiles(n, 1) : deal(n, t, p, c);
         long long sum = 0;
         for (int64_t i = 0; i < d.count(); ++i) sum += d.steps(i);
         std::printf("%d %d %d %lld %lld %lld %lld %lld %lld %lld\n", p.cols, p.rows, p.steps, (long long)d.tiles,

@@ -23,7 +23,7 @@ def deal(tmp_path_factory):
                     f"-Wl,-rpath,{B.OUT_DIR}", "-Wl,--allow-shlib-undefined"], check=True)
 
     def run(calls):
-        text = "\n".join(" ".join(map(str, (STENCIL[k], F.DTYPE[d], int(w), int(f), int(disk), nx, ny, n)))
+        text = "\n".join(" ".join(map(str, (STENCIL.get(k, k), F.DTYPE.get(d, d), int(w), int(f), int(disk), nx, ny, n)))
                          for k, d, w, f, disk, nx, ny, n in calls)
         out = subprocess.run([exe], input=text, capture_output=True, text=True, check=True).stdout.split("\n")
         keys = ("cols", "rows", "steps", "tiles", "fives", "threes", "twos", "ones", "sum", "count")
@@ -42,6 +42,23 @@ def test_every_deal_adds_up_and_keeps_the_buffer(deal, kind, dtype, nx, ny):
     ns = list(range(1, 300)) + [997, 1000, 65536, 10 ** 6 + 1]
     for n, d in zip(ns, deal([(kind, dtype, 0, 0, 0, nx, ny, n) for n in ns])):
         assert d["sum"] == n and d["count"] % 2 == n % 2, (n, d)
+
+
+@pytest.mark.parametrize("one,two,three,want", [
+    (46, 74, 119, "twos"),     # FP32 8 x 1024^2: 37 us per step, in threes 39.7
+    (10, 10, 15, "threes"),    # FP32 4 x 64^2: as fast in twos, and fewer launches
+    (37, 78, 129, "ones"),     # FP16 8 x 1024^2: the one-step kernel takes four columns per lane
+    (24, 35, 52, "threes"),    # FP16, odd widths
+    (24, 35, 70, "twos"),
+    (19, 34, 63, "twos")])     # FP32, 30 grids of 32 to 496 columns
+def test_a_batch_takes_the_fastest_deal(deal, one, two, three, want):
+    """Times in us of launches of one, two and three steps of all instances."""
+    ns = list(range(1, 300)) + [10 ** 6 + 1]
+    deals = deal([(0, one, two, three, 0, 0, 0, n) for n in ns])
+    for n, d in zip(ns, deals):
+        assert d["sum"] == n and d["count"] % 2 == n % 2, (n, d)
+    d = deals[95]  # 96 steps: a multiple of three and of four
+    assert d[want] == 96 // {"ones": 1, "twos": 2, "threes": 3}[want], d
 
 
 # us per step, measured: (n, single steps, steps together in the sweep, tiles as planned); the launch
