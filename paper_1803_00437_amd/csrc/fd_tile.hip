@@ -79,14 +79,15 @@ __global__ void __launch_bounds__(64 * TW) fd_tile_kernel(TileStepArgs<T> a)
         }
 #pragma unroll
         for (int c = 0; c < CPL; ++c) {
-            const int x = (int)col[c];
-            if (!DISK || (x >= glo && x <= ghi)) {
+            // every lane loads its node while the row's numbers are on their way
 #pragma unroll
-                for (int f = 0; f < 3; ++f) v[i][f][c] = Storage<T>::load(row[(size_t)f * nx + col[c]]);
-            } else if (x < ga || x > gb) {
+            for (int f = 0; f < 3; ++f) v[i][f][c] = Storage<T>::load(row[(size_t)f * nx + col[c]]);
+            if constexpr (!DISK) continue;
+            const int x = (int)col[c];
+            if (x < ga || x > gb) {
 #pragma unroll
                 for (int f = 0; f < 3; ++f) v[i][f][c] = C(0);
-            } else {
+            } else if (x < glo || x > ghi) {
                 const int g = g0 + (x < glo ? x - ga : (glo - ga) + (x - ghi - 1));
                 const unsigned src = (unsigned)a.disk.src[g], sy = src / (unsigned)nx, sx = src - sy * (unsigned)nx;
                 const C wx = C(a.disk.w[3 * g]), wy = C(a.disk.w[3 * g + 1]), sj = C(a.disk.w[3 * g + 2]);
