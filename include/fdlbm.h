@@ -21,8 +21,9 @@
  *   - Velocity order of the populations (section 1): e_0 = (0,0), e_1..e_4 = (1,0), (0,1),
  *     (-1,0), (0,-1), e_5..e_8 = (1,1), (-1,1), (-1,-1), (1,-1).
  *   - Device buffers are owned by the caller (allocated e.g. by PyTorch) and must stay
- *     valid until fdlbm_destroy.  The library never allocates or frees device memory (it holds
- *     one page of pinned host memory while contexts that read their diagnostics often exist).
+ *     valid until fdlbm_destroy.  The library never allocates or frees device memory (from a
+ *     process's twentieth read of diagnostics on it holds one page of pinned host memory, 4 KB,
+ *     until the process ends).
  *   - A step call of several steps may take some of them together in one launch; the state
  *     after it, its buffer and its bits are those of as many single steps.
  *   - All work is issued on the HIP stream given at creation (NULL = the default stream).

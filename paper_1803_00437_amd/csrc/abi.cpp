@@ -6,10 +6,10 @@
 #include <vector>
 #include <cstdio>
 #include <cstring>
-#include <mutex>
 #include <new>
 
 #include "fdlbm_device.hpp"
+#include "host_slots.hpp"
 #include "internal.hpp"
 
 using namespace fdlbm;
@@ -198,53 +198,21 @@ Layout layout(const fdlbm_params &p)
     return L;
 }
 
-// Pinned host memory that the diagnostics of a context are written to: slots of one page, which is
-// allocated for the first context that wants one, shared by the next ones and freed with the last.
-// Contexts beyond its slots, or all if it cannot be had, get null.  A slot saves 13 us a read and the
-// page takes 100 .. 250 us, so a context asks for one with its HOST_READS-th read: programs that
-// look at their state a few times do without.
-constexpr int HOST_READS = 4;
-constexpr int HOST_SLOTS = 64;
-std::mutex host_mu;
-double *host_page = nullptr;
-uint64_t host_used = 0;  // one bit per slot
-
-// Another thread may be recording a stream: allocating and freeing here are no part of its graph.
+// Another thread may be recording a stream: allocating here is no part of its graph.
 struct RelaxedCapture {
     hipStreamCaptureMode mode = hipStreamCaptureModeRelaxed;
     RelaxedCapture() { (void)hipThreadExchangeStreamCaptureMode(&mode); }
     ~RelaxedCapture() { (void)hipThreadExchangeStreamCaptureMode(&mode); }
 };
-
-double *host_slot_take()
+double *pinned_page(size_t bytes)
 {
-    std::lock_guard<std::mutex> lock(host_mu);
-    if (host_used == ~uint64_t(0)) return nullptr;
-    if (!host_page) {
-        void *p = nullptr;
-        RelaxedCapture relaxed;
-        if (hipHostMalloc(&p, HOST_SLOTS * DIAG_SLOTS * sizeof(double), hipHostMallocPortable) != hipSuccess) {
-            (void)hipGetLastError();
-            return nullptr;
-        }
-        host_page = static_cast<double *>(p);
-    }
-    const int i = __builtin_ctzll(~host_used);
-    host_used |= uint64_t(1) << i;
-    return host_page + (size_t)i * DIAG_SLOTS;
+    void *p = nullptr;
+    RelaxedCapture relaxed;
+    if (hipHostMalloc(&p, bytes, hipHostMallocPortable) == hipSuccess) return static_cast<double *>(p);
+    (void)hipGetLastError();
+    return nullptr;
 }
-
-void host_slot_give(double *slot)
-{
-    if (!slot) return;
-    std::lock_guard<std::mutex> lock(host_mu);
-    host_used &= ~(uint64_t(1) << ((slot - host_page) / DIAG_SLOTS));
-    if (host_used == 0) {
-        RelaxedCapture relaxed;
-        (void)hipHostFree(host_page);
-        host_page = nullptr;
-    }
-}
+HostSlots host_slots(DIAG_SLOTS, pinned_page);
 
 // Runs an entry point's body so that no C++ exception crosses the C ABI: host allocation
 // failure (std::bad_alloc from the tables) becomes FDLBM_ENOMEM, anything else FDLBM_EINVAL.
@@ -276,7 +244,6 @@ struct fdlbm_ctx {
     MrtDisk mdisk;   // FDLBM_BC_DISK, MRT: the boundary-link table in the scratch buffer
     bool disk_full;  // the next fill sets every rest node to rest (the state was just set)
     double *host = nullptr;  // pinned: DIAG_SLOTS values of the diagnostics (null: copied instead)
-    int reads = 0;           // of the diagnostics, up to HOST_READS
     StepPlan plan;   // how steps are dealt to launches
     TileDisk tdisk;  // FDLBM_BC_DISK: the tiles' view of the ghost-node table
 
@@ -402,7 +369,7 @@ int fdlbm_create(const fdlbm_params *p, void *state_a, void *state_b, void *scra
 
 void fdlbm_destroy(fdlbm_ctx *c)
 {
-    if (c) host_slot_give(c->host);
+    if (c) host_slots.give(c->host);
     delete c;
 }
 
@@ -484,7 +451,7 @@ static int run_diag(fdlbm_ctx *c, double out[DIAG_SLOTS])
     const double *m = c->mode_set ? c->sd(c->L.mode) : nullptr;
     // the last kernel writes its few numbers to pinned host memory: a copy would be one more
     // operation on the stream, staged through a buffer of the runtime
-    if (c->reads < HOST_READS && ++c->reads == HOST_READS) c->host = host_slot_take();
+    if (!c->host) c->host = host_slots.take();
     double *to = c->host ? c->host : c->sd(c->L.out);
     HIPCHK(launch_diag(c->p.scheme, c->p.dtype, c->buf[c->cur], c->p.nx, c->p.ny, m, m ? m + n : nullptr,
                        c->sd(c->L.partials), to, c->stream),
