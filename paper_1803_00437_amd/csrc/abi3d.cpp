@@ -110,6 +110,7 @@ struct fdlbm3d_ctx {
     int device = 0;
     int cur = 0;
     int64_t steps = 0;
+    int planes = 0;  // per block of the sweep: tile_planes(p), which searches
     double *sd(size_t off) const { return reinterpret_cast<double *>(scratch + off); }
 };
 
@@ -139,6 +140,7 @@ int fdlbm3d_create(const fdlbm3d_params *p, void *state_a, void *state_b, void *
     fdlbm3d_ctx *c = new (std::nothrow) fdlbm3d_ctx;
     if (!c) return FDLBM_ENOMEM;
     c->p = *p;
+    c->planes = tile_planes(*p);
     c->L = L;
     c->buf[0] = state_a;
     c->buf[1] = state_b;
@@ -201,7 +203,7 @@ int fdlbm3d_step(fdlbm3d_ctx *c, int64_t nsteps)
                                         c->stream),
                     "d3 reference step");
         else
-            HIPCHK3(launch_d3_sweep(p.dtype, in, out, p.nx, p.ny, p.nz, p.s_nu, p.s_e, tile_rows(p), tile_planes(p),
+            HIPCHK3(launch_d3_sweep(p.dtype, in, out, p.nx, p.ny, p.nz, p.s_nu, p.s_e, tile_rows(p), c->planes,
                                     c->stream),
                     "d3 sweep step");
         c->cur = 1 - c->cur;
@@ -283,6 +285,7 @@ int fdlbm3d_autotune(fdlbm3d_ctx *c, int32_t reps, int32_t *out_rows, int32_t *o
     if (p.kernel != FDLBM_KERNEL_REFERENCE) {
         p.tile_rows = best.rows;
         p.tile_planes = best.planes;
+        c->planes = best.planes;
     }
     if (out_rows) *out_rows = tile_rows(p);
     if (out_planes) *out_planes = tile_planes(p);
