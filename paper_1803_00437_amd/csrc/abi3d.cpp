@@ -263,9 +263,15 @@ int fdlbm3d_autotune(fdlbm3d_ctx *c, int32_t reps, int32_t *out_rows, int32_t *o
                                        c->stream);
         return launch_d3_sweep(p.dtype, src, dst, p.nx, p.ny, p.nz, p.s_nu, p.s_e, sh.rows, sh.planes, c->stream);
     };
+    // the planes chosen from the grid, too, unless a shape was asked for: timed last, kept if they are faster
+    const bool rule = p.kernel != FDLBM_KERNEL_REFERENCE && p.tile_rows == 0 && p.tile_planes == 0;
+    const size_t shapes = cand.size();
+    if (rule) cand.push_back({tile_rows(p), tile_planes(p)});
     Shape best{0, 0};
     float best_ms = 0.0f;
-    for (const Shape &sh : cand) {
+    bool keep_rule = false;
+    for (size_t i = 0; i < cand.size(); ++i) {
+        const Shape sh = cand[i];
         if (e == hipSuccess) e = launch(sh);  // warm-up
         if (e == hipSuccess) e = hipEventRecord(e0, c->stream);
         for (int r = 0; r < reps && e == hipSuccess; ++r) e = launch(sh);
@@ -274,7 +280,9 @@ int fdlbm3d_autotune(fdlbm3d_ctx *c, int32_t reps, int32_t *out_rows, int32_t *o
         float ms = 0.0f;
         if (e == hipSuccess) e = hipEventElapsedTime(&ms, e0, e1);
         if (e != hipSuccess) break;
-        if (best_ms == 0.0f || ms < best_ms) {
+        if (i >= shapes) {
+            keep_rule = ms < best_ms;
+        } else if (best_ms == 0.0f || ms < best_ms) {
             best_ms = ms;
             best = sh;
         }
@@ -282,13 +290,15 @@ int fdlbm3d_autotune(fdlbm3d_ctx *c, int32_t reps, int32_t *out_rows, int32_t *o
     if (e0) (void)hipEventDestroy(e0);
     if (e1) (void)hipEventDestroy(e1);
     if (e != hipSuccess) return device_error3(e, "fdlbm3d_autotune");
-    if (p.kernel != FDLBM_KERNEL_REFERENCE) {
+    if (p.kernel == FDLBM_KERNEL_REFERENCE) {
+        best = Shape{tile_rows(p), c->planes};
+    } else if (!keep_rule) {
         p.tile_rows = best.rows;
         p.tile_planes = best.planes;
         c->planes = best.planes;
     }
-    if (out_rows) *out_rows = tile_rows(p);
-    if (out_planes) *out_planes = tile_planes(p);
+    if (out_rows) *out_rows = best.rows;
+    if (out_planes) *out_planes = best.planes;
     if (out_ms) *out_ms = (double)best_ms / reps;
     return FDLBM_OK;
 }

@@ -112,3 +112,32 @@ def test_mrt_single_steps_equal_reference(F, dtype, nx, ny, bc):
         assert bool((getattr(got.buffers, name) == getattr(ref.buffers, name)).all())
     got.close()
     ref.close()
+
+
+def test_d3_autotune_leaves_no_slower_steps(F):
+    """A thin grid runs in many blocks of a few planes (8.4 us per step at 8 x 8 x 64), which none of the
+    tuner's shapes has (16 planes and more: 25 us and more)."""
+    import torch
+
+    sim = F.FdLbm3D(8, 8, 64, dtype="f32", s_nu=1.4, s_e=1.2)
+    sim.set_state(*W.random_state3(8, 8, 64, seed=1, amp=0.02))
+
+    def step_us():
+        best = 1e9
+        for _ in range(5):
+            e0, e1 = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+            e0.record()
+            sim.step(50)
+            e1.record()
+            e1.synchronize()
+            best = min(best, 1e3 * e0.elapsed_time(e1) / 50)
+        return best
+
+    step_us()
+    before = step_us()
+    rows, planes, ms = sim.autotune(reps=5)
+    after = step_us()
+    print(f"  d3 8x8x64: {before:.1f} us, autotune {rows} rows {planes} planes {1e3 * ms:.1f} us, then {after:.1f} us", flush=True)
+    assert rows in (8, 12, 16) and planes in (16, 32, 64, 128)
+    assert after < 1.7 * before
+    sim.close()
