@@ -85,7 +85,7 @@ typedef struct fdlbm_params {
     double force_x, force_y; /* uniform body force per node and step, Strang-split (section 1) */
     int32_t kernel;     /* FDLBM_KERNEL_*                                                     */
     int32_t tile_rows;  /* sweep kernel: rows per wavefront, 2..1024 (0 or 1 = choose); tuning.
-                         * Other than 0, every launch takes one step                          */
+                         * From 2 on, every launch takes one step                             */
     int32_t check_every;/* > 0: fdlbm_step / mrt_step scan the state for non-finite values
                          * every check_every steps and return FDLBM_EUNSTABLE if one is found
                          * (this synchronises the stream at each check)                       */

@@ -90,7 +90,7 @@ StepPlan step_plan(const fdlbm_params &p, double s_q)
 {
     StepPlan plan;
     const bool disk = p.bc == FDLBM_BC_DISK, fd = three_words(p.scheme);
-    if (uses_reference(p) || p.tile_rows != 0 || p.lane_cols != 0 || (disk && !fd)) return plan;
+    if (uses_reference(p) || p.tile_rows > 1 || (fd && p.lane_cols != 0) || (disk && !fd)) return plan;
     const bool tiles = p.kernel == FDLBM_KERNEL_AUTO;
     if (fd) {
         const FdArgs a = fd_args(p);

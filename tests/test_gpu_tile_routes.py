@@ -141,3 +141,33 @@ def test_d3_autotune_leaves_no_slower_steps(F):
     assert rows in (8, 12, 16) and planes in (16, 32, 64, 128)
     assert after < 1.7 * before
     sim.close()
+
+
+def launches(F, n, nx, ny, **kw):
+    """Kernel launches that a call of n steps records."""
+    import ctypes
+
+    import torch
+
+    sim = F.FdLbm(nx, ny, s_xx=1.3, s_e=1.1, stream=torch.cuda.Stream(), **kw)
+    sim.set_state(*random_state(nx, ny))
+    sim.step(n)
+    torch.cuda.synchronize()
+    hip = ctypes.CDLL("libamdhip64.so")
+    stream, graph, count = ctypes.c_void_p(sim.stream.cuda_stream), ctypes.c_void_p(), ctypes.c_size_t()
+    assert hip.hipStreamBeginCapture(stream, 1) == 0  # thread-local
+    sim.step(n)
+    assert hip.hipStreamEndCapture(stream, ctypes.byref(graph)) == 0
+    assert hip.hipGraphGetNodes(graph, None, ctypes.byref(count)) == 0
+    hip.hipGraphDestroy(graph)
+    sim.close()
+    return count.value
+
+
+@pytest.mark.parametrize("kw", [dict(dtype="f64"), dict(dtype="f32", scheme="mrt"), dict(dtype="f32", scheme="lwacm"),
+                                dict(dtype="f32", kernel="sweep")])
+def test_one_row_per_tile_is_no_choice(F, kw):
+    """tile_rows = 1 leaves the choice to the library, as 0 does; other rows are those of one-step launches."""
+    n = [launches(F, 12, 200, 150, tile_rows=rows, **kw) for rows in (0, 1, 4)]
+    print(f"  {kw}: launches of 12 steps {n}", flush=True)
+    assert n[0] == n[1] < n[2] == 12
