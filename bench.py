@@ -45,13 +45,26 @@ def bytes_per_node(scheme, dtype):
     return 2 * words * {"f64": 8, "f32": 4, "f16": 2, "f16sr": 2}[dtype]
 
 
-def steps_per_launch(scheme, dtype, stencil, nodes):
-    """Time steps that one launch takes of a grid of the sizes below (the periodic ones and those
-    between walls): its state crosses HBM once for all of them.  Smaller grids stay in registers
-    for several steps: 1 then, the bytes of one step."""
-    if nodes < 2048 * 2048 or dtype == "f16sr":
-        return 1
-    return {"mrt": 5, "lwacm": 3, "fd": 2}[scheme]
+def count_launches(F, torch, nx, ny, steps, kw):
+    """Launches that the library deals a call of `steps` steps to: the call is recorded, not run, on a
+    context of its own, and the kernels in the record are counted."""
+    import ctypes
+
+    sim = F.FdLbm(nx, ny, stream=torch.cuda.Stream(), **kw)
+    torch.cuda.synchronize()
+    hip = ctypes.CDLL("libamdhip64.so")
+    stream, graph, count = ctypes.c_void_p(sim.stream.cuda_stream), ctypes.c_void_p(), ctypes.c_size_t()
+    ok = hip.hipStreamBeginCapture(stream, 1) == 0  # of this thread only
+    if ok:
+        sim.step(steps)
+        ok = hip.hipStreamEndCapture(stream, ctypes.byref(graph)) == 0
+    ok = ok and hip.hipGraphGetNodes(graph, None, ctypes.byref(count)) == 0
+    if graph:
+        hip.hipGraphDestroy(graph)
+    sim.close()
+    if not ok:
+        raise RuntimeError("the steps could not be recorded")
+    return count.value
 
 
 def run_case(F, torch, init, scheme, dtype, stencil, steps, warmup, kernel, with_diag, tile_rows=0, lane_cols=0,
@@ -66,12 +79,18 @@ def run_case(F, torch, init, scheme, dtype, stencil, steps, warmup, kernel, with
         kw["stencil"] = stencil
     elif scheme == "mrt":
         kw["quartic"] = True
+    # the state crosses HBM once per launch (in the disk a step is the ghost fill and the step)
+    launches = steps if bc == "disk" else count_launches(F, torch, nx, ny, steps, kw)
     sim = F.FdLbm(nx, ny, **kw)
     sim.set_state(*init)
     shape = None
     if autotune and not (tile_rows or lane_cols):
-        # tile shape picked by the library's tuner on this grid (untimed set-up)
+        # tile shape of one-step launches, picked by the library's tuner on this grid (untimed set-up, which
+        # also brings the clocks up: 20 steps of 8192^2 after 5 take 0.25 ms each from idle, 0.20 after it);
+        # launches of several steps choose their own shape
         shape = sim.autotune(reps=10)[:2]
+        if launches < steps:
+            shape = None
     sim.step(warmup)
     torch.cuda.synchronize()
     # kernel-only region, timed with HIP events on the library's stream
@@ -96,13 +115,13 @@ def run_case(F, torch, init, scheme, dtype, stencil, steps, warmup, kernel, with
     diag = sim.diagnostics()
     sim.close()
     nodes = nx * ny
-    per_launch = 1 if bc == "disk" or kernel == "reference" else steps_per_launch(scheme, dtype, stencil, nodes)
+    per_launch = steps / launches
     return {
         "ms_per_step": wall_ms,
         "kernel_ms": kernel_ms,
         "mlups": nodes / (wall_ms * 1e3),
         "kernel_mlups": nodes / (kernel_ms * 1e3),
-        "steps_per_launch": per_launch,
+        "steps_per_launch": round(per_launch, 3),
         "alg_gbs": bytes_per_node(scheme, dtype) * nodes / (per_launch * kernel_ms * 1e6),
         "nonfinite": diag["nonfinite"],
         "tile": {"lane_cols": shape[0], "tile_rows": shape[1]} if shape else None,
@@ -515,7 +534,7 @@ def main():
         # the rate that one step per launch would need at this speed: above the copy's, so memory is no longer the bound
         "one_step_equivalent_gbs": round(achieved * per_launch, 1),
     }
-    alu = alu_roofline("fd3_f32", kernel_ms, n * n) if per_launch == 2 else None
+    alu = alu_roofline("fd3_f32", kernel_ms, n * n) if round(per_launch) == 2 else None
     line = {
         "metric": METRIC,
         "value": round(main_case["mlups"], 1),

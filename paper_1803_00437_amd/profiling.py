@@ -289,7 +289,7 @@ def _run(cmd, log, limit, kill_signal):
 def valu_summary(raw, out_md, command):
     """VALU busy of each pass: SQ_ACTIVE_INST_VALU x 4 cycles (a wave64 VALU instruction holds
     a SIMD for 4 cycles; packed FP32 is not used) over the SIMD-cycles of the dispatch
-    (GRBM_GUI_ACTIVE is summed over the XCDs), and VALU instructions per node of a launch
+    (GRBM_GUI_ACTIVE is summed over the XCDs; the share overstates by up to 6 %), and VALU instructions per node of a launch
     (SQ_INSTS_VALU x 64 lanes / nodes) and per node and step."""
     lines = ["# rocprofv3 VALU counters of the step kernels", "",
              "Written by: `python -m paper_1803_00437_amd.profiling collect --raw <dir> --out profiles`", "",
@@ -312,7 +312,9 @@ def valu_summary(raw, out_md, command):
                      insts, active, cycles * XCDS, waves, busy, insts * 64 / nodes, VALU_STEPS[name]))
     lines += ["", "Per dispatch of the step kernel (for the batch, summed over one of each of its kernels), averaged "
               "over the dispatches. VALU busy = SQ_ACTIVE_INST_VALU x 4 / (1024 SIMDs x GRBM_GUI_ACTIVE / 8); "
-              "per node = SQ_INSTS_VALU x 64 / nodes of the grid; a dispatch takes `steps` time steps.", "",
+              "per node = SQ_INSTS_VALU x 64 / nodes of the grid; a dispatch takes `steps` time steps. The busy "
+              "share overstates: it reads up to 106 %, so the instructions do not all hold a SIMD for 4 cycles of "
+              "this clock. The sounder figure is the bench's instructions per second against the issue rate.", "",
               "| kernel | dispatches | SQ_INSTS_VALU | SQ_ACTIVE_INST_VALU | GRBM_GUI_ACTIVE (sum of 8 XCDs) | "
               "SQ_WAVES | VALU busy | VALU instructions per node | steps | per node and step |",
               "|---|---|---|---|---|---|---|---|---|---|"]
