@@ -237,6 +237,9 @@ int fdlbm_set_step_count(fdlbm_ctx *c, int64_t steps);
  * current state and writes the spare buffer, which the next step overwrites.  Synchronises
  * the stream.  The chosen shape goes to *out_lane_cols and *out_tile_rows (0 where the
  * kernel has no such parameter) and its time per step in ms to *out_ms; each may be NULL.
+ * That is the time of a step launched alone, not of one among many.  Given to a new context as
+ * tile_rows and lane_cols the shape makes every launch take one step, which is slower for
+ * calls of many steps; leave both 0 there.
  * FDLBM_EINVAL for a NULL context or reps out of range, FDLBM_EDEVICE on a HIP error. */
 int fdlbm_autotune(fdlbm_ctx *c, int32_t reps, int32_t *out_lane_cols, int32_t *out_tile_rows, double *out_ms);
 
@@ -284,7 +287,7 @@ int fdlbm_batch_create(const fdlbm_instance *instances, int32_t count, int32_t d
 int fdlbm_batch_set_state(fdlbm_batch *b, int32_t i, const double *drho, const double *jx, const double *jy);
 int fdlbm_batch_get_state(fdlbm_batch *b, int32_t i, double *drho, double *jx, double *jy);
 
-/* Advance every instance by nsteps (launches of two or three steps for all instances).  With
+/* Advance every instance by nsteps (launches of one, two or three steps for all instances).  With
  * sample_every > 0 (nsteps must be a multiple), A(t) of every instance is recorded after
  * each sample_every steps; with use_graph != 0 each chunk of sample_every steps plus its
  * sample is captured once in a HIP graph and replayed.  Asynchronous. */
@@ -293,8 +296,9 @@ int fdlbm_batch_step(fdlbm_batch *b, int64_t nsteps, int32_t sample_every, int32
 /* The same steps with one launch per instance per step (the comparison path). */
 int fdlbm_batch_step_per_instance(fdlbm_batch *b, int64_t nsteps);
 
-/* Tile-height tuning of the launches of one step (those left over by launches of two or
- * three): times `reps` (1..10000) steps of all instances for 4, 6, 8, 12 and 16 rows per wavefront, keeps the fastest (it is 8
+/* Tile-height tuning of the launches of one step (calls of one step, steps left over by
+ * launches of two or three, and one launch per instance): times `reps` (1..10000) steps of all
+ * instances for 4, 6, 8, 12 and 16 rows per wavefront, keeps the fastest (it is 8
  * until tuned) and drops the cached graph replays, which are captured again on the next
  * fdlbm_batch_step.  No step is taken (timed launches write the spare buffer).
  * Synchronises the stream.  *out_rows, *out_ms (may be NULL): the choice and its time

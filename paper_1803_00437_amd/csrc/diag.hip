@@ -2,7 +2,8 @@
 // device storage dtype.
 //
 // The reduction is deterministic: DIAG_BLOCKS blocks (one per row on a lower grid) walk the
-// rows, each block reduces its threads in a fixed tree (wavefront shuffles, then LDS) and writes one partial; a single block then reduces the partials in order.
+// rows, each block reduces its threads in a fixed tree (wavefront shuffles, then LDS) and writes
+// one partial; a single block then reduces the partials in order.
 // Quantities (section 3-a uses the correlation A(t) = <J(t), J0>/<J0, J0>):
 //   [0] sum drho, [1] sum jx, [2] sum jy, [3] 1/2 sum |J|^2/rho, [4] max |J|,
 //   [5] sum J.J0, [6] sum J0.J0, [7] count of nodes with a non-finite field.

@@ -47,7 +47,7 @@ __global__ void __launch_bounds__(64 * WV) fd_batch_kernel(const T *__restrict__
 }
 
 // K steps of every instance: each wavefront looks up its instance, columns and rows and runs the
-// body of fd_fused_kernel.  Two columns per lane where the width allows, else one: a strip of 512
+// body of fd_fused_kernel.  Two columns per lane where the width allows, else one: a strip of 64
 // four-column lanes fits the widths of small grids badly (32 .. 512 columns: 62 % of the columns
 // computed are stored, 81 % with two), and two leave registers for more wavefronts.  128 grids of
 // 32 .. 512 columns (12 M nodes), FP32: 97 us per step one by one in two classes.

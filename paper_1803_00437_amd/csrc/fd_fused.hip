@@ -3,8 +3,8 @@
 // wavefront.
 //
 // Measured (us per step, one by one and here): FP32 8192^2 294 and 190, now bound by instruction
-// issue (vector units 100 % busy, 105 instructions per node and step of which the halo lanes, the
-// part-filled last strip and the rows formed twice are 15); FP64 4096^2 148 and 98 (80 % busy at a
+// issue (94 % of the rate at 2.4 GHz; 105 instructions per node and step of which the halo lanes, the
+// part-filled last strip and the rows formed twice are 10); FP64 4096^2 148 and 98 (80 % busy at a
 // clock that falls to 2.1-2.2 GHz); FP16 6002 x 4095 89 and 76; walls and force 16384 x 1024 FP32 82
 // and 60; LW-ACM 8192^2 FP32 283 and 123; 5-point 1001 x 777 FP32 22.7 and 12.8.
 #include <algorithm>

@@ -381,7 +381,7 @@ __global__ void __launch_bounds__(256) mrt_xi_kernel(const T *__restrict__ in, T
 // their way up wait for the next tick as that row's downward ones.
 //
 // What bounds it (8192^2 FP32): one step moved 18 words per node and took 866 us; five take 5 x 232 us,
-// 109 vector instructions per node and step with the halo (93 % busy) and 4.9 TB/s.  What a stage keeps is 9 CPL
+// 109 vector instructions per node and step with the halo (80 % of the issue rate at 2.4 GHz) and 4.2 TB/s.  What a stage keeps is 9 CPL
 // registers; with every stage in registers three steps spilled (349 us per step against 340), so
 // the first one or two stages stay there and the others in LDS (9 KB per stage and wavefront: two
 // blocks of four wavefronts fit a compute unit up to two such stages).
