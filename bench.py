@@ -79,8 +79,9 @@ def run_case(F, torch, init, scheme, dtype, stencil, steps, warmup, kernel, with
         kw["stencil"] = stencil
     elif scheme == "mrt":
         kw["quartic"] = True
-    # the state crosses HBM once per launch (in the disk a step is the ghost fill and the step)
-    launches = steps if bc == "disk" else count_launches(F, torch, nx, ny, steps, kw)
+    # the state crosses HBM once per launch (a step in the disk is the ghost fill and the step, one of the
+    # reference kernels two passes)
+    launches = steps if bc == "disk" or kernel == "reference" else count_launches(F, torch, nx, ny, steps, kw)
     sim = F.FdLbm(nx, ny, **kw)
     sim.set_state(*init)
     shape = None
